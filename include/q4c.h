@@ -65,7 +65,12 @@ enum {
  * V always runs on FP64 MFMA (its elements reach ~1e2 Ha, beyond what FP32
  * accumulation can hold to 1e-8 Ha).  The W parts (9 of the 10 P n^2 flops
  * of a batch):
- *   Q4C_PREC_F64        FP64 MFMA, FP64 accumulation.
+ *   Q4C_PREC_F64        FP64 MFMA, FP64 accumulation.  The nine products of
+ *                       two gradients a, b come from six sums: D_m = a_m b_m
+ *                       and M_x = (a_y - a_z)(b_y + b_z) (and cyclic), with
+ *                       Ws = D_x + D_y + D_z, Wso_x = M_x - (D_y - D_z), so the
+ *                       rounding of Wso_x is relative to the magnitudes of
+ *                       the products in M_x and D_y, D_z.
  *   Q4C_PREC_F32        FP32 MFMA on FP32 operands (sqrt|w v| times the
  *                       gradient, formed in FP64 and rounded once; the row
  *                       operand carries the sign of w v);

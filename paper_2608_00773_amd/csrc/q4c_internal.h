@@ -24,6 +24,15 @@ struct WorkItem {
   int16_t ti, tj;
 };
 
+// Item of one wave of the FP64 forward contraction: the 16 x 16 blocks
+// (rb, cb .. cb + nb - 1) of a batch's function matrix, rb <= cb (block indices).
+struct BlockItem {
+  int32_t batch;
+  uint16_t rb;
+  uint16_t cb : 15, wide : 1;
+};
+static_assert(sizeof(BlockItem) == 8, "BlockItem is 8 bytes");
+
 // Everything a kernel needs about the plan, as raw device pointers.
 struct DevPlan {
   // basis
@@ -100,6 +109,7 @@ struct Pass {
   int64_t partial_len;   // doubles (adjoint partials, stored after the staging)
   int64_t panel_len;     // doubles (operand panels, stored after the partials)
   int64_t ap0, ap1;      // adjoint positions (d_adjpos, d_adjpos_cost)
+  int64_t bi0, bi1;      // forward block items (d_blocks, d_blocks_cost)
 };
 
 // Scalar -> spinor transformation (Eq. 33): coefficients of one spinor type
@@ -208,6 +218,8 @@ struct q4c_plan {
   double *d_om = nullptr;  // [n_active + 16] point weights w_g v_g of the current call
   q4c::AdjPos *d_adjpos = nullptr;       // adjoint positions per pass, batch order
   q4c::AdjPos *d_adjpos_cost = nullptr;  // the same, work items by decreasing cost
+  q4c::BlockItem *d_blocks = nullptr;       // forward block items per pass, batch order
+  q4c::BlockItem *d_blocks_cost = nullptr;  // the same by decreasing cost
   double *d_coef_fold = nullptr;  // [5][store_len + 16] the adjoint's coefficients of the current call (k_coef_fold)
   double *d_ucoef = nullptr;         // ket-potential tables (q4c_plan_set_ket_potential)
   int64_t *d_shell_us_off = nullptr;
@@ -330,6 +342,8 @@ int launch_spinor_transform(const q4c_plan *pl, const double *hs_large, const do
 // k_contract_hs over work items [w0, w0 + nw) of a pass (q4c_hs_kernels.hip)
 int launch_contract_hs(const q4c_plan *p, int64_t w0, int64_t nw, const int32_t *order, const double *panel,
                        unsigned *tickets, unsigned grid, hipStream_t s);
+// FP64 contraction of all five parts over the block items of a pass (q4c_forward_kernels.hip)
+int launch_forward(const q4c_plan *p, const Pass &ps, const double *panel, unsigned *tickets, hipStream_t s);
 int launch_coef_from_spinor(const q4c_plan *p, const double *spin_d, double *coef_out, hipStream_t s);
 int launch_check_finite(const q4c_plan *p, const double *v, hipStream_t s, bool *finite);
 

@@ -6,17 +6,17 @@
 //  k_om              w_g v_g per active point (the weighting of Eq. 29).
 //  k_panel           per (batch, 64-function tile): phi and grad phi at all
 //                    batch points into the batch's operand panel (HBM).
-//  k_contract<prec>  per (batch, tile ti <= tj) work item: 16-point chunks of
-//                    the two tiles' panels are copied into LDS (the column
-//                    operand weighted by w v on the way) and the five
-//                    weighted products
+//  k_contract_*      per (batch, tile ti <= tj) work item, or smaller items of
+//                    it: the weighted products
 //                        V  = Phi^T diag(w v) Phi
 //                        Gs = sum_a dPhi_a^T diag(w v) dPhi_a
 //                        Gm = dPhi_b^T diag(w v) dPhi_c - dPhi_c^T diag(w v) dPhi_b
 //                    accumulate on MFMA (Eq. 29 restricted to the batch,
-//                    Eq. 31).  The lower atom-block triangle follows from
-//                    (anti)symmetry.  Results go to a staging buffer laid
-//                    out per (batch, atom pair).
+//                    Eq. 31): the reduced precisions, V alone and the vector
+//                    ALU baseline here, FP64 in q4c_forward_kernels.hip.  The
+//                    lower atom-block triangle follows from (anti)symmetry.
+//                    Results go to a staging buffer laid out per (batch, atom
+//                    pair).
 //  k_reduce          deterministic batch-to-global sum: every stored atom
 //                    pair adds its staged blocks in batch order (FP64).
 //  k_spinor          2x2-spinor assembly of the W and V blocks.
@@ -472,34 +472,24 @@ __global__ __launch_bounds__(256) void k_panel(DevPlan d, const WorkItem *tiles,
   }
 }
 
-// Modes of the FP64 contraction: all five parts, or V alone (phi only: the
-// V part of the split precisions, and V-only calls).  V alone does one MFMA
-// per row and column value, too little work per chunk to hide the next
-// chunk's loads at two workgroups per CU: its 16-point chunks (33 KB of LDS)
-// and 110 VGPRs let four share a CU.
-enum { MODE_F64 = 0, MODE_V = 1 };
-
+// V alone (the V part of F32 and SPLIT_F32, and V-only calls): one MFMA per
+// row and column value, too little work per chunk to hide the next chunk's
+// loads at two workgroups per CU: its 16-point chunks (33 KB of LDS) and 110
+// VGPRs let four share a CU.
 // Work item positions 0..nw-1 of a pass map to work items w0 + order[w0 + pos]
 // (order != NULL: cost-sorted) or w0 + pos.  tickets == NULL: one workgroup
 // per position; otherwise a persistent loop (next_item).
-template <int MODE, bool PERSIST>
-__global__ __launch_bounds__(NT, MODE == MODE_V ? 4 : 2) void k_contract(
+template <bool PERSIST>
+__global__ __launch_bounds__(NT, 4) void k_contract_v(
     DevPlan d, const WorkItem *work, const int32_t *order, int64_t w0, int64_t nw, const double *om,
     const double *panel, double *staging, unsigned *tickets) {
-  constexpr bool VONLY = MODE == MODE_V;
-  constexpr int NQ = VONLY ? 1 : 4;        // panel components multiplied
-  constexpr int NP = VONLY ? 1 : 5;        // parts accumulated
   // Chunks of CH points in two LDS buffers, the next chunk's DMA in flight
   // while this one is multiplied (one barrier per chunk)
-  constexpr int CH = VONLY ? 16 : 8;
-  constexpr int RPQ = CH / 2;              // LDS rows per component
-  constexpr int BUFD = NQ * RPQ * DROW;    // doubles per chunk image
+  constexpr int CH = 16;
+  constexpr int RPQ = CH / 2;              // LDS rows: point pairs
+  constexpr int BUFD = RPQ * DROW;         // doubles per chunk image
   __shared__ double sa[2 * BUFD], sb[2 * BUFD];
   __shared__ int64_t s_pos;
-  // slot data of the tile's 64 rows and 64 columns for the epilogue, loaded
-  // when the work item starts (slot -1: beyond n)
-  __shared__ int s_fslot[2 * T], s_ffn[2 * T], s_fnf[2 * T];
-  __shared__ int64_t s_frow[2 * T];
   int64_t pos = PERSIST ? next_item(tickets, nw, order != nullptr, &s_pos)
                         : (order ? (int64_t)blockIdx.x : xcd_map(blockIdx.x, nw));
   while (!PERSIST || pos < nw) {
@@ -520,13 +510,9 @@ __global__ __launch_bounds__(NT, MODE == MODE_V ? 4 : 2) void k_contract(
   bool act[4];
   wave_blocks(r0, c0, n, wave, brow, bcol, act);
 
-  dbl4 acc[4][NP];
+  dbl4 acc[4];
 #pragma unroll
-  for (int sl = 0; sl < 4; ++sl)
-#pragma unroll
-    for (int q = 0; q < NP; ++q) acc[sl][q] = dbl4{0.0, 0.0, 0.0, 0.0};
-
-  const double cp = d.cprime;
+  for (int sl = 0; sl < 4; ++sl) acc[sl] = dbl4{0.0, 0.0, 0.0, 0.0};
   // K steps go in pairs over 8 points: K index lk of the first step of the
   // pair is point 2 lk of the 8, of the second point 2 lk + 1 (one 16-byte
   // LDS read per operand gives a lane both).  w v at the points this lane's
@@ -542,20 +528,8 @@ __global__ __launch_bounds__(NT, MODE == MODE_V ? 4 : 2) void k_contract(
     }
   };
   load_om(0);
-  dma_chunk<NT, CH, T, DROW, NQ>(pb, plane, np, r0, 0, sa);
-  dma_chunk<NT, CH, T, DROW, NQ>(pb, plane, np, c0, 0, sb);
-  if (!VONLY && tid < 2 * T) {  // visible from the first chunk's barrier on
-    const int lf = tid < T ? r0 + tid : c0 + tid - T;
-    int64_t v = 0, ro = 0;
-    if (lf < n) {
-      v = d.loc_info[f0 + lf];
-      ro = d.loc_rowoff[f0 + lf];
-    }
-    s_fslot[tid] = lf < n ? (int)(v & 0xFFFFF) : -1;
-    s_ffn[tid] = (int)((v >> 20) & 0xFFFFF);
-    s_fnf[tid] = (int)(v >> 40);
-    s_frow[tid] = ro;
-  }
+  dma_chunk<NT, CH, T, DROW, 1>(pb, plane, np, r0, 0, sa);
+  dma_chunk<NT, CH, T, DROW, 1>(pb, plane, np, c0, 0, sb);
   for (int k0 = 0; k0 < Pp; k0 += CH) {
     const int bo = ((k0 / CH) & 1) * BUFD;  // this chunk's buffer
     __builtin_amdgcn_s_waitcnt(0);  // this thread's loads of this chunk have landed
@@ -566,77 +540,43 @@ __global__ __launch_bounds__(NT, MODE == MODE_V ? 4 : 2) void k_contract(
     if (k0 + CH < Pp) {
       const int nbo = BUFD - bo;
       load_om(k0 + CH);
-      dma_chunk<NT, CH, T, DROW, NQ>(pb, plane, np, r0, (k0 + CH) >> 2, sa + nbo);
-      dma_chunk<NT, CH, T, DROW, NQ>(pb, plane, np, c0, (k0 + CH) >> 2, sb + nbo);
+      dma_chunk<NT, CH, T, DROW, 1>(pb, plane, np, r0, (k0 + CH) >> 2, sa + nbo);
+      dma_chunk<NT, CH, T, DROW, 1>(pb, plane, np, c0, (k0 + CH) >> 2, sb + nbo);
     }
     const double *ca = sa + bo, *cb = sb + bo;
 #pragma unroll
     for (int kp = 0; kp < CH / 8; ++kp) {
       // image row 4 kp + lk holds points 8 kp + 2 lk and 8 kp + 2 lk + 1 of
-      // the chunk; the column operand takes its weight w v there (the
-      // weighting of Eq. 29)
+      // the chunk; the row operand takes the weight w v there, as in k_forward
       const int row = 4 * kp + lk;
 #pragma unroll
       for (int sl = 0; sl < 4; ++sl) {
         if (!act[sl]) continue;  // wave-uniform
-        dbl2 ap[NQ], bp[NQ];
+        const dbl2 ap = *reinterpret_cast<const dbl2 *>(&ca[row * DROW + 2 * (brow[sl] + li16)]);
+        const dbl2 bp = *reinterpret_cast<const dbl2 *>(&cb[row * DROW + 2 * (bcol[sl] + li16)]);
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-          ap[q] = *reinterpret_cast<const dbl2 *>(&ca[(q * RPQ + row) * DROW + 2 * (brow[sl] + li16)]);
-          bp[q] = *reinterpret_cast<const dbl2 *>(&cb[(q * RPQ + row) * DROW + 2 * (bcol[sl] + li16)]);
-        }
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-        const double omk = omv[2 * kp + h];
-        double av[NQ], bv[NQ];
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-          av[q] = ap[q][h];
-          bv[q] = bp[q][h] * omk;
-        }
-        acc[sl][0] = mfma64(av[0], bv[0], acc[sl][0]);
-        if (!VONLY) {
-          acc[sl][1] = mfma64(av[1], bv[1], acc[sl][1]);
-          acc[sl][2] = mfma64(av[2], bv[3], acc[sl][2]);
-          acc[sl][3] = mfma64(av[3], bv[1], acc[sl][3]);
-          acc[sl][4] = mfma64(av[1], bv[2], acc[sl][4]);
-          acc[sl][1] = mfma64(av[2], bv[2], acc[sl][1]);
-          acc[sl][2] = mfma64(-av[3], bv[2], acc[sl][2]);
-          acc[sl][3] = mfma64(-av[1], bv[3], acc[sl][3]);
-          acc[sl][4] = mfma64(-av[2], bv[1], acc[sl][4]);
-          acc[sl][1] = mfma64(av[3], bv[3], acc[sl][1]);
-        }
-        }
+        for (int h = 0; h < 2; ++h) acc[sl] = mfma64(ap[h] * omv[2 * kp + h], bp[h], acc[sl]);
       }
     }
   }
-  // write the computed blocks to the staged atom-pair blocks
+  // write the computed blocks to the staged atom-pair blocks (slot data
+  // looked up here: tables loaded into LDS up front compiled to 256 VGPRs
+  // instead of 148 and ran 45% slower)
 #pragma unroll
   for (int sl = 0; sl < 4; ++sl) {
     if (!act[sl]) continue;
     const int cbk = c0 + bcol[sl];
     const int lj = cbk + li16;
     if (lj >= n) continue;
-    const int cj = T + bcol[sl] + li16;
-    // V alone keeps the two dependent lookups here: with the tables it
-    // compiled to 256 VGPRs instead of 148 and ran 45% slower
-    const SlotInfo sj = VONLY ? slot_of(d, f0, d.batch_slot_off[b], lj)
-                              : SlotInfo{s_fslot[cj], s_ffn[cj], s_fnf[cj], s_frow[cj]};
+    const SlotInfo sj = slot_of(d, f0, d.batch_slot_off[b], lj);
     const int rb = r0 + brow[sl];
-    const bool upper = rb < cbk;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       // FP64 MFMA rows lk + 4 r
       const int li = rb + d_row_f64(lk, r);
       if (li < n) {
-        const int ri = li - r0;
-        const SlotInfo si = VONLY ? slot_of(d, f0, d.batch_slot_off[b], li)
-                                  : SlotInfo{s_fslot[ri], s_ffn[ri], s_fnf[ri], s_frow[ri]};
-        double vals[5];
-        vals[0] = acc[sl][0][r];
-#pragma unroll
-        for (int q = 1; q < NP; ++q) vals[q] = cp * acc[sl][q][r];
-        stage_store<0, NP>(staging, si, sj, li, lj, upper, vals);
+        const double v = acc[sl][r];
+        stage_store<0, 1>(staging, slot_of(d, f0, d.batch_slot_off[b], li), sj, li, lj, rb < cbk, &v);
       }
     }
   }
@@ -647,7 +587,7 @@ __global__ __launch_bounds__(NT, MODE == MODE_V ? 4 : 2) void k_contract(
 
 // The plain FP64 baseline (precision F64_VALU): the five parts of a work
 // item on the vector ALU, no matrix cores.  Same work items, FP64 panels,
-// chunk DMA and staging as k_contract<MODE_F64>; each thread owns a 4 x 4
+// chunk DMA and staging as the other contractions; each thread owns a 4 x 4
 // patch of the 64 x 64 tile (rows 4 (t / 16), columns 4 (t % 16)) and adds
 // every point's ten products to its 80 FP64 sums with fused multiply-adds,
 // point after point.  Patches in blocks no work item computes (below the
@@ -770,8 +710,8 @@ __global__ __launch_bounds__(NT, 1) void k_contract_valu(DevPlan d, const WorkIt
 
 // The four W parts on FP32 MFMA (precisions F32 and SPLIT_F32), from the FP32
 // gradient planes of a PK_F32 / PK_SPLIT panel; V runs beside it on FP64
-// (k_contract<MODE_V>).  Same work items, wave blocks and staging as
-// k_contract.  F32: both operands are sqrt|w v| times the gradient (formed in
+// (k_contract_v).  Same work items, wave blocks and staging as
+// k_contract_v.  F32: both operands are sqrt|w v| times the gradient (formed in
 // FP64, rounded to FP32 once in the panel), the row operand with the sign of
 // w v.  Per 16 points, every element's FP32 partial sum (of at most 48
 // products: 16 points x 3) is converted to FP64 and added to an FP64 running
@@ -1169,10 +1109,10 @@ __global__ __launch_bounds__(NT, 2) void k_contract_b3(DevPlan d, const WorkItem
           if (ACT[c]) bp[c] = *reinterpret_cast<const dbl2 *>(&dc[bi][row * CDW + 2 * (16 * c + l16)]);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const double omk = som[bi][8 * kp + 2 * lk + h];
+          const double apw = ap[h] * som[bi][8 * kp + 2 * lk + h];
 #pragma unroll
           for (int c = 0; c < 2; ++c)
-            if (ACT[c]) accv[c] = mfma64(ap[h], bp[c][h] * omk, accv[c]);
+            if (ACT[c]) accv[c] = mfma64(apw, bp[c][h], accv[c]);
         }
       }
       // W: this chunk's FP32 sums, Ws then (+, -) of Wso_x, Wso_y, Wso_z
@@ -1981,8 +1921,7 @@ int launch_integrate(const q4c_plan *p, const double *v, int precision, uint32_t
         hipLaunchKernelGGL(k_contract_valu, dim3((unsigned)nw), dim3(NT), 0, s, p->dp, p->d_work, order, ps.w0, nw,
                            p->d_om, panel, p->d_staging, (unsigned *)nullptr);
       } else if (full64) {
-        launch_work(k_contract<MODE_F64, true>, k_contract<MODE_F64, false>, grid, pers, s, p->dp, p->d_work, order,
-                    ps.w0, nw, p->d_om, panel, p->d_staging, tick_a);
+        if ((rc = launch_forward(p, ps, panel, tick_a, s)) != Q4C_OK) return rc;
       } else if (fused_b3) {
         // one workgroup per column half of each work item
         const unsigned grid2 = (unsigned)(pers ? std::min<int64_t>(cfg.persistent, 2 * nw) : 2 * nw);
@@ -1993,7 +1932,7 @@ int launch_integrate(const q4c_plan *p, const double *v, int precision, uint32_t
           // four V-only workgroups fit on a CU, twice the other contraction
           // kernels' two: twice the persistent workgroups
           const unsigned grid_v = (unsigned)(pers ? std::min<int64_t>(2 * (int64_t)cfg.persistent, nw) : nw);
-          launch_work(k_contract<MODE_V, true>, k_contract<MODE_V, false>, grid_v, pers, s, p->dp, p->d_work, order,
+          launch_work(k_contract_v<true>, k_contract_v<false>, grid_v, pers, s, p->dp, p->d_work, order,
                       ps.w0, nw, p->d_om, panel, p->d_staging, tick_a);
         }
         if (wantW && precision == Q4C_PREC_SPLIT_F32)

@@ -495,7 +495,6 @@ int build_host(q4c_plan *p, const q4c_basis *b, const q4c_grid *g, const std::ve
     }
     int nt = (nb_fn + T - 1) / T;
     int64_t bpart = 2 * (int64_t)(nt * (nt + 1) / 2) * (g1 - g0);  // two column halves per work item
-    // panel: 4 FP64 components (or phi in FP64 and up to 6 FP32 gradient planes: as much)
     // panel: 4 FP64 planes (the largest kind)
     int64_t bpanel = 4 * q4c::pad16(g1 - g0) * q4c::pad16(nb_fn);
     if (bt > cur.b0 && (staging + partial + panel + bstage + bpart + bpanel > budget_doubles)) close_pass(bt);
@@ -722,6 +721,41 @@ int build_device(q4c_plan *p) {
     }
     if ((rc = upload(p, ab, &p->d_adjpos)) != Q4C_OK) return rc;
     if ((rc = upload(p, ac, &p->d_adjpos_cost)) != Q4C_OK) return rc;
+  }
+  {
+    // forward block items: per pair of block columns (the last may be single)
+    // its rows down to the diagonal, so that neighbouring items share their
+    // columns; and the same by decreasing cost (points x blocks), counted
+    // into buckets
+    std::vector<q4c::BlockItem> ib, ic;
+    for (q4c::Pass &ps : p->passes) {
+      ps.bi0 = (int64_t)ib.size();
+      int64_t top = 0;
+      auto cost = [&](const q4c::BlockItem &x) {
+        return (q4c::pad16(p->batch_pt_off[x.batch + 1] - p->batch_pt_off[x.batch]) >> 4) * (1 + x.wide);
+      };
+      for (int64_t b = ps.b0; b < ps.b1; ++b) {
+        const int m = (int)(q4c::pad16(p->batch_fn_off[b + 1] - p->batch_fn_off[b]) >> 4);
+        for (int c = 0; c < m; c += 2)
+          for (int r = 0; r <= std::min(c + 1, m - 1); ++r) {
+            q4c::BlockItem x{};
+            x.batch = (int32_t)b;
+            x.rb = (uint16_t)r;
+            x.cb = (uint16_t)std::max(c, r);
+            x.wide = r <= c && c + 1 < m;
+            ib.push_back(x);
+            top = std::max(top, cost(x));
+          }
+      }
+      ps.bi1 = (int64_t)ib.size();
+      std::vector<int64_t> at(top + 2, 0);
+      for (int64_t i = ps.bi0; i < ps.bi1; ++i) at[top - cost(ib[i]) + 1]++;
+      for (int64_t k = 0; k <= top; ++k) at[k + 1] += at[k];
+      ic.resize(ib.size());
+      for (int64_t i = ps.bi0; i < ps.bi1; ++i) ic[ps.bi0 + at[top - cost(ib[i])]++] = ib[i];
+    }
+    if ((rc = upload(p, ib, &p->d_blocks)) != Q4C_OK) return rc;
+    if ((rc = upload(p, ic, &p->d_blocks_cost)) != Q4C_OK) return rc;
   }
   {
     const size_t nt = 2 * std::max<size_t>(p->passes.size(), 1) * q4c::kTicketsPerLaunch;
