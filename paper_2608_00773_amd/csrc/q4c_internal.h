@@ -24,8 +24,9 @@ struct WorkItem {
   int16_t ti, tj;
 };
 
-// Item of one wave of the FP64 forward contraction: the 16 x 16 blocks
-// (rb, cb .. cb + nb - 1) of a batch's function matrix, rb <= cb (block indices).
+// 16 x 16 blocks of a batch's function matrix, rb <= cb (block indices).  Item
+// of one wave of the FP64 forward contraction: (rb, cb) and, if wide,
+// (rb, cb + 1).  Item of one adjoint workgroup: rows rb .. of column cb.
 struct BlockItem {
   int32_t batch;
   uint16_t rb;
@@ -59,11 +60,10 @@ struct DevPlan {
   const int32_t *slot_fnoff;        // [n_slots] local function offset of the slot
   const int32_t *slot_nfn;          // [n_slots]
   const int64_t *slot_row_off;      // [n_slots] staging offset of the slot's block row (pass relative)
-  const int64_t *work_part_off;     // [n_work] adjoint partial offset (pass relative)
+  const int64_t *batch_part_off;    // [n_batches] first adjoint partial of the batch (pass relative)
   const int64_t *pair_off;          // [n_pairs + 1]
   const int32_t *pair_na, *pair_nb; // [n_pairs]
   const int32_t *pair_a, *pair_b;   // [n_pairs]
-  const int64_t *batch_work_off;    // [n_batches + 1] first work item of each batch
   // per batch, for slot pairs si <= sj (upper triangle, row-major): the stored
   // pair of the two atoms, or -1; batch b's table starts at batch_sp_off[b]
   const int32_t *sp_pair;
@@ -85,20 +85,16 @@ struct LaunchCfg {
   int32_t persistent = 0;
 };
 
-// One adjoint position: a column half (32 columns from tj * 64 + 32 half) of
-// work item (batch, ti, tj) whose columns start inside the batch, with the
-// batch data its kernel needs (64 bytes, one load).
-struct AdjPos {
-  int32_t batch;
-  int16_t ti, tj;
-  int32_t half, f0;
-  int32_t n, g0, P, sbase;
-  int32_t ns, pad_;
-  int64_t panel_off;  // pass relative
-  int64_t spb;        // batch_sp_off of the batch
-  int64_t part;       // pass-relative offset of the half's P partials
-};
-static_assert(sizeof(AdjPos) == 64, "AdjPos is 64 bytes");
+// Adjoint items of a batch with m blocks of 16 functions: per block column cb
+// its row blocks 0 .. cb in groups of kDenRows (rb is a group's first), in
+// this order; item t's P partials follow those of item t - 1.
+constexpr int kDenRows = 3;
+constexpr int kFold = 8;  // values per element of the folded coefficients (k_coef_fold)
+// items of the first m block columns: sum of ceil(j / kDenRows), j = 1..m
+__host__ __device__ inline int den_items(int m) {
+  const int q = m / kDenRows, r = m % kDenRows;
+  return kDenRows * q * (q + 1) / 2 + r * (q + 1);
+}
 
 struct Pass {
   int64_t b0, b1;        // batch range
@@ -108,7 +104,7 @@ struct Pass {
   int64_t staging_len;   // doubles
   int64_t partial_len;   // doubles (adjoint partials, stored after the staging)
   int64_t panel_len;     // doubles (operand panels, stored after the partials)
-  int64_t ap0, ap1;      // adjoint positions (d_adjpos, d_adjpos_cost)
+  int64_t di0, di1;      // adjoint items (d_den, d_den_cost)
   int64_t bi0, bi1;      // forward block items (d_blocks, d_blocks_cost)
 };
 
@@ -184,14 +180,14 @@ struct q4c_plan {
 
   // ---- work, passes, reductions
   std::vector<q4c::WorkItem> work;
-  std::vector<int64_t> work_part_off;
+  std::vector<int64_t> batch_part_off;
   std::vector<q4c::Pass> passes;
   std::vector<int32_t> red_pair;
   std::vector<uint8_t> red_first;
   std::vector<int64_t> red_inc_off;  // [n_red + 1]
   std::vector<int64_t> inc_src;      // staging offsets (pass relative)
   std::vector<int32_t> untouched_pairs;
-  std::vector<int64_t> batch_work_off, tab_off, panel_off;
+  std::vector<int64_t> tab_off, panel_off;
   std::vector<q4c::WorkItem> ptile;  // (batch, function tile) list of the panel kernel
   std::vector<int64_t> batch_tile_off;  // [n_batches + 1] first ptile item of each batch
   std::vector<int32_t> work_order;   // per pass, pass-relative work indices by decreasing cost
@@ -216,11 +212,11 @@ struct q4c_plan {
   int32_t *d_untouched = nullptr;
   q4c::WorkItem *d_ptile = nullptr;
   double *d_om = nullptr;  // [n_active + 16] point weights w_g v_g of the current call
-  q4c::AdjPos *d_adjpos = nullptr;       // adjoint positions per pass, batch order
-  q4c::AdjPos *d_adjpos_cost = nullptr;  // the same, work items by decreasing cost
+  q4c::BlockItem *d_den = nullptr;       // adjoint items per pass, batch order
+  q4c::BlockItem *d_den_cost = nullptr;  // the same by decreasing cost
   q4c::BlockItem *d_blocks = nullptr;       // forward block items per pass, batch order
   q4c::BlockItem *d_blocks_cost = nullptr;  // the same by decreasing cost
-  double *d_coef_fold = nullptr;  // [5][store_len + 16] the adjoint's coefficients of the current call (k_coef_fold)
+  double *d_coef_fold = nullptr;  // [store_len + 1][kFold] the adjoint's coefficients of the current call (k_coef_fold)
   double *d_ucoef = nullptr;         // ket-potential tables (q4c_plan_set_ket_potential)
   int64_t *d_shell_us_off = nullptr;
   double *d_staging = nullptr;
@@ -344,6 +340,11 @@ int launch_contract_hs(const q4c_plan *p, int64_t w0, int64_t nw, const int32_t 
                        unsigned *tickets, unsigned grid, hipStream_t s);
 // FP64 contraction of all five parts over the block items of a pass (q4c_forward_kernels.hip)
 int launch_forward(const q4c_plan *p, const Pass &ps, const double *panel, unsigned *tickets, hipStream_t s);
+// the adjoint's folded coefficients of a call, and one pass of its items and
+// point sums on the pass's panel (q4c_density_kernels.hip)
+int launch_density_fold(const q4c_plan *p, const double *coef, uint32_t terms, int precision, hipStream_t s);
+int launch_density_pass(const q4c_plan *p, const Pass &ps, int precision, int weight_mode, const double *panel,
+                        double *partial, unsigned *tickets, double *out, hipStream_t s);
 int launch_coef_from_spinor(const q4c_plan *p, const double *spin_d, double *coef_out, hipStream_t s);
 int launch_check_finite(const q4c_plan *p, const double *v, hipStream_t s, bool *finite);
 

@@ -20,12 +20,7 @@
 //  k_reduce          deterministic batch-to-global sum: every stored atom
 //                    pair adds its staged blocks in batch order (FP64).
 //  k_spinor          2x2-spinor assembly of the W and V blocks.
-//  k_density_tiles,
-//  k_density_points  density_on_grid: the transpose of the steps above
-//                    (Eq. 39): each column half of a work item reads its
-//                    coefficients from the store, contracts a_g^T C b_g at its
-//                    points on MFMA, and every point sums its partials in a
-//                    fixed order.
+// The adjoint (density_on_grid) is in q4c_density_kernels.hip.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -1322,477 +1317,6 @@ __global__ void k_spinor(DevPlan d, const double *store, double *spin_w, double 
   }
 }
 
-// ---------------------------------------------------------------------------
-// Adjoint / density
-// ---------------------------------------------------------------------------
-
-// The adjoint runs per column half of a work item: the tile's 64 rows and 32
-// of its columns (half h: columns tj*64 + 32 h ..), four waves, each with 32
-// rows and 16 columns.  Positions 2 w + h.
-constexpr int NTD = 256;
-// LDS image of one 16-point chunk of the 64 row functions (layout of
-// dma_chunk): row (q, u) every RSA doubles; 2 mod 16, so 16 lanes reading 16
-// consecutive points of one function hit distinct banks
-constexpr int RSA = 2 * T + 2;
-constexpr int AIMG = 4 * 8 * RSA;   // doubles per image: 4 components x 8 point pairs
-
-// A column half has work iff its columns start inside the batch's n functions.
-__device__ __forceinline__ bool half_valid(const WorkItem &it, int h, int n) { return it.tj * T + 32 * h < n; }
-
-// The row values of K steps KS and KS + 1 of one lane, four components
-// each: component q of step k at LDS byte address a + 64 RSA q + 64 k.  Read
-// in one asm block that also waits for them, by hand: the compiler cannot
-// tell these reads from the next chunk's LDS DMA into the other image buffer
-// and would otherwise wait for that DMA before the first read.
-template <int KS>
-__device__ __forceinline__ void read_rows2(uint32_t a, double (&y)[2][4]) {
-  constexpr int QS = 64 * RSA, K = 64 * KS;
-  asm volatile(
-      "ds_read_b64 %0, %8 offset:%9\n"
-      "ds_read_b64 %1, %8 offset:%10\n"
-      "ds_read_b64 %2, %8 offset:%11\n"
-      "ds_read_b64 %3, %8 offset:%12\n"
-      "ds_read_b64 %4, %8 offset:%13\n"
-      "ds_read_b64 %5, %8 offset:%14\n"
-      "ds_read_b64 %6, %8 offset:%15\n"
-      "ds_read_b64 %7, %8 offset:%16\n"
-      "s_waitcnt lgkmcnt(0)"
-      : "=&v"(y[0][0]), "=&v"(y[0][1]), "=&v"(y[0][2]), "=&v"(y[0][3]), "=&v"(y[1][0]), "=&v"(y[1][1]),
-        "=&v"(y[1][2]), "=&v"(y[1][3])
-      : "v"(a), "i"(K), "i"(K + QS), "i"(K + 2 * QS), "i"(K + 3 * QS), "i"(K + 64), "i"(K + 64 + QS),
-        "i"(K + 64 + 2 * QS), "i"(K + 64 + 3 * QS)
-      : "memory");
-}
-
-// Slot data and pair offsets of one adjoint position (column half of a work
-// item) in LDS: the tile's 64 rows and the half's 32 columns (slot -1:
-// beyond n), the store offset of the pair block of (row slot, column slot)
-// for the slots the half spans (-1: lower atom-block triangle or not a stored
-// pair) when they are at most ADJ_POFF pairs (atoms of 5 or more functions:
-// at most 14 x 8; otherwise each lane looks its pairs up in the plan), and
-// the slot ranges.
-constexpr int ADJ_POFF = 256;
-struct AdjTab {
-  int rslot[T], rfn[T], cslot[T / 2], cfn[T / 2], cnf[T / 2];
-  int64_t poff[ADJ_POFF];
-  int rs0, cs0, ncs, lds_table;
-};
-
-// store offset of the pair block of slots (si, sj) of a batch, -1 if none
-__device__ __forceinline__ int64_t adj_pair_offset(const DevPlan &d, const AdjPos &D, int si, int sj) {
-  if (si > sj) return -1;
-  return d.sp_poff[D.spb + (int64_t)si * D.ns - (int64_t)si * (si - 1) / 2 + (sj - si)];
-}
-
-// Fills a position's AdjTab (every thread of the workgroup calls it): two
-// dependent rounds of loads, each ended by a barrier: the slot data (threads
-// 0 .. 95, one packed load each), then the pair offsets of the slot ranges
-// (one load per thread).
-__device__ __forceinline__ void adj_fill(const DevPlan &d, const AdjPos &D, AdjTab &tb) {
-  const int tid = threadIdx.x;
-  const int r0 = D.ti * T, c0 = D.tj * T + 32 * D.half;
-  if (tid < T + T / 2) {
-    const bool row = tid < T;
-    const int lf = row ? r0 + tid : c0 + tid - T;
-    int64_t v = 0;
-    if (lf < D.n) v = d.loc_info[D.f0 + lf];
-    const int slot = lf < D.n ? (int)(v & 0xFFFFF) : -1;
-    const int fnoff = (int)((v >> 20) & 0xFFFFF), nfn = (int)(v >> 40);
-    if (row) {
-      tb.rslot[tid] = slot;
-      tb.rfn[tid] = fnoff;
-    } else {
-      tb.cslot[tid - T] = slot;
-      tb.cfn[tid - T] = fnoff;
-      tb.cnf[tid - T] = nfn;
-    }
-  }
-  __syncthreads();  // slot data visible
-  // slot ranges of the tile's rows and the half's columns (slots ascend with
-  // the functions; rows and columns beyond n carry slot -1)
-  const int rs0 = tb.rslot[0], cs0 = tb.cslot[0];
-  const int rs1 = tb.rslot[min(T, D.n - r0) - 1], cs1 = tb.cslot[min(T / 2, D.n - c0) - 1];
-  const int nrs = rs1 - rs0 + 1, ncs = cs1 - cs0 + 1;
-  const bool in_lds = nrs * ncs <= ADJ_POFF;  // workgroup-uniform
-  if (in_lds && tid < nrs * ncs) tb.poff[tid] = adj_pair_offset(d, D, rs0 + tid / ncs, cs0 + tid % ncs);
-  if (tid == 0) {
-    tb.rs0 = rs0;
-    tb.cs0 = cs0;
-    tb.ncs = ncs;
-    tb.lds_table = in_lds;
-  }
-  __syncthreads();  // pair offsets visible
-}
-
-// partial[g] of a position (P doubles at its pass-relative part offset) = sum
-// over its stored elements ij of the selected terms at point g:
-//   C^V phi_i phi_j + c' C^Ws grad phi_i . grad phi_j + c' sum_m C^m (grad phi_i x grad phi_j)_m
-// (Eq. 39 on the scalar basis).  A position is one column half of a work
-// item (the tile's 64 rows, 32 columns), four waves of 32 rows and 16 columns
-// each.  Per wave, the 32 x 16 coefficient block sits in registers as the
-// MFMA's second operand (5 parts x 8 K steps of 4 rows), and per 16-point
-// chunk four accumulators collect (Y^T C) grouped by the column component Z
-// they are multiplied with afterwards:
-//   u_phi = C^V phi,  u_x = C^Ws dx - C^z dy + C^y dz,
-//   u_y = C^z dx + C^Ws dy - C^x dz,  u_z = -C^y dx + C^x dy + C^Ws dz
-// (rows i, the K index: Y = the row functions' values at the chunk's points),
-// then one drain sum_j u . Z per chunk.  The row image arrives by LDS DMA,
-// double-buffered (the next chunk's loads in flight while this one is
-// multiplied, one barrier per chunk); each lane's 16 column values Z come from
-// the panel straight into registers, two chunks ahead.  Two workgroups fit on a
-// CU.  A persistent workgroup draws its next position after the last chunk of
-// a position (drawn when a position starts, the tickets ran one position
-// ahead of need and the launch read twice the bytes, at the same speed).
-// F32W (density_on_grid in FP32): the nine W-term products per K step run on
-// FP32 MFMA with the coefficients and row values rounded to FP32; each
-// chunk's FP32 sums over the wave's 32 rows (at most 96 products per column
-// and point) are drained into the FP64 point sum, so the FP32 error of a
-// point is at most gamma_98 (u = 2^-24) times the magnitudes of its W terms.
-// The V term stays FP64.
-template <bool F32W, bool PERSIST>
-__global__ __launch_bounds__(NTD, 2) void k_density_tiles(DevPlan d, const AdjPos *apos, int64_t npos, int global_queue,
-                                                          const double *cf, const double *panel, double *partial,
-                                                          unsigned *tickets) {
-  constexpr int NC = 5;  // coefficient parts
-  __shared__ double img[2][AIMG];        // row images, alternating chunks
-  __shared__ double s_red[2][4][16];     // per-wave point sums, alternating chunks
-  __shared__ int64_t s_pos, s_next[2];
-  __shared__ AdjTab tb;                  // the position's slot and pair tables
-  const bool gq = global_queue != 0;
-  int64_t pos = PERSIST ? next_item(tickets, npos, gq, &s_pos) : (gq ? (int64_t)blockIdx.x : xcd_map(blockIdx.x, npos));
-  if (pos >= npos) return;  // workgroup-uniform
-  AdjPos D = adj_uniform(apos[pos]);
-  const int tid = threadIdx.x;
-  // wave index as a scalar: conditions derived from it stay uniform
-  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int js = wave & 1, ih = wave >> 1;  // column block, row half
-  const int l16 = lane & 15, lk = lane >> 4;
-  // column values of a chunk.  FP64 (TR): the MFMA takes the row values as
-  // its first operand (lane l16 supplying point 4 (l16 % 4) + l16 / 4) and
-  // the coefficients as its second, so result register r of lane (l16, lk)
-  // is point 4 lk + r at column colb + l16: each lane's four points of a
-  // component are one 32-byte quad of the panel, two 16-byte loads.  F32W:
-  // coefficients first, register r is column lk + 4 r (FP64 MFMA) or
-  // 4 lk + r (FP32 MFMA) at point l16.
-  constexpr bool TR = !F32W;
-  const int ptA = TR ? 4 * (l16 & 3) + (l16 >> 2) : l16;  // the point this lane supplies to the row operand
-  int par = 0;
-  for (;;) {
-  const int n = D.n, P = D.P;
-  const int r0 = D.ti * T, c0 = D.tj * T + 32 * D.half;
-  const int Pp = (int)pad16(P), np = (int)pad16(n);
-  const double *pb = panel + D.panel_off;
-  const int64_t plane = (int64_t)Pp * np;
-  const int colb = c0 + 16 * js;
-  const int lj = colb + l16;
-  // row origin of this wave's two 16-row blocks.  Column half 0 of a diagonal
-  // tile has 3 active blocks, (0,0), (0,1) and (1,1) in 16-blocks: block (1,1)
-  // moves from wave (ih 0, js 1) to the otherwise idle wave (ih 1, js 1), so
-  // no wave of that half carries two.
-  const bool dg0 = D.ti == D.tj && D.half == 0;
-  const int iloc = (dg0 && ih == 1 && js == 1) ? 16 : 32 * ih;
-  bool act[2], upper[2];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int rb = r0 + iloc + 16 * h;
-    act[h] = block_active(rb, colb, n) && !(dg0 && ih == 0 && js == 1 && h == 1);
-    upper[h] = rb < colb;
-  }
-  const bool any = act[0] || act[1];
-  // The row image of a chunk comes by buffer loads straight into LDS: image
-  // row r = (component r / 8, point pair r % 8) holds 16 bytes per function;
-  // the lane offset is fixed, the chunk and image row go into the scalar offset.
-  // Lanes whose function lies at or beyond np, and column loads of a wave
-  // without active blocks, take an offset past the end of the buffer: the
-  // load is still issued (so every wave issues the same loads per chunk) but
-  // reads nothing and returns zero.
-  const __amdgpu_buffer_rsrc_t prs =
-      __builtin_amdgcn_make_buffer_rsrc((void *)pb, (short)0, (int)(32 * plane), 0x00020000);
-  constexpr uint32_t OOB = 0x80000000u;
-  const uint32_t vrow = r0 + lane < np ? lane * 32u : OOB;
-  auto dma_rows = [&](int ks0, double *dst) {
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int r = wave + 4 * k, q = r >> 3, u = r & 7;
-      const uint32_t so = (uint32_t)((q * plane + ((int64_t)(ks0 + (u >> 1)) * np + r0) * 4 + 2 * (u & 1)) * 8);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(prs, (lds_void *)(dst + r * RSA), 16, vrow, so, 0, 0);
-    }
-  };
-  // column values of two chunks in flight: zb[c & 1] holds chunk c's, loaded
-  // at the end of chunk c - 2.  Each wave issues the same ZLOADS buffer loads
-  // for every chunk, unconditionally (past the last chunk the last one is read
-  // again), so that at each chunk's barrier "this chunk's image and column
-  // values have landed" is "at most ZLOADS loads outstanding": only the next
-  // chunk's column loads, issued after the image DMA, remain in flight.
-  double zb[2][4][4];
-  const uint32_t zoob = any ? 0u : OOB;  // or-ed into the offsets: no branch around the loads
-  auto load_z = [&](int k, auto zc) {
-    constexpr int ZB = decltype(zc)::value;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const uint32_t qo = (uint32_t)(q * plane * 8);
-      if (TR) {
-        const uint32_t zo = (uint32_t)(((int64_t)((k >> 2) + lk) * np + colb + l16) * 32) | zoob;
-        const dbl2 z01 = __builtin_bit_cast(dbl2, __builtin_amdgcn_raw_buffer_load_b128(prs, zo, qo, 0));
-        const dbl2 z23 = __builtin_bit_cast(dbl2, __builtin_amdgcn_raw_buffer_load_b128(prs, zo + 16, qo, 0));
-        zb[ZB][q][0] = z01[0];
-        zb[ZB][q][1] = z01[1];
-        zb[ZB][q][2] = z23[0];
-        zb[ZB][q][3] = z23[1];
-      } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int jr = (F32W && q > 0) ? d_row_f32(lk, r) : d_row_f64(lk, r);
-          const uint32_t zo = (uint32_t)((((int64_t)((k + l16) >> 2) * np + colb + jr) * 4 + (l16 & 3)) * 8) | zoob;
-          zb[ZB][q][r] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(prs, zo, qo, 0));
-        }
-      }
-    }
-  };
-  // column loads per chunk: one buffer load instruction each
-  constexpr int ZLOADS = TR ? 8 : 16;
-  // the first chunk's loads go out before anything else of the position
-  dma_rows(0, img[0]);
-  load_z(0, std::integral_constant<int, 0>{});
-  load_z(min(16, Pp - 16), std::integral_constant<int, 1>{});
-  adj_fill(d, D, tb);
-  // coefficient slice: rows i = r0 + iloc + 4 ks + lk (ks = 0..7), column lj:
-  // element (li, lj) of the folded coefficients (k_coef_fold) in the pair
-  // block of its two atoms (upper atom-block triangle only); lanes without a
-  // stored element read the zeros past the end of each part
-  double creg[NC][8];
-  {
-    const int64_t Lf = d.store_len + 16;
-    const int cl = 16 * js + l16;
-    const int cslot = tb.cslot[cl], cfn = tb.cfn[cl], cnf = tb.cnf[cl];
-    const int rs0 = tb.rs0, cs0 = tb.cs0, ncs = tb.ncs;
-    const bool lds_table = tb.lds_table != 0;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      const int rl = iloc + 4 * ks + lk;
-      const int li = r0 + rl;
-      const int rslot = tb.rslot[rl], rfn = tb.rfn[rl];
-      int64_t po = -1;
-      if (act[ks >> 2] && rslot >= 0 && cslot >= 0)
-        po = lds_table ? tb.poff[(rslot - rs0) * ncs + (cslot - cs0)] : adj_pair_offset(d, D, rslot, cslot);
-      const int64_t ea = po >= 0 ? po + (int64_t)(li - rfn) * cnf + (lj - cfn) : d.store_len;
-#pragma unroll
-      for (int q = 0; q < NC; ++q) creg[q][ks] = cf[q * Lf + ea];
-    }
-  }
-  // F32W: the W coefficients as FP32 MFMA operands
-  float cw[4][8];
-  if (F32W) {
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) cw[q][ks] = (float)creg[q + 1][ks];
-  }
-  double *out = partial + D.part;
-  // the coefficients (and the first chunks' loads) have landed before the
-  // chunks begin, so that no wait for them falls inside a chunk
-  __builtin_amdgcn_s_waitcnt(0);
-
-
-  auto chunk = [&](int k0, auto zc) {
-    constexpr int bi = decltype(zc)::value;  // chunk parity: image buffer and column-value set
-    // this wave's image and column loads of this chunk have landed (only the
-    // next chunk's column loads may be outstanding) ... and everyone's; the
-    // previous chunk is consumed, its sums visible
-    barrier_vm<ZLOADS>();
-    if (k0 > 0 && tid < 16 && k0 - 16 + tid < P)
-      out[k0 - 16 + tid] = (s_red[bi ^ 1][0][tid] + s_red[bi ^ 1][1][tid]) +
-                           (s_red[bi ^ 1][2][tid] + s_red[bi ^ 1][3][tid]);
-    dma_rows(min(k0 + 16, Pp - 16) >> 2, img[bi ^ 1]);
-    // this chunk's column values landed before the barrier above; the empty
-    // asm makes them its own result, so the compiler, which cannot follow the
-    // loads across the barrier, places no wait for them inside the chunk
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      asm volatile("" : "+v"(zb[bi][q][0]), "+v"(zb[bi][q][1]), "+v"(zb[bi][q][2]), "+v"(zb[bi][q][3]));
-    const double (&zt)[4][4] = zb[bi];
-    double x = 0.0;
-    if (any && F32W) {
-      // this lane's row values of K step 0, component 0 (point ptA, row iloc + lk)
-      const uint32_t ybase = lds_addr(img[bi]) + 8u * (uint32_t)((ptA >> 1) * RSA + 2 * (iloc + lk) + (ptA & 1));
-      dbl4 uf = dbl4{0.0, 0.0, 0.0, 0.0};
-      flt4 vx = flt4{0.f, 0.f, 0.f, 0.f}, vy = vx, vz = vx;
-      auto ksteps = [&](auto k0c, auto k1c) {
-        constexpr int K0 = decltype(k0c)::value, K1 = decltype(k1c)::value;
-        static_for<K0, K1, 2>([&](auto kpc) {
-        constexpr int KP = decltype(kpc)::value;
-        double yy[2][4];
-        read_rows2<KP>(ybase, yy);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int ks = KP + h;
-          const double y0 = yy[h][0];
-          const float y1 = (float)yy[h][1];
-          const float y2 = (float)yy[h][2];
-          const float y3 = (float)yy[h][3];
-          uf = mfma64(creg[0][ks], y0, uf);
-          vx = mfma32(cw[0][ks], y1, vx);
-          vy = mfma32(cw[3][ks], y1, vy);
-          vz = mfma32(cw[2][ks], -y1, vz);
-          vx = mfma32(cw[3][ks], -y2, vx);
-          vy = mfma32(cw[0][ks], y2, vy);
-          vz = mfma32(cw[1][ks], y2, vz);
-          vx = mfma32(cw[2][ks], y3, vx);
-          vy = mfma32(cw[1][ks], -y3, vy);
-          vz = mfma32(cw[0][ks], y3, vz);
-        }
-        });
-      };
-      if (act[0] && act[1])
-        ksteps(std::integral_constant<int, 0>{}, std::integral_constant<int, 8>{});
-      else if (act[0])
-        ksteps(std::integral_constant<int, 0>{}, std::integral_constant<int, 4>{});
-      else
-        ksteps(std::integral_constant<int, 4>{}, std::integral_constant<int, 8>{});
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        x += (uf[r] * zt[0][r] + (double)vx[r] * zt[1][r]) + ((double)vy[r] * zt[2][r] + (double)vz[r] * zt[3][r]);
-      x += __shfl_xor(x, 16);
-      x += __shfl_xor(x, 32);
-    } else if (any) {
-      // this lane's row values of K step 0, component 0 (point ptA, row iloc + lk)
-      const uint32_t ybase = lds_addr(img[bi]) + 8u * (uint32_t)((ptA >> 1) * RSA + 2 * (iloc + lk) + (ptA & 1));
-      dbl4 uf = dbl4{0.0, 0.0, 0.0, 0.0}, ux = uf, uy = uf, uz = uf;
-      // the K steps of active 16-row blocks, as straight-line code
-      auto ksteps = [&](auto k0c, auto k1c) {
-        constexpr int K0 = decltype(k0c)::value, K1 = decltype(k1c)::value;
-        static_for<K0, K1, 2>([&](auto kpc) {
-        constexpr int KP = decltype(kpc)::value;
-        double yy[2][4];
-        read_rows2<KP>(ybase, yy);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          // row values Y[q][pt = ptA][i = iloc + 4 ks + lk]: the K index is lk;
-          // row values first, so the result is points x columns
-          const int ks = KP + h;
-          const double y0 = yy[h][0], y1 = yy[h][1], y2 = yy[h][2], y3 = yy[h][3];
-          uf = mfma64(y0, creg[0][ks], uf);
-          ux = mfma64(y1, creg[1][ks], ux);
-          uy = mfma64(y1, creg[4][ks], uy);
-          uz = mfma64(-y1, creg[3][ks], uz);
-          ux = mfma64(-y2, creg[4][ks], ux);
-          uy = mfma64(y2, creg[1][ks], uy);
-          uz = mfma64(y2, creg[2][ks], uz);
-          ux = mfma64(y3, creg[3][ks], ux);
-          uy = mfma64(-y3, creg[2][ks], uy);
-          uz = mfma64(y3, creg[1][ks], uz);
-        }
-        });
-      };
-      if (act[0] && act[1])
-        ksteps(std::integral_constant<int, 0>{}, std::integral_constant<int, 8>{});
-      else if (act[0])
-        ksteps(std::integral_constant<int, 0>{}, std::integral_constant<int, 4>{});
-      else
-        ksteps(std::integral_constant<int, 4>{}, std::integral_constant<int, 8>{});
-      // per point (register r: point 4 lk + r), the sum over the 16 columns
-      // (lanes l16 of the row): halve the points per lane twice (xor 8, 4),
-      // then finish the sum (xor 2, 1); lane l16 ends with point 4 lk + r*,
-      // r* = 2 (l16 >> 3 & 1) + (l16 >> 2 & 1)
-      double xr[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) xr[r] = (uf[r] * zt[0][r] + ux[r] * zt[1][r]) + (uy[r] * zt[2][r] + uz[r] * zt[3][r]);
-      const bool h8 = (l16 & 8) != 0, h4 = (l16 & 4) != 0;
-      double s0 = h8 ? xr[2] : xr[0], s1 = h8 ? xr[3] : xr[1];
-      s0 += dpp_f64<DPP_ROW_MIRROR>(h8 ? xr[0] : xr[2]);
-      s1 += dpp_f64<DPP_ROW_MIRROR>(h8 ? xr[1] : xr[3]);
-      x = h4 ? s1 : s0;
-      x += dpp_f64<DPP_ROW_HALF_MIRROR>(h4 ? s0 : s1);
-      x += dpp_f64<DPP_QUAD_XOR2>(x);
-      x += dpp_f64<DPP_QUAD_XOR1>(x);
-    }
-    if (TR) {
-      if ((l16 & 3) == 0) s_red[bi][wave][4 * lk + 2 * ((l16 >> 3) & 1) + ((l16 >> 2) & 1)] = x;
-    } else {
-      if (lane < 16) s_red[bi][wave][l16] = x;
-    }
-    load_z(min(k0 + 32, Pp - 16), zc);
-  };
-  // pairs of chunks (even, odd) as straight-line code, then an odd last one
-  int k0 = 0;
-  for (; k0 + 32 <= Pp; k0 += 32) {
-    chunk(k0, std::integral_constant<int, 0>{});
-    chunk(k0 + 16, std::integral_constant<int, 1>{});
-  }
-  if (k0 < Pp) chunk(k0, std::integral_constant<int, 0>{});
-  __syncthreads();  // the last chunk's per-wave sums
-  {
-    const int k0 = Pp - 16, bi = (k0 >> 4) & 1;
-    if (tid < 16 && k0 + tid < P)
-      out[k0 + tid] = (s_red[bi][0][tid] + s_red[bi][1][tid]) + (s_red[bi][2][tid] + s_red[bi][3][tid]);
-  }
-  if (!PERSIST) return;
-  // the next position, drawn once this one is done; two slots in turn:
-  // thread 0 may write the next slot before every thread has read this one
-  if (tid == 0) s_next[par] = ticket_pos(tickets, npos, gq, draw_ticket(tickets, gq));
-  __syncthreads();
-  pos = uniform_i64(s_next[par]);
-  par ^= 1;
-  if (pos >= npos) return;
-  D = adj_uniform(apos[pos]);
-  }
-}
-
-// The adjoint's coefficients, folded once per call.  Eq. 39 sums every stored
-// element ij of the selected terms; the adjoint's work items cover the upper
-// 16 x 16 blocks of each batch, so in the diagonal block of one atom element
-// (i, j), i < j, takes C_q(i, j) + s_q C_q(j, i) (s_q = +1 for V and Ws, -1
-// for the spin-orbit parts, whose terms change sign under i <-> j), (i, i)
-// keeps C_q(i, i) and i > j is zero: every term is then carried once.  Blocks
-// of two atoms are copied.  c' multiplies the W parts, unselected terms are
-// zero, and each part ends in 16 zeros (row stride store_len + 16), the
-// element of lanes without a stored one.  One workgroup per pair.
-__global__ void k_coef_fold(DevPlan d, const double *coef, uint32_t terms, double *cf) {
-  const int64_t L = d.store_len, Lf = L + 16;
-  const int64_t q = blockIdx.x;
-  const bool on[5] = {(terms & Q4C_TERM_LL) != 0, (terms & Q4C_TERM_SS) != 0, (terms & Q4C_TERM_SO) != 0,
-                      (terms & Q4C_TERM_SO) != 0, (terms & Q4C_TERM_SO) != 0};
-  if (q == 0 && threadIdx.x < 16)
-    for (int p = 0; p < 5; ++p) cf[p * Lf + L + threadIdx.x] = 0.0;
-  const int64_t po = d.pair_off[q];
-  const int na = d.pair_na[q], nb = d.pair_nb[q];
-  const bool diag = d.pair_a[q] == d.pair_b[q];
-  for (int t = threadIdx.x; t < na * nb; t += blockDim.x) {
-    const int i = t / nb, j = t - i * nb;
-#pragma unroll
-    for (int p = 0; p < 5; ++p) {
-      double c = coef[p * L + po + t];
-      if (diag) {
-        if (i < j)
-          c += mirror_sign(p) * coef[p * L + po + (int64_t)j * nb + i];
-        else if (i > j)
-          c = 0.0;
-      }
-      cf[p * Lf + po + t] = on[p] ? (p > 0 ? c * d.cprime : c) : 0.0;
-    }
-  }
-}
-
-// Point sums: out[perm[g]] = (w_g if weighted) * sum over the batch's work
-// items (in order) and their valid column halves (in order).
-__global__ void k_density_points(DevPlan d, const WorkItem *work, int64_t b0, const double *partial, int weight_mode,
-                                 double *out) {
-  const int64_t b = b0 + blockIdx.x;
-  const int g0 = d.batch_pt_off[b], P = d.batch_pt_off[b + 1] - g0;
-  const int n = d.batch_fn_off[b + 1] - d.batch_fn_off[b];
-  const int64_t wa = d.batch_work_off[b], wb = d.batch_work_off[b + 1];
-  for (int g = threadIdx.x; g < P; g += blockDim.x) {
-    double s = 0.0;
-    for (int64_t w = wa; w < wb; ++w) {
-      const WorkItem it = work[w];
-      const double *pw = partial + 2 * d.work_part_off[w];
-      s += pw[g];
-      if (half_valid(it, 1, n)) s += pw[P + g];
-    }
-    out[d.perm[g0 + g]] = weight_mode ? d.pw[g0 + g] * s : s;
-  }
-}
-
 __global__ void k_fill(double *p, int64_t n, double v) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     p[i] = v;
@@ -2042,14 +1566,7 @@ int launch_density(const q4c_plan *p, const double *coef, uint32_t terms, int pr
     }
     if ((rc = check_launch("k_fill")) != Q4C_OK) return rc;
   }
-  if (p->n_pairs > 0) {
-    {
-      TimedLaunch tl_(p, Q4C_TIMER_OTHER, s);
-      hipLaunchKernelGGL(k_coef_fold, dim3((unsigned)p->n_pairs), dim3(256), 0, s, p->dp, coef, terms,
-                         p->d_coef_fold);
-    }
-    if ((rc = check_launch("k_coef_fold")) != Q4C_OK) return rc;
-  }
+  if ((rc = launch_density_fold(p, coef, terms, precision, s)) != Q4C_OK) return rc;
   const LaunchCfg cfg = p->cfg_density;
   unsigned *tick0 = p->d_tickets + p->passes.size() * kTicketsPerLaunch;
   if (cfg.persistent > 0) {
@@ -2062,12 +1579,8 @@ int launch_density(const q4c_plan *p, const double *coef, uint32_t terms, int pr
   for (size_t ipr = p->passes.size(); ipr-- > 0;) {
     const size_t ip = ipr;
     const Pass &ps = p->passes[ip];
-    const int64_t nw = ps.ap1 - ps.ap0, nbt = ps.b1 - ps.b0;
-    const AdjPos *apos = (cfg.order ? p->d_adjpos_cost : p->d_adjpos) + ps.ap0;
     const int64_t nt = (int64_t)ip == resident_pass ? 0 : ps.t1 - ps.t0;
     unsigned *tickets = cfg.persistent > 0 ? tick0 + ip * kTicketsPerLaunch : nullptr;
-    // one workgroup position per column half of a work item
-    const unsigned grid = (unsigned)(cfg.persistent > 0 ? std::min<int64_t>(cfg.persistent, nw) : nw);
     double *partial = p->d_staging + ps.staging_len;
     double *panel = partial + ps.partial_len;
     if (nt > 0) {
@@ -2078,35 +1591,7 @@ int launch_density(const q4c_plan *p, const double *coef, uint32_t terms, int pr
       }
       if ((rc = check_launch("k_panel")) != Q4C_OK) return rc;
     }
-    if (nw > 0) {
-      {
-        TimedLaunch tl_(p, Q4C_TIMER_DENSITY_TILES, s);
-        if (precision == Q4C_PREC_F32) {
-          if (tickets)
-            hipLaunchKernelGGL((k_density_tiles<true, true>), dim3(grid), dim3(NTD), 0, s, p->dp, apos, nw,
-                               cfg.order, p->d_coef_fold, panel, partial, tickets);
-          else
-            hipLaunchKernelGGL((k_density_tiles<true, false>), dim3(grid), dim3(NTD), 0, s, p->dp, apos, nw,
-                               cfg.order, p->d_coef_fold, panel, partial, tickets);
-        } else {
-          if (tickets)
-            hipLaunchKernelGGL((k_density_tiles<false, true>), dim3(grid), dim3(NTD), 0, s, p->dp, apos, nw,
-                               cfg.order, p->d_coef_fold, panel, partial, tickets);
-          else
-            hipLaunchKernelGGL((k_density_tiles<false, false>), dim3(grid), dim3(NTD), 0, s, p->dp, apos, nw,
-                               cfg.order, p->d_coef_fold, panel, partial, tickets);
-        }
-      }
-      if ((rc = check_launch("k_density_tiles")) != Q4C_OK) return rc;
-    }
-    if (nbt > 0) {
-      {
-        TimedLaunch tl_(p, Q4C_TIMER_DENSITY_POINTS, s);
-        hipLaunchKernelGGL(k_density_points, dim3((unsigned)nbt), dim3(256), 0, s, p->dp, p->d_work, ps.b0, partial,
-                           weight_mode, out);
-      }
-      if ((rc = check_launch("k_density_points")) != Q4C_OK) return rc;
-    }
+    if ((rc = launch_density_pass(p, ps, precision, weight_mode, panel, partial, tickets, out, s)) != Q4C_OK) return rc;
   }
   return Q4C_OK;
 }

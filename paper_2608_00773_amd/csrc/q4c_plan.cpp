@@ -494,7 +494,7 @@ int build_host(q4c_plan *p, const q4c_basis *b, const q4c_grid *g, const std::ve
       }
     }
     int nt = (nb_fn + T - 1) / T;
-    int64_t bpart = 2 * (int64_t)(nt * (nt + 1) / 2) * (g1 - g0);  // two column halves per work item
+    int64_t bpart = (int64_t)q4c::den_items((int)(q4c::pad16(nb_fn) >> 4)) * (g1 - g0);  // adjoint partials
     // panel: 4 FP64 planes (the largest kind)
     int64_t bpanel = 4 * q4c::pad16(g1 - g0) * q4c::pad16(nb_fn);
     if (bt > cur.b0 && (staging + partial + panel + bstage + bpart + bpanel > budget_doubles)) close_pass(bt);
@@ -541,10 +541,9 @@ int build_host(q4c_plan *p, const q4c_basis *b, const q4c_grid *g, const std::ve
     for (int ti = 0; ti < nt; ++ti)
       for (int tj = ti; tj < nt; ++tj) {
         p->work.push_back(q4c::WorkItem{(int32_t)bt, (int16_t)ti, (int16_t)tj});
-        // adjoint partials of this work item: two column halves of P doubles at 2 * work_part_off
-        p->work_part_off.push_back(partial / 2);
-        partial += 2 * (g1 - g0);
       }
+    p->batch_part_off.push_back(partial);
+    partial += bpart;
     p->max_batch_points = std::max<int64_t>(p->max_batch_points, g1 - g0);
     p->max_batch_fn = std::max<int64_t>(p->max_batch_fn, nb_fn);
     p->flops_alg += 10.0 * (double)(g1 - g0) * (double)nb_fn * (double)nb_fn;
@@ -553,9 +552,6 @@ int build_host(q4c_plan *p, const q4c_basis *b, const q4c_grid *g, const std::ve
   close_pass(p->n_batches);
   p->batch_tile_off.push_back((int64_t)p->ptile.size());
   p->red_inc_off.push_back((int64_t)p->inc_src.size());
-  p->batch_work_off.assign(p->n_batches + 1, 0);
-  for (auto &w : p->work) p->batch_work_off[w.batch + 1]++;
-  for (int64_t b = 0; b < p->n_batches; ++b) p->batch_work_off[b + 1] += p->batch_work_off[b];
   p->tab_off.assign(p->n_batches + 1, 0);
   for (int64_t b = 0; b < p->n_batches; ++b)
     p->tab_off[b + 1] = p->tab_off[b] + (int64_t)(p->batch_pt_off[b + 1] - p->batch_pt_off[b]) *
@@ -600,7 +596,7 @@ int build_device(q4c_plan *p) {
   } while (0)
   double *R, *rcut, *coef, *px, *py, *pz, *pw;
   int32_t *fn_atom, *fn_shlm, *nint, *perm, *bpo, *bfo, *lfn, *lsl, *bso, *sfo, *snf, *pna, *pnb, *pa, *pb;
-  int64_t *coff, *sro, *wpo, *poff, *bwo, *toff, *pnoff;
+  int64_t *coff, *sro, *bpt, *poff, *toff, *pnoff;
   double *sknot;
   UP(p->R, R);
   UP(p->fn_atom, fn_atom);
@@ -623,13 +619,12 @@ int build_device(q4c_plan *p) {
   UP(p->slot_fnoff, sfo);
   UP(p->slot_nfn, snf);
   UP(p->slot_row_off, sro);
-  UP(p->work_part_off, wpo);
+  UP(p->batch_part_off, bpt);
   UP(p->pair_off, poff);
   UP(p->pair_na, pna);
   UP(p->pair_nb, pnb);
   UP(p->pair_a, pa);
   UP(p->pair_b, pb);
-  UP(p->batch_work_off, bwo);
   UP(p->tab_off, toff);
   UP(p->panel_off, pnoff);
   UP(p->ptile, p->d_ptile);
@@ -682,80 +677,60 @@ int build_device(q4c_plan *p) {
   if (rc != Q4C_OK) return rc;
   rc = device_alloc(p, (size_t)(p->n_active + 16) * sizeof(double), (void **)&p->d_om);
   if (rc != Q4C_OK) return rc;
-  rc = device_alloc(p, (size_t)5 * (p->store_len + 16) * sizeof(double), (void **)&p->d_coef_fold);
+  rc = device_alloc(p, (size_t)q4c::kFold * (p->store_len + 1) * sizeof(double), (void **)&p->d_coef_fold);
   if (rc != Q4C_OK) return rc;
   {
-    // adjoint positions: the column halves of the work items that start
-    // inside their batch, per pass, in batch order and in the work items'
-    // cost order
-    std::vector<q4c::AdjPos> ab, ac;
-    auto add = [&](std::vector<q4c::AdjPos> &v, int64_t w) {
-      const q4c::WorkItem &it = p->work[w];
-      const int b = it.batch;
-      const int f0 = p->batch_fn_off[b], n = p->batch_fn_off[b + 1] - f0;
-      const int g0 = p->batch_pt_off[b], P = p->batch_pt_off[b + 1] - g0;
-      for (int h = 0; h < 2; ++h) {
-        if (it.tj * q4c::kTile + 32 * h >= n) continue;
-        q4c::AdjPos a{};
-        a.batch = b;
-        a.ti = it.ti;
-        a.tj = it.tj;
-        a.half = h;
-        a.f0 = f0;
-        a.n = n;
-        a.g0 = g0;
-        a.P = P;
-        a.sbase = p->batch_slot_off[b];
-        a.ns = p->batch_slot_off[b + 1] - p->batch_slot_off[b];
-        a.panel_off = p->panel_off[b];
-        a.spb = p->batch_sp_off[b];
-        a.part = 2 * p->work_part_off[w] + (int64_t)h * P;
-        v.push_back(a);
-      }
+    // Items of the FP64 forward contraction (per pair of block columns, the
+    // last may be single, its rows down to the diagonal, so that neighbouring
+    // items share their columns) and of the adjoint (see den_items), per pass
+    // in batch order and by decreasing cost (points x blocks, counted into
+    // buckets).
+    std::vector<q4c::BlockItem> fwd, fwd_cost, den, den_cost;
+    auto rows = [](const q4c::BlockItem &x) { return std::min<int>(q4c::kDenRows, x.cb + 1 - x.rb); };
+    auto by_cost = [&](const std::vector<q4c::BlockItem> &v, int64_t i0, std::vector<q4c::BlockItem> &out, bool fw) {
+      auto cost = [&](const q4c::BlockItem &x) {
+        return (q4c::pad16(p->batch_pt_off[x.batch + 1] - p->batch_pt_off[x.batch]) >> 4) *
+               (fw ? 1 + x.wide : rows(x));
+      };
+      int64_t top = 0;
+      for (size_t i = i0; i < v.size(); ++i) top = std::max(top, cost(v[i]));
+      std::vector<int64_t> at(top + 2, 0);
+      for (size_t i = i0; i < v.size(); ++i) at[top - cost(v[i]) + 1]++;
+      for (int64_t k = 0; k <= top; ++k) at[k + 1] += at[k];
+      out.resize(v.size());
+      for (size_t i = i0; i < v.size(); ++i) out[i0 + at[top - cost(v[i])]++] = v[i];
     };
     for (q4c::Pass &ps : p->passes) {
-      ps.ap0 = (int64_t)ab.size();
-      for (int64_t w = ps.w0; w < ps.w1; ++w) add(ab, w);
-      for (int64_t i = 0; i < ps.w1 - ps.w0; ++i) add(ac, ps.w0 + p->work_order[ps.w0 + i]);
-      ps.ap1 = (int64_t)ab.size();
-    }
-    if ((rc = upload(p, ab, &p->d_adjpos)) != Q4C_OK) return rc;
-    if ((rc = upload(p, ac, &p->d_adjpos_cost)) != Q4C_OK) return rc;
-  }
-  {
-    // forward block items: per pair of block columns (the last may be single)
-    // its rows down to the diagonal, so that neighbouring items share their
-    // columns; and the same by decreasing cost (points x blocks), counted
-    // into buckets
-    std::vector<q4c::BlockItem> ib, ic;
-    for (q4c::Pass &ps : p->passes) {
-      ps.bi0 = (int64_t)ib.size();
-      int64_t top = 0;
-      auto cost = [&](const q4c::BlockItem &x) {
-        return (q4c::pad16(p->batch_pt_off[x.batch + 1] - p->batch_pt_off[x.batch]) >> 4) * (1 + x.wide);
-      };
+      ps.bi0 = (int64_t)fwd.size();
+      ps.di0 = (int64_t)den.size();
       for (int64_t b = ps.b0; b < ps.b1; ++b) {
         const int m = (int)(q4c::pad16(p->batch_fn_off[b + 1] - p->batch_fn_off[b]) >> 4);
+        q4c::BlockItem x{};
+        x.batch = (int32_t)b;
         for (int c = 0; c < m; c += 2)
           for (int r = 0; r <= std::min(c + 1, m - 1); ++r) {
-            q4c::BlockItem x{};
-            x.batch = (int32_t)b;
             x.rb = (uint16_t)r;
             x.cb = (uint16_t)std::max(c, r);
             x.wide = r <= c && c + 1 < m;
-            ib.push_back(x);
-            top = std::max(top, cost(x));
+            fwd.push_back(x);
+          }
+        x.wide = 0;
+        for (int c = 0; c < m; ++c)
+          for (int r = 0; r <= c; r += q4c::kDenRows) {
+            x.rb = (uint16_t)r;
+            x.cb = (uint16_t)c;
+            den.push_back(x);
           }
       }
-      ps.bi1 = (int64_t)ib.size();
-      std::vector<int64_t> at(top + 2, 0);
-      for (int64_t i = ps.bi0; i < ps.bi1; ++i) at[top - cost(ib[i]) + 1]++;
-      for (int64_t k = 0; k <= top; ++k) at[k + 1] += at[k];
-      ic.resize(ib.size());
-      for (int64_t i = ps.bi0; i < ps.bi1; ++i) ic[ps.bi0 + at[top - cost(ib[i])]++] = ib[i];
+      ps.bi1 = (int64_t)fwd.size();
+      ps.di1 = (int64_t)den.size();
+      by_cost(fwd, ps.bi0, fwd_cost, true);
+      by_cost(den, ps.di0, den_cost, false);
     }
-    if ((rc = upload(p, ib, &p->d_blocks)) != Q4C_OK) return rc;
-    if ((rc = upload(p, ic, &p->d_blocks_cost)) != Q4C_OK) return rc;
+    if ((rc = upload(p, fwd, &p->d_blocks)) != Q4C_OK) return rc;
+    if ((rc = upload(p, fwd_cost, &p->d_blocks_cost)) != Q4C_OK) return rc;
+    if ((rc = upload(p, den, &p->d_den)) != Q4C_OK) return rc;
+    if ((rc = upload(p, den_cost, &p->d_den_cost)) != Q4C_OK) return rc;
   }
   {
     const size_t nt = 2 * std::max<size_t>(p->passes.size(), 1) * q4c::kTicketsPerLaunch;
@@ -786,13 +761,12 @@ int build_device(q4c_plan *p) {
   d.slot_fnoff = sfo;
   d.slot_nfn = snf;
   d.slot_row_off = sro;
-  d.work_part_off = wpo;
+  d.batch_part_off = bpt;
   d.pair_off = poff;
   d.pair_na = pna;
   d.pair_nb = pnb;
   d.pair_a = pa;
   d.pair_b = pb;
-  d.batch_work_off = bwo;
   d.tab_off = toff;
   d.panel_off = pnoff;
   d.store_len = p->store_len;
