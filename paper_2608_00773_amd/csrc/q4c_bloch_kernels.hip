@@ -8,14 +8,15 @@
 //
 // Two kernels per chunk of at most KB k-points:
 //   k_bloch_phase  exp(i k.T) once per (contribution, k-point), [t][k] layout;
-//   k_bloch_sum    one workgroup per (cell pair, part): the cell pair's
-//                  contributions and their phases are staged in LDS, each
+//   k_bloch_sum    one workgroup per (cell pair, part, group of k-points):
+//                  contributions' offsets and phases are staged in LDS, each
 //                  thread keeps a few elements x KC k-points of complex sums
-//                  in registers, so the store is streamed ceil(n_k / KC)
-//                  times and no sine or cosine is evaluated per element.
+//                  in registers, and the stored blocks are read in their own
+//                  order, the transposed ones' sums turned once at the end.
 // The reverse direction (q4c_bloch_density, the periodic density matrix of
 // the same section) reuses k_bloch_phase with k-point weights, per stored
-// pair, and k_bloch_density runs one workgroup per stored pair.
+// pair; k_bloch_density runs one workgroup per group of stored pairs that
+// share a cell pair.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -36,7 +37,6 @@ static __device__ __align__(256) double scratch[q4c::kNoAllocScratchDoubles];
 namespace q4c {
 namespace {
 
-constexpr int KC = 8;    // k-points per register pass
 constexpr int KB = kBlochKChunk;  // k-points per phase-table chunk
 
 // ph[t][k] = w_k exp(i k.T_t) (w_k = 1 without weights)
@@ -55,142 +55,207 @@ __global__ __launch_bounds__(256) void k_bloch_phase(int n_k, int64_t n_ct, cons
   }
 }
 
-constexpr int BS_EPT = 2;  // cell elements per thread per pass
+constexpr int BS_EPT = 3;  // cell elements per thread: blocks of up to 27 x 28 functions in one go
+constexpr int BS_EL = 256 * BS_EPT;
 constexpr int BS_TB = 64;  // contributions staged in LDS at a time
+constexpr int BS_PF = 4;   // contributions whose values are loaded together
 
-// One workgroup per (cell pair c, part q): the contributions' store offsets,
-// column counts, orientations and phases for KC k-points are staged in LDS
-// (BS_TB contributions at a time) and read as broadcasts; each thread holds
-// BS_EPT elements x KC k-points of complex sums, so that one staged phase
-// serves BS_EPT elements and every stored value is read once per pass.
+// One workgroup per (cell pair c, part q) and group of kper <= KC k-points.
+// The contributions' store offsets and phases are staged in LDS (BS_TB
+// contributions at a time) and read as broadcasts; each thread holds BS_EPT
+// elements x KC k-points of complex sums, so that one staged phase serves
+// BS_EPT elements.  A cell pair's contributions come transposed ones first:
+// both kinds are read in the stored order (contiguous), the sums of the
+// transposed ones are turned through LDS and the direct ones added on.
+// Bound: HBM, the store read once (the groups of k-points of a cell pair run
+// side by side and share its L2), and the latency of those reads, hence the
+// values of the next contributions in flight while these are added.  2 x 2 x 1
+// cell (9.5M elements, 5 parts, 18 k-points, 494 MB): 414 -> 155 us (3.2 TB/s)
+// against 8 k-points at a time one launch row after the other, transposed
+// blocks read by column and two elements per thread; 301 us without the loads
+// ahead and with the groups apart.
 // ph: [n_ct][n_k] complex phases of this chunk; out: [n_k][n_parts][clen] complex.
-__global__ __launch_bounds__(256) void k_bloch_sum(DevPlan d, int n_parts, int64_t ncp, const int64_t *cp_off,
-                                                   const int64_t *ct_off, const int32_t *ct_pair,
-                                                   const int32_t *ct_flag, int n_k, const double *ph,
-                                                   const double *__restrict__ store, double *__restrict__ out) {
+template <int KC>
+__global__ __launch_bounds__(256, 2) void k_bloch_sum(DevPlan d, int n_parts, int64_t ncp, const int64_t *cp_off,
+                                                      const int64_t *ct_off, const int32_t *ct_pair,
+                                                      const int32_t *ct_flag, int n_k, int n_grp, int kper, const double *ph,
+                                                      const double *__restrict__ store, double *__restrict__ out) {
   __shared__ int64_t s_off[BS_TB];
-  __shared__ int s_nbp[BS_TB], s_tr[BS_TB];
-  __shared__ double s_ph[BS_TB][KC][2];
-  const int64_t c = blockIdx.x / n_parts;
-  const int q = (int)(blockIdx.x - c * n_parts);
+  __shared__ dbl2 s_ph[BS_TB][KC];
+  __shared__ dbl2 s_turn[BS_EL];
+  // the k-point groups of one (cell pair, part) next to each other on one XCD:
+  // they read the same blocks
+  const int64_t wg = xcd_map(blockIdx.x, gridDim.x), cq = wg / n_grp;
+  const int64_t c = cq / n_parts;
+  const int q = (int)(cq - c * n_parts);
+  const int k0 = (int)(wg - cq * n_grp) * kper, nk = min(kper, n_k - k0);
   const int64_t clen = cp_off[ncp];
   const int64_t e0 = cp_off[c], blk = cp_off[c + 1] - e0;
-  const int64_t t0 = ct_off[c], nt = ct_off[c + 1] - t0;
+  const int64_t t0 = ct_off[2 * c], tm = ct_off[2 * c + 1], t1 = ct_off[2 * c + 2];
   const double sq = (n_parts == 5 && q >= 2) ? -1.0 : 1.0;
   const int64_t L = d.store_len;
   // columns of the cell-pair block: those of the stored block (direct) or
   // its rows (transposed), the same for every contribution of the cell pair
   const int64_t p0 = ct_pair[t0];
   const int ncol = ct_flag[t0] ? d.pair_na[p0] : d.pair_nb[p0];
+  const int64_t nrow = blk / ncol;
   const int tid = threadIdx.x;
-  for (int64_t eb = 0; eb < blk; eb += 256 * BS_EPT) {
-    int ei[BS_EPT], ej[BS_EPT];
-    bool ev[BS_EPT];
+  const bool whole = blk <= BS_EL;  // workgroup-uniform: the transposed sums can be turned
+  for (int64_t eb = 0; eb < blk; eb += BS_EL) {
+    double re[BS_EPT][KC], im[BS_EPT][KC];
 #pragma unroll
-    for (int x = 0; x < BS_EPT; ++x) {
-      const int64_t le = eb + tid + 256 * x;
-      ev[x] = le < blk;
-      ei[x] = ev[x] ? (int)(le / ncol) : 0;
-      ej[x] = ev[x] ? (int)(le - (int64_t)ei[x] * ncol) : 0;
-    }
-    for (int k0 = 0; k0 < n_k; k0 += KC) {
-      double re[BS_EPT][KC], im[BS_EPT][KC];
+    for (int x = 0; x < BS_EPT; ++x)
 #pragma unroll
-      for (int x = 0; x < BS_EPT; ++x)
-#pragma unroll
-        for (int kk = 0; kk < KC; ++kk) re[x][kk] = im[x][kk] = 0.0;
-      for (int64_t tb = 0; tb < nt; tb += BS_TB) {
-        const int nb = (int)min<int64_t>(BS_TB, nt - tb);
+      for (int kk = 0; kk < KC; ++kk) re[x][kk] = im[x][kk] = 0.0;
+    // adds contributions [ta, tz), element le + 256 x at at[x] of the stored block
+    auto add = [&](int64_t ta, int64_t tz, const int64_t (&at)[BS_EPT], double sign) {
+      for (int64_t tb = ta; tb < tz; tb += BS_TB) {
+        const int nb = (int)min<int64_t>(BS_TB, tz - tb);
         __syncthreads();  // the previous batch is consumed
-        for (int x = tid; x < nb; x += 256) {
-          const int64_t pp = ct_pair[t0 + tb + x];
-          s_off[x] = (int64_t)q * L + d.pair_off[pp];
-          s_nbp[x] = d.pair_nb[pp];
-          s_tr[x] = ct_flag[t0 + tb + x];
-        }
+        for (int x = tid; x < nb; x += 256) s_off[x] = (int64_t)q * L + d.pair_off[ct_pair[tb + x]];
         for (int x = tid; x < nb * KC; x += 256) {
           const int tt = x / KC, kk = x - tt * KC;
-          const bool in = k0 + kk < n_k;
-          const double *pt = ph + 2 * ((t0 + tb + tt) * n_k + k0 + kk);
-          s_ph[tt][kk][0] = in ? pt[0] : 0.0;
-          s_ph[tt][kk][1] = in ? pt[1] : 0.0;
+          const double *pt = ph + 2 * ((tb + tt) * n_k + k0 + kk);
+          s_ph[tt][kk] = kk < nk ? dbl2{sign * pt[0], sign * pt[1]} : dbl2{0.0, 0.0};
         }
         __syncthreads();  // the batch is visible
-        for (int tt = 0; tt < nb; ++tt) {
-          const int64_t off = s_off[tt];
-          const int nbp = s_nbp[tt];
-          const bool tr = s_tr[tt] != 0;
-          double v[BS_EPT];
+        // BS_PF contributions at a time, the next ones' values loaded while
+        // these are added (past the last one: it again, with zero phases)
+        double v[2][BS_PF][BS_EPT];
+        auto load = [&](int tt, double (&w)[BS_PF][BS_EPT]) {
+#pragma unroll
+          for (int u = 0; u < BS_PF; ++u) {
+            const double *b = store + s_off[min(tt + u, nb - 1)];
+#pragma unroll
+            for (int x = 0; x < BS_EPT; ++x) w[u][x] = b[at[x]];
+          }
+        };
+        auto sum = [&](int tt, const double (&w)[BS_PF][BS_EPT]) {
+#pragma unroll
+          for (int u = 0; u < BS_PF; ++u)
+            if (tt + u < nb) {  // workgroup-uniform
+#pragma unroll
+              for (int kk = 0; kk < KC; ++kk) {
+                const dbl2 f = s_ph[tt + u][kk];
+#pragma unroll
+                for (int x = 0; x < BS_EPT; ++x) {
+                  re[x][kk] = fma(f[0], w[u][x], re[x][kk]);
+                  im[x][kk] = fma(f[1], w[u][x], im[x][kk]);
+                }
+              }
+            }
+        };
+        load(0, v[0]);
+        for (int tt = 0; tt < nb; tt += 2 * BS_PF) {
+          load(tt + BS_PF, v[1]);
+          __builtin_amdgcn_sched_barrier(0);
+          sum(tt, v[0]);
+          __builtin_amdgcn_sched_barrier(0);
+          load(tt + 2 * BS_PF, v[0]);
+          __builtin_amdgcn_sched_barrier(0);
+          sum(tt + BS_PF, v[1]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    };
+    int64_t at[BS_EPT], turned[BS_EPT];
+#pragma unroll
+    for (int x = 0; x < BS_EPT; ++x) {
+      const int64_t le = min<int64_t>(eb + tid + 256 * x, blk - 1);  // beyond the block: its last element, not written
+      const int64_t i = le / ncol, j = le - i * ncol;
+      at[x] = le;
+      turned[x] = j * nrow + i;
+    }
+    if (t0 < tm && whole) {
+      add(t0, tm, at, sq);
+#pragma unroll
+      for (int kk = 0; kk < KC; ++kk) {
+        if (kk < nk) {      // workgroup-uniform
+          __syncthreads();  // the previous k-point is read
+#pragma unroll
+          for (int x = 0; x < BS_EPT; ++x) s_turn[tid + 256 * x] = dbl2{re[x][kk], im[x][kk]};
+          __syncthreads();
 #pragma unroll
           for (int x = 0; x < BS_EPT; ++x) {
-            const int64_t a = tr ? off + (int64_t)ej[x] * nbp + ei[x] : off + (int64_t)ei[x] * nbp + ej[x];
-            v[x] = ev[x] ? store[a] : 0.0;
-            if (tr) v[x] *= sq;
-          }
-#pragma unroll
-          for (int kk = 0; kk < KC; ++kk) {
-            const double cs = s_ph[tt][kk][0], sn = s_ph[tt][kk][1];
-#pragma unroll
-            for (int x = 0; x < BS_EPT; ++x) {
-              re[x][kk] += cs * v[x];
-              im[x][kk] += sn * v[x];
-            }
+            re[x][kk] = s_turn[turned[x]][0];
+            im[x][kk] = s_turn[turned[x]][1];
           }
         }
       }
+    } else {
+      add(t0, tm, turned, sq);
+    }
+    add(tm, t1, at, 1.0);
 #pragma unroll
-      for (int x = 0; x < BS_EPT; ++x)
-        if (ev[x]) {
+    for (int x = 0; x < BS_EPT; ++x) {
+      const int64_t le = eb + tid + 256 * x;
+      if (le < blk) {
 #pragma unroll
-          for (int kk = 0; kk < KC; ++kk)
-            if (k0 + kk < n_k) {
-              const int64_t o = ((int64_t)(k0 + kk) * n_parts + q) * clen + e0 + eb + tid + 256 * x;
-              out[2 * o] = re[x][kk];
-              out[2 * o + 1] = im[x][kk];
-            }
-        }
+        for (int kk = 0; kk < KC; ++kk)
+          if (kk < nk)
+            *reinterpret_cast<dbl2 *>(out + 2 * (((int64_t)(k0 + kk) * n_parts + q) * clen + e0 + le)) =
+                dbl2{re[x][kk], im[x][kk]};
+      }
     }
   }
 }
 
-// The reverse direction (the periodic density matrix of Sec. II C): one
-// workgroup per stored image pair p = (A', B') (grouped by cell pair, so that
-// a cell pair's rho is re-read from one L2), one thread per element (i, j):
+// The reverse direction (the periodic density matrix of Sec. II C): a group
+// of up to kBlochGroup stored image pairs p = (A', B') of one cell pair in one
+// orientation, one thread per element (i, j):
 //   coef = f Re sum_k w_k exp(i k.(T_B' - T_A')) rho_ab(k)[i][j],
 // rho_ab(k)[i][j] = conj(rho_ba(k)[j][i]) when the cell atoms run a > b,
-// f = 2 off the self pairs.  ph: [n_pairs][n_k] weighted phases of this
-// chunk (uniform per workgroup); rho: this chunk's [n_k][n_parts][clen]
-// complex; acc: add to coef.
-__global__ __launch_bounds__(256) void k_bloch_density(DevPlan d, int n_parts, int64_t n_pairs, int64_t ncp,
+// f = 2 off the self pairs.  Each rho value read serves the whole group.
+// Bound: L2 reads of rho, once per group (one pair per workgroup read it for
+// every pair: 168 -> 50 us for 15k pairs and 18 k-points).  ph:
+// [n_pairs][n_k] weighted phases of this chunk (uniform per workgroup); rho:
+// this chunk's [n_k][n_parts][clen] complex; acc: add to coef.
+__global__ __launch_bounds__(256) void k_bloch_density(DevPlan d, int n_parts, int64_t n_groups, int64_t ncp,
                                                        const int64_t *cp_off, const int32_t *pc_cp,
-                                                       const int32_t *pc_flag, const int32_t *pc_order, int n_k,
+                                                       const int32_t *pc_flag, const int32_t *pc_order,
+                                                       const int32_t *pc_group, int n_k,
                                                        const double *__restrict__ ph,
                                                        const double *__restrict__ rho, int acc,
                                                        double *__restrict__ coef) {
-  // the image pairs of one cell pair run one after another on one XCD
-  const int64_t p = pc_order[xcd_map(blockIdx.x, n_pairs)];
-  const int64_t L = d.store_len;
-  const int64_t clen = cp_off[ncp];
-  const int na = d.pair_na[p], nb = d.pair_nb[p];
-  const int64_t blk = (int64_t)na * nb, po = d.pair_off[p];
-  const bool tr = pc_flag[p] != 0;
-  const int64_t ce0 = cp_off[pc_cp[p]];
+  constexpr int G = kBlochGroup;
+  // the groups of one cell pair run one after another on one XCD
+  const int64_t g = xcd_map(blockIdx.x, n_groups);
+  const int first = pc_group[g], np = pc_group[g + 1] - first;
+  const int64_t p0 = pc_order[first];
+  const int64_t L = d.store_len, clen = cp_off[ncp];
+  const int na = d.pair_na[p0], nb = d.pair_nb[p0];
+  const int64_t blk = (int64_t)na * nb;
+  const int64_t e = (int64_t)blockIdx.y * 256 + threadIdx.x;
+  if (e >= blk) return;
+  const bool tr = pc_flag[p0] != 0;
   const double sg = tr ? 1.0 : -1.0;  // Re(e^{i t} r) = c Re r - s Im r; conj(r): c Re r + s Im r
-  const double f = d.pair_a[p] == d.pair_b[p] ? 1.0 : 2.0;
-  const double *pp = ph + 2 * p * n_k;
-  for (int q = 0; q < n_parts; ++q)
-    for (int64_t e = threadIdx.x; e < blk; e += blockDim.x) {
-      const int i = (int)(e / nb), j = (int)(e - (int64_t)i * nb);
-      // element of the cell-pair block: (i, j) of (a, b), or (j, i) of (b, a)
-      const int64_t ce = ce0 + (tr ? (int64_t)j * na + i : (int64_t)i * nb + j);
-      double s = 0.0;
-      for (int k = 0; k < n_k; ++k) {
-        const double *r = rho + 2 * (((int64_t)k * n_parts + q) * clen + ce);
-        s += pp[2 * k] * r[0] + sg * pp[2 * k + 1] * r[1];
-      }
-      double *o = coef + (int64_t)q * L + po + e;
-      *o = acc ? *o + f * s : f * s;
+  // element of the cell-pair block: (i, j) of (a, b), or (j, i) of (b, a)
+  const int i = (int)(e / nb), j = (int)(e - (int64_t)i * nb);
+  const int64_t ce = cp_off[pc_cp[p0]] + (tr ? (int64_t)j * na + i : e);
+  const double *pp[G];  // the pairs' phases (uniform)
+#pragma unroll
+  for (int x = 0; x < G; ++x) pp[x] = ph + 2 * (int64_t)pc_order[first + min(x, np - 1)] * n_k;
+  for (int q = 0; q < n_parts; ++q) {
+    double s[G];
+#pragma unroll
+    for (int x = 0; x < G; ++x) s[x] = 0.0;
+#pragma unroll 2
+    for (int k = 0; k < n_k; ++k) {
+      const dbl2 r = *reinterpret_cast<const dbl2 *>(rho + 2 * (((int64_t)k * n_parts + q) * clen + ce));
+      const double ri = sg * r[1];
+#pragma unroll
+      for (int x = 0; x < G; ++x) s[x] = fma(pp[x][2 * k + 1], ri, fma(pp[x][2 * k], r[0], s[x]));
     }
+#pragma unroll
+    for (int x = 0; x < G; ++x) {
+      if (x < np) {  // workgroup-uniform
+        const int64_t p = pc_order[first + x];
+        const double f = d.pair_a[p] == d.pair_b[p] ? 1.0 : 2.0;
+        double *o = coef + (int64_t)q * L + d.pair_off[p] + e;
+        *o = acc ? *o + f * s[x] : f * s[x];
+      }
+    }
+  }
 }
 
 }  // namespace
@@ -220,10 +285,22 @@ static int launch_bloch_sum_chunks(const q4c_plan *p, int n_parts, const double 
     {
       std::optional<TimedLaunch> tl_;
       if (timed) tl_.emplace(p, Q4C_TIMER_BLOCH, s);
-      const unsigned grid = (unsigned)(ncp * n_parts);
-      hipLaunchKernelGGL(k_bloch_sum, dim3(grid), dim3(256), 0, s, p->dp, n_parts, ncp, p->d_cp_off, p->d_ct_off,
-                         p->d_ct_pair, p->d_ct_flag, nk, (const double *)phase, store,
-                         out + 2 * (int64_t)k0 * n_parts * clen);
+      // k-points in equal groups of at most 9 (a thread's registers hold 3
+      // elements x 9 complex sums)
+      const int groups = (nk + 8) / 9, kper = (nk + groups - 1) / groups;
+      auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(ncp * n_parts * groups)), dim3(256), 0, s, p->dp, n_parts, ncp,
+                           p->d_cp_off, p->d_ct_off, p->d_ct_pair, p->d_ct_flag, nk, groups, kper,
+                           (const double *)phase, store, out + 2 * (int64_t)k0 * n_parts * clen);
+      };
+      if (kper <= 2)
+        launch(k_bloch_sum<2>);
+      else if (kper <= 4)
+        launch(k_bloch_sum<4>);
+      else if (kper <= 6)
+        launch(k_bloch_sum<6>);
+      else
+        launch(k_bloch_sum<9>);
     }
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "k_bloch_sum");
@@ -289,8 +366,10 @@ int launch_bloch_density(const q4c_plan *p, int n_parts, const double *rho, int 
     if (e != hipSuccess) return hip_fail(e, "k_bloch_phase");
     {
       TimedLaunch tl_(p, Q4C_TIMER_BLOCH, s);
-      hipLaunchKernelGGL(k_bloch_density, dim3((unsigned)np_), dim3(256), 0, s, p->dp, n_parts, np_, ncp,
-                         p->d_cp_off, p->d_pc_cp, p->d_pc_flag, p->d_pc_order, nk, (const double *)phase,
+      const int64_t ng = p->n_bloch_groups;
+      hipLaunchKernelGGL(k_bloch_density, dim3((unsigned)ng, (unsigned)((p->max_pair_block + 255) / 256)), dim3(256), 0,
+                         s, p->dp, n_parts, ng, ncp, p->d_cp_off, p->d_pc_cp, p->d_pc_flag, p->d_pc_order,
+                         p->d_pc_group, nk, (const double *)phase,
                          rho + 2 * (int64_t)k0 * n_parts * clen, k0 > 0 ? 1 : 0, coef);
     }
     e = hipGetLastError();

@@ -246,13 +246,16 @@ struct q4c_plan {
   std::vector<int32_t> cp_a, cp_b;      // [n_cell_pairs]
   std::vector<int64_t> cp_off;          // [n_cell_pairs + 1] block offsets (n_a n_b each)
   int32_t *d_cp_a = nullptr, *d_cp_b = nullptr;
-  int64_t *d_cp_off = nullptr, *d_ct_off = nullptr;  // contributions of cell pair c: [ct_off[c], ct_off[c+1])
+  // contributions of cell pair c: transposed ones [ct_off[2c], ct_off[2c+1]), direct ones [ct_off[2c+1], ct_off[2c+2])
+  int64_t *d_cp_off = nullptr, *d_ct_off = nullptr;
   int32_t *d_ct_pair = nullptr, *d_ct_flag = nullptr;  // stored pair; 1: transposed orientation
   double *d_ct_T = nullptr;             // [3 per contribution] translation of the phase exp(i k.T)
   int64_t n_contrib = 0;                // contributions over all cell pairs
   int32_t *d_pc_cp = nullptr, *d_pc_flag = nullptr;  // per stored pair: cell pair; 1: reached transposed (a > b)
   double *d_pc_T = nullptr;             // [3 per stored pair] T_B' - T_A'
-  int32_t *d_pc_order = nullptr;        // stored pairs sorted by cell pair
+  int32_t *d_pc_order = nullptr;        // stored pairs sorted by cell pair and orientation
+  int32_t *d_pc_group = nullptr;        // first entry in d_pc_order of each group of at most kBlochGroup pairs
+  int64_t n_bloch_groups = 0;
   mutable double *d_kpts = nullptr;     // k-points (3 n_k) and weights (n_k) of the last call (grown on demand)
   mutable int64_t kpts_cap = 0;
   mutable double *d_bloch_ph = nullptr; // phases of one k chunk: kBlochKChunk max(n_contrib, n_pairs) complex
@@ -317,6 +320,7 @@ int launch_grad_pass(const q4c_plan *p, size_t ip, const double *coef, const dou
 // Bloch sums of a store over the plan's cell pairs (q4c_bloch_kernels.hip),
 // k-points in chunks of kBlochKChunk; phase: 2 kBlochKChunk n_contrib doubles
 constexpr int kBlochKChunk = 64;
+constexpr int kBlochGroup = 8;  // stored pairs of one k_bloch_density workgroup
 int launch_bloch_sum(const q4c_plan *p, int n_parts, const double *store, int n_k, const double *kpts_dev,
                      double *phase, double *out, hipStream_t s);
 // q4c_bloch_sum_noalloc: the phase table in the library's fixed device

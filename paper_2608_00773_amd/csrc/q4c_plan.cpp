@@ -1522,7 +1522,12 @@ int q4c_plan_set_cells(q4c_plan *p, int32_t n_cell_atoms, const int32_t *cell_at
     ca.push_back(a);
     cb.push_back(b);
     coff.push_back(coff.back() + (int64_t)nf[a] * nf[b]);
+    // transposed contributions first (k_bloch_sum turns their sums once)
+    std::stable_sort(kv.second.begin(), kv.second.end(),
+                     [](const std::pair<int64_t, int> &x, const std::pair<int64_t, int> &y) { return x.second > y.second; });
+    size_t n_tr = 0;
     for (auto &e : kv.second) {
+      n_tr += e.second;
       const int A = p->pair_a[e.first], B = p->pair_b[e.first];
       // phase exp(i k.(T_col - T_row)): rows of the target block are the row atom's images
       const int rowat = e.second ? B : A, colat = e.second ? A : B;
@@ -1530,6 +1535,7 @@ int q4c_plan_set_cells(q4c_plan *p, int32_t n_cell_atoms, const int32_t *cell_at
       ct_flag.push_back(e.second);
       for (int d = 0; d < 3; ++d) ct_T.push_back(shift[3 * colat + d] - shift[3 * rowat + d]);
     }
+    ctoff.push_back(ctoff.back() + (int64_t)n_tr);
     ctoff.push_back((int64_t)ct_pair.size());
   }
   p->n_cell_atoms = n_cell_atoms;
@@ -1555,7 +1561,14 @@ int q4c_plan_set_cells(q4c_plan *p, int32_t n_cell_atoms, const int32_t *cell_at
   // rho for all of its image pairs; consecutive ones share an XCD's L2)
   std::vector<int32_t> pc_order(p->n_pairs);
   for (int64_t q = 0; q < p->n_pairs; ++q) pc_order[q] = (int32_t)q;
-  std::stable_sort(pc_order.begin(), pc_order.end(), [&](int32_t x, int32_t y) { return pc_cp[x] < pc_cp[y]; });
+  auto key = [&](int32_t x) { return 2 * (int64_t)pc_cp[x] + pc_flag[x]; };
+  std::stable_sort(pc_order.begin(), pc_order.end(), [&](int32_t x, int32_t y) { return key(x) < key(y); });
+  std::vector<int32_t> pc_group;
+  for (int32_t i = 0; i < (int32_t)p->n_pairs; ++i)
+    if (i == 0 || key(pc_order[i]) != key(pc_order[i - 1]) || i - pc_group.back() == q4c::kBlochGroup)
+      pc_group.push_back(i);
+  p->n_bloch_groups = (int64_t)pc_group.size();
+  pc_group.push_back((int32_t)p->n_pairs);
   if (!p->on_device) return Q4C_OK;
   int rc = check_plan_dev(p);
   if (rc != Q4C_OK) return rc;
@@ -1571,6 +1584,7 @@ int q4c_plan_set_cells(q4c_plan *p, int32_t n_cell_atoms, const int32_t *cell_at
   if ((rc = upload(p, pc_flag, &p->d_pc_flag)) != Q4C_OK) return rc;
   if ((rc = upload(p, pc_T, &p->d_pc_T)) != Q4C_OK) return rc;
   if ((rc = upload(p, pc_order, &p->d_pc_order)) != Q4C_OK) return rc;
+  if ((rc = upload(p, pc_group, &p->d_pc_group)) != Q4C_OK) return rc;
   return Q4C_OK;
 }
 
