@@ -106,6 +106,7 @@ struct Pass {
   int64_t panel_len;     // doubles (operand panels, stored after the partials)
   int64_t di0, di1;      // adjoint items (d_den, d_den_cost)
   int64_t bi0, bi1;      // forward block items (d_blocks, d_blocks_cost)
+  int32_t p_max;         // points of its largest batch
 };
 
 // Scalar -> spinor transformation (Eq. 33): coefficients of one spinor type

@@ -4,8 +4,8 @@
 //                    functions at its points (Eq. 12a, App. B), as the
 //                    panels compute them; FP64 or FP32 hi + lo output.
 //  k_om              w_g v_g per active point (the weighting of Eq. 29).
-//  k_panel           per (batch, 64-function tile): phi and grad phi at all
-//                    batch points into the batch's operand panel (HBM).
+//  k_panel           per (batch, function tile, 64 points): phi and grad phi
+//                    into the batch's operand panel (HBM).
 //  k_contract_*      per (batch, tile ti <= tj) work item, or smaller items of
 //                    it: the weighted products
 //                        V  = Phi^T diag(w v) Phi
@@ -123,7 +123,6 @@ struct TileMeta {
   double rc[T];                // cutoffs (0 for padding)
   double k1[T], k2[T];         // nint^2 / rcut, rcut / nint^2
   int64_t coef[T];             // offset of the shell's table
-  int64_t uoff[T];             // offset of the shell's ket-potential table (H/S panels)
   int nint[T], lm[T];
   int order[T];                // tile functions sorted by lm
 };
@@ -145,7 +144,6 @@ __device__ __forceinline__ void load_tile_meta(const DevPlan &d, TileMeta &M, in
       M.k1[tid] = d.shell_knot[2 * sh];
       M.k2[tid] = d.shell_knot[2 * sh + 1];
       M.coef[tid] = d.shell_coef_off[sh];
-      M.uoff[tid] = d.shell_u_off ? d.shell_u_off[sh] : 0;
       M.nint[tid] = d.shell_nint[sh];
       M.lm[tid] = shlm & 31;
     } else {
@@ -153,7 +151,6 @@ __device__ __forceinline__ void load_tile_meta(const DevPlan &d, TileMeta &M, in
       M.rc[tid] = 0.0;
       M.k1[tid] = M.k2[tid] = 0.0;
       M.coef[tid] = 0;
-      M.uoff[tid] = 0;
       M.nint[tid] = 0;
       M.lm[tid] = 32;  // padding sorts last
     }
@@ -167,9 +164,27 @@ __device__ __forceinline__ void load_tile_meta(const DevPlan &d, TileMeta &M, in
   }
 }
 
-// phi and grad phi of tile function m at point (px, py, pz); see tab_one.
-// 1/s comes from a Newton-refined reciprocal square root, and the interval
-// index from an approximate square root corrected against the exact knots.
+// Radial interval of a shell (cutoff > s) at distance s: index j and s - r_j.
+// The index comes from an approximate square root corrected against the exact
+// knots r_j = j^2 k2.
+__device__ __forceinline__ int radial_interval(double s, int n, double k1, double k2, double &dd) {
+  const double u = s * k1;
+  int j = u > 0.0 ? (int)(u * __builtin_amdgcn_rsq(u)) : 0;
+  j = j < 0 ? 0 : (j > n - 1 ? n - 1 : j);
+  double rj = (double)j * (double)j * k2;
+  if (s < rj && j > 0) {
+    --j;
+    rj = (double)j * (double)j * k2;
+  } else if (j < n - 1 && s >= (double)(j + 1) * (double)(j + 1) * k2) {
+    ++j;
+    rj = (double)j * (double)j * k2;
+  }
+  dd = s - rj;
+  return j;
+}
+
+// phi and grad phi of tile function m at point (px, py, pz).  1/s comes from a
+// Newton-refined reciprocal square root.
 __device__ __forceinline__ void tab_meta(const DevPlan &d, const TileMeta &M, int m, double px, double py,
                                          double pz, double &f, double &fx, double &fy, double &fz) {
   const double dx = px - M.ax[m], dy = py - M.ay[m], dz = pz - M.az[m];
@@ -185,20 +200,8 @@ __device__ __forceinline__ void tab_meta(const DevPlan &d, const TileMeta &M, in
     rinv = rinv * (1.5 - 0.5 * s2 * rinv * rinv);
     s = s2 * rinv;
   }
-  const int n = M.nint[m];
-  const double k1 = M.k1[m], k2 = M.k2[m];
-  const double u = s * k1;
-  int j = u > 0.0 ? (int)(u * __builtin_amdgcn_rsq(u)) : 0;
-  j = j < 0 ? 0 : (j > n - 1 ? n - 1 : j);
-  double rj = (double)j * (double)j * k2;
-  if (s < rj && j > 0) {
-    --j;
-    rj = (double)j * (double)j * k2;
-  } else if (j < n - 1 && s >= (double)(j + 1) * (double)(j + 1) * k2) {
-    ++j;
-    rj = (double)j * (double)j * k2;
-  }
-  const double dd = s - rj;
+  double dd;
+  const int j = radial_interval(s, M.nint[m], M.k1[m], M.k2[m], dd);
   const dbl4 c = *reinterpret_cast<const dbl4 *>(d.coef + M.coef[m] + 4 * (int64_t)j);
   const double R = ((c[3] * dd + c[2]) * dd + c[1]) * dd + c[0];
   const double q = ((3.0 * c[3] * dd + 2.0 * c[2]) * dd + c[1]) * rinv;  // Rt'(s) / s
@@ -208,48 +211,6 @@ __device__ __forceinline__ void tab_meta(const DevPlan &d, const TileMeta &M, in
   fx = q * dx * S + R * gx;
   fy = q * dy * S + R * gy;
   fz = q * dz * S + R * gz;
-}
-
-// phi and psi = u phi / 2 of tile function m at (px, py, pz): the H/S panels.
-// u, the shell's ket potential, is a cubic on the radial table's own knots,
-// so it is evaluated on the same interval.
-__device__ __forceinline__ void tab_meta_hs(const DevPlan &d, const TileMeta &M, int m, double px, double py,
-                                            double pz, double &f, double &psi) {
-  const double dx = px - M.ax[m], dy = py - M.ay[m], dz = pz - M.az[m];
-  const double s2 = dx * dx + dy * dy + dz * dz;
-  const double rc = M.rc[m];
-  if (!(s2 < rc * rc)) {
-    f = psi = 0.0;
-    return;
-  }
-  double s = 0.0;
-  if (s2 > 0.0) {
-    double rinv = __builtin_amdgcn_rsq(s2);
-    rinv = rinv * (1.5 - 0.5 * s2 * rinv * rinv);
-    s = s2 * rinv;
-  }
-  const int n = M.nint[m];
-  const double k1 = M.k1[m], k2 = M.k2[m];
-  const double u = s * k1;
-  int j = u > 0.0 ? (int)(u * __builtin_amdgcn_rsq(u)) : 0;
-  j = j < 0 ? 0 : (j > n - 1 ? n - 1 : j);
-  double rj = (double)j * (double)j * k2;
-  if (s < rj && j > 0) {
-    --j;
-    rj = (double)j * (double)j * k2;
-  } else if (j < n - 1 && s >= (double)(j + 1) * (double)(j + 1) * k2) {
-    ++j;
-    rj = (double)j * (double)j * k2;
-  }
-  const double dd = s - rj;
-  const dbl4 c = *reinterpret_cast<const dbl4 *>(d.coef + M.coef[m] + 4 * (int64_t)j);
-  const dbl4 e = *reinterpret_cast<const dbl4 *>(d.ucoef + M.uoff[m] + 4 * (int64_t)j);
-  const double R = ((c[3] * dd + c[2]) * dd + c[1]) * dd + c[0];
-  const double U = ((e[3] * dd + e[2]) * dd + e[1]) * dd + e[0];
-  double S, gx, gy, gz;
-  solid_harmonic(M.lm[m], dx, dy, dz, S, gx, gy, gz);
-  f = R * S;
-  psi = 0.5 * U * f;
 }
 
 // ---------------------------------------------------------------------------
@@ -339,10 +300,7 @@ __global__ void k_om(DevPlan d, const double *v, double *om) {
     om[g] = g < n ? d.pw[g] * v[d.perm[g]] : 0.0;
 }
 
-// One (batch, function tile of 64): tabulate the tile's functions at all
-// points of the batch into the panel.  Each group of 8 points is computed in
-// lm order (few divergent harmonic branches per wave) into LDS, then written
-// out as contiguous runs of the tile's functions.  Panel kinds:
+// Panel kinds:
 //   PK_F64:   phi, d/dx, d/dy, d/dz in FP64 (4 planes of Pp np doubles)
 //   PK_HS:    phi and psi = u phi / 2 in FP64 (2 planes)
 //   PK_F32:   phi in FP64 (1 plane), then sqrt|w v| times d/dx, d/dy, d/dz
@@ -363,6 +321,7 @@ enum { PK_F64 = 0, PK_HS = 1, PK_F32 = 2, PK_SPLIT = 3, PK_BF16 = 4 };
 // |x - x1 - x2 - x3| <= (2^-24 + 2^-24) |x|.  Part k of both values comes
 // as one word wk (a in the low half, b in the high half), from one packed
 // conversion per part.
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
@@ -375,96 +334,230 @@ __device__ __forceinline__ void split3_bf16x2(double a, double b, uint32_t &w1, 
   w2 = pack_bf16(ra, rb);
   w3 = pack_bf16(ra - __uint_as_float(w2 << 16), rb - __uint_as_float(w2 & 0xffff0000u));
 }
-constexpr int PLD = T + 1;  // padded LDS row of the panel stage
+
+// One wave (a workgroup of its own: nothing is shared) per (batch, T / sub
+// functions, 64 points), one point per lane.  All lanes work on the same
+// function, so a shell's interval search, table read and cubic are done once
+// for its 2 l + 1 functions, no branch diverges and the functions' data come
+// from scalar registers (lane k holds the wave's function k); the table entry
+// of the next shell is fetched while this one's rows are formed.  The values
+// of neighbouring panel rows are staged in LDS and written out as whole
+// 128-byte lines: four rows of an FP64 plane, eight of an FP32 or BF16 plane.
+// Bound by the writes: 10.9 GB of FP64 panels (120 atoms, 2.2 M points) take
+// 2.05 ms, 5.3 TB/s (a fill reaches 6.6), 0.9 ms without the stores; tiles of 64
+// functions staged by a workgroup, every function on its own, took 2.43 ms.
+// The FP32 kind 1.07 -> 0.85 ms (48 atoms), BF16 2.51 -> 1.68 ms, H/S 1.93 ->
+// 1.16 ms.  What did not reach this: 32-byte stores straight from the lanes
+// (4.9 ms: 16 requests to L2 each), rows cut at the atoms (2.85 ms: a line
+// that two workgroups write is written twice), 64-byte runs of the BF16 planes
+// (2.85 ms).
+// Points P .. Pp - 1 and rows n .. np - 1 are written as zeros.
+// the staged bytes are written and read as different types
+typedef double stage_f64 __attribute__((may_alias));
+typedef float stage_f32 __attribute__((may_alias));
+typedef uint16_t stage_u16 __attribute__((may_alias));
+typedef u32x4 stage_u32x4 __attribute__((may_alias));
+constexpr int PR8 = 576, PR4 = 272, PR2 = 144;  // bytes of a staged row: 64 values and a pad against bank conflicts
+constexpr int panel_stage(int kind) {           // staged bytes per wave: four rows of the FP64 planes, eight of the others
+  return kind == PK_F64   ? 16 * PR8
+         : kind == PK_HS  ? 8 * PR8
+         : kind == PK_F32 ? 4 * PR8 + 24 * PR4
+         : kind == PK_SPLIT ? 4 * PR8 + 48 * PR4
+                            : 4 * PR8 + 72 * PR2;
+}
+// lane k's value of a vector register as a scalar
+__device__ __forceinline__ int64_t lane_i64(int64_t v, int k) {
+  const uint32_t lo = __builtin_amdgcn_readlane((int)v, k), hi = __builtin_amdgcn_readlane((int)(v >> 32), k);
+  return (int64_t)((uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ double lane_f64(double v, int k) {
+  return __builtin_bit_cast(double, lane_i64(__builtin_bit_cast(int64_t, v), k));
+}
 
 template <int KIND>
-__global__ __launch_bounds__(256) void k_panel(DevPlan d, const WorkItem *tiles, int64_t t0, int64_t nt,
-                                               double *panel, const double *om) {
-  constexpr bool HS = KIND == PK_HS;
-  constexpr int NQ = HS ? 2 : 4;  // components: phi, psi (H/S) or phi and its gradient
-  constexpr int CP = 8;           // points per chunk: a small stage keeps 7 workgroups on a CU
-  __shared__ TileMeta M;
-  __shared__ double st[NQ * CP * PLD];
-  __shared__ double s_sw[CP];  // PK_BF16: sqrt|w v| at the chunk's points
-  const WorkItem it = tiles[t0 + xcd_map(blockIdx.x, nt)];
-  const int b = it.batch;
+__global__ __launch_bounds__(64, 3) void k_panel(DevPlan d, const WorkItem *tiles, int64_t t0, int64_t nt,
+                                                             int sub, int npb, double *panel, const double *om) {
+  __shared__ __attribute__((aligned(16))) unsigned char st[panel_stage(KIND)];
+  // neighbouring waves (of one batch) on one XCD
+  const int64_t bid = xcd_map(blockIdx.x, nt * sub * npb), pos = bid / npb;
+  const int p0 = 64 * (int)(bid % npb);
+  const WorkItem it = tiles[t0 + pos / sub];
+  const int b = it.batch, rows = T / sub;
   const int g0 = d.batch_pt_off[b], P = d.batch_pt_off[b + 1] - g0;
   const int f0 = d.batch_fn_off[b], n = d.batch_fn_off[b + 1] - f0;
+  const int r0 = it.ti * T + (int)(pos % sub) * rows;
   const int Pp = (int)pad16(P), np = (int)pad16(n);
-  const int r0 = it.ti * T;
-  const int nrow = np - r0 < T ? np - r0 : T;  // panel rows of this tile
-  load_tile_meta(d, M, f0, n, r0);
-  __syncthreads();
+  if (r0 >= np || p0 >= Pp) return;
+  const int r1 = r0 + rows < np ? r0 + rows : np, rn = r1 < n ? r1 : n;  // rows written; of functions
+  const int lane = threadIdx.x;
+  // lane k: function r0 + k
+  const int mine = r0 + lane < n ? r0 + lane : n - 1;
+  const int fn = d.loc_fn[f0 + mine], m_atom = d.fn_atom[fn], m_shlm = d.fn_shlm[fn], m_sh = m_shlm >> 5;
+  const int m_lm = m_shlm & 31, m_l = (m_lm >= 1) + (m_lm >= 4) + (m_lm >= 9) + (m_lm >= 16);
+  const double m_ax = d.R[3 * m_atom], m_ay = d.R[3 * m_atom + 1], m_az = d.R[3 * m_atom + 2];
+  const double m_rc = d.shell_rcut[m_sh], m_k1 = d.shell_knot[2 * m_sh], m_k2 = d.shell_knot[2 * m_sh + 1];
+  const int m_nint = d.shell_nint[m_sh];
+  const int64_t m_coef = d.shell_coef_off[m_sh], m_u = KIND == PK_HS ? d.shell_u_off[m_sh] : 0;
+  // the first function's shell may begin before r0
+  const int i_first = r0 - __builtin_amdgcn_readlane(m_lm - m_l * m_l, 0);
   double *pb = panel + d.panel_off[b];
-  float *pf = reinterpret_cast<float *>(pb + (int64_t)Pp * np);  // FP32 planes (PK_F32, PK_SPLIT)
-  const int64_t fplane = (int64_t)Pp * np;
-  for (int g8 = 0; g8 < Pp; g8 += CP) {
-    if ((KIND == PK_BF16 || KIND == PK_F32) && threadIdx.x < CP)  // visible after the stage's barrier
-      s_sw[threadIdx.x] = g8 + (int)threadIdx.x < P ? sqrt(fabs(om[g0 + g8 + threadIdx.x])) : 0.0;
-    for (int e = threadIdx.x; e < T * CP; e += 256) {
-      const int k = e / CP, pt = e % CP;
-      const int fl = M.order[k];
-      double f = 0.0, fx = 0.0, fy = 0.0, fz = 0.0;
-      const int g = g8 + pt;
-      if (HS) {
-        if (M.nint[fl] > 0 && g < P) tab_meta_hs(d, M, fl, d.px[g0 + g], d.py[g0 + g], d.pz[g0 + g], f, fx);
-      } else {
-        if (M.nint[fl] > 0 && g < P) tab_meta(d, M, fl, d.px[g0 + g], d.py[g0 + g], d.pz[g0 + g], f, fx, fy, fz);
-      }
-      st[(0 * CP + pt) * PLD + fl] = f;
-      st[(1 * CP + pt) * PLD + fl] = fx;
-      if (!HS) {
-        st[(2 * CP + pt) * PLD + fl] = fy;
-        st[(3 * CP + pt) * PLD + fl] = fz;
-      }
-    }
-    __syncthreads();
-    // (q, point quad) runs: rows r0 .. r0 + nrow - 1, 4 points each, contiguous
-    constexpr int NQW = KIND == PK_BF16 ? 1 : NQ;  // PK_BF16: phi here, the gradient below
+  const int64_t plane = (int64_t)Pp * np;
+  constexpr int NQ = KIND == PK_HS ? 2 : KIND == PK_F64 ? 4 : 1;  // FP64 planes
+  const int pt = p0 + lane;
+  const bool live = pt < P;
+  const int g = g0 + (live ? pt : 0);
+  const double px = d.px[g], py = d.py[g], pz = d.pz[g];
+  double sw = 0.0;
+  if (KIND == PK_F32 || KIND == PK_BF16) sw = live ? sqrt(fabs(om[g])) : 0.0;
+  constexpr int S4 = 4 * NQ * PR8, N4 = KIND == PK_F32 ? 3 : KIND == PK_SPLIT ? 6 : 0;  // FP32 planes staged from S4 on
+  constexpr int S2 = 4 * NQ * PR8, N2 = KIND == PK_BF16 ? 9 : 0;                         // BF16 planes from S2 on
+  // writes the staged group of four (panel rows 4 r4 .. 4 r4 + 3), by global
+  // stores: 16-byte buffer stores with the offset in a scalar register have
+  // written registers that the next instructions had already reused
+  auto flush = [&](int r4) {
+    // every lane has staged its values: the barrier (no instruction) also
+    // keeps the compiler from running lanes with different radial branches
+    // through here apart
+    __builtin_amdgcn_wave_barrier();
+    {
+      // FP64 planes: 8 quads of four rows per store, 16 bytes per lane
+      const int row = (lane >> 1) & 3, qd = lane >> 3;
 #pragma unroll
-    for (int q = 0; q < NQW; ++q)
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t vo = ((uint32_t)(8 * h + qd) * np + row) * 32u + 16u * (lane & 1);
+        if (p0 + 32 * h + 4 * qd < Pp) {
 #pragma unroll
-      for (int p4 = 0; p4 < CP / 4; ++p4) {
-        const int e = threadIdx.x;  // 256 = 64 rows x 4 points
-        const int il = e >> 2, pp = e & 3;
-        if (il < nrow) {
-          const double x = st[(q * CP + 4 * p4 + pp) * PLD + il];
-          if (KIND == PK_F64 || KIND == PK_HS || q == 0) {
-            pb[((int64_t)(q * (Pp >> 2) + (g8 >> 2) + p4) * np + r0 + il) * 4 + pp] = x;
-          } else {
-            const int64_t o = ((int64_t)((q - 1) * (Pp >> 2) + (g8 >> 2) + p4) * np + r0 + il) * 4 + pp;
-            const float hi = KIND == PK_F32 ? (float)(s_sw[4 * p4 + pp] * x) : (float)x;
-            pf[o] = hi;
-            if (KIND == PK_SPLIT) pf[3 * fplane + o] = (float)(x - (double)hi);
-          }
+          for (int q = 0; q < NQ; ++q)
+            *reinterpret_cast<u32x4 *>(reinterpret_cast<char *>(pb + q * plane + (int64_t)p0 * np + r4 * 16) + vo) =
+                *reinterpret_cast<const stage_u32x4 *>(st + (4 * q + row) * PR8 + (8 * h + qd) * 32 + 16 * (lane & 1));
         }
       }
+    }
+    if (N4 > 0 && (r4 & 1)) {
+      // FP32 planes: 8 quads of eight rows per store
+      const int row = lane & 7, qd = lane >> 3;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t vo = ((uint32_t)(8 * h + qd) * np + row) * 16u;
+        if (p0 + 32 * h + 4 * qd < Pp) {
+#pragma unroll
+          for (int q = 0; q < N4; ++q)
+            *reinterpret_cast<u32x4 *>(reinterpret_cast<char *>(reinterpret_cast<float *>(pb + plane) + q * plane +
+                                                                (int64_t)p0 * np + (r4 >> 1) * 32) + vo) =
+                *reinterpret_cast<const stage_u32x4 *>(st + S4 + (8 * q + row) * PR4 + (8 * h + qd) * 16);
+        }
+      }
+    }
+    if (N2 > 0 && (r4 & 1)) {
+      // BF16 planes: 8 octets of eight rows per store
+      const int row = lane & 7, oc = lane >> 3;
+      const uint32_t vo = ((uint32_t)oc * np + row) * 16u;
+      if (p0 + 8 * oc < Pp) {
+#pragma unroll
+        for (int q = 0; q < N2; ++q)
+          *reinterpret_cast<u32x4 *>(reinterpret_cast<char *>(reinterpret_cast<uint16_t *>(pb + plane) + q * plane +
+                                                              (int64_t)p0 * np + (r4 >> 1) * 64) + vo) =
+              *reinterpret_cast<const stage_u32x4 *>(st + S2 + (8 * q + row) * PR2 + oc * 16);
+      }
+    }
+    __builtin_amdgcn_wave_barrier();  // the rows are read
+  };
+  // stages the values of panel row i: phi, then psi (H/S) or the gradient
+  auto put = [&](int i, double f, double fx, double fy, double fz) {
+    if (i < r0 || i >= r1) return;  // of a shell that another wave shares
+    const double x[4] = {f, fx, fy, fz};
+    const int row = i & 3, row8 = i & 7;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) *reinterpret_cast<stage_f64 *>(st + (4 * q + row) * PR8 + 8 * lane) = x[q];
+    if (KIND == PK_F32 || KIND == PK_SPLIT) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        const float hi = KIND == PK_F32 ? (float)(sw * x[q + 1]) : (float)x[q + 1];
+        *reinterpret_cast<stage_f32 *>(st + S4 + (8 * q + row8) * PR4 + 4 * lane) = hi;
+        if (KIND == PK_SPLIT)
+          *reinterpret_cast<stage_f32 *>(st + S4 + (8 * (3 + q) + row8) * PR4 + 4 * lane) =
+              (float)(x[q + 1] - (double)hi);
+      }
+    }
     if (KIND == PK_BF16) {
-      // one task per (component, function): the 8 points of this octet,
-      // sqrt|w v| times the gradient split into three BF16 parts, 16 bytes
-      // per part
-      u32x4 *pbf = reinterpret_cast<u32x4 *>(pb + fplane);
-      const int64_t noct = Pp >> 3;
-      for (int t = threadIdx.x; t < 3 * T; t += 256) {
-        const int il = t % T, q = t / T;
-        if (il >= nrow) continue;
-        u32x4 w[3];
+      uint32_t w[2][3];
+      split3_bf16x2(sw * fx, sw * fy, w[0][0], w[0][1], w[0][2]);
+      split3_bf16x2(sw * fz, 0.0, w[1][0], w[1][1], w[1][2]);
 #pragma unroll
-        for (int e = 0; e < CP; e += 2) {
-          const double xa = s_sw[e] * st[((q + 1) * CP + e) * PLD + il];
-          const double xb = s_sw[e + 1] * st[((q + 1) * CP + e + 1) * PLD + il];
-          uint32_t w1, w2, w3;
-          split3_bf16x2(xa, xb, w1, w2, w3);
-          w[0][e >> 1] = w1;
-          w[1][e >> 1] = w2;
-          w[2][e >> 1] = w3;
-        }
-#pragma unroll
-        for (int k = 0; k < 3; ++k) pbf[((int64_t)(3 * q + k) * noct + (g8 >> 3)) * np + r0 + il] = w[k];
+      for (int k = 0; k < 3; ++k) {
+        *reinterpret_cast<stage_u16 *>(st + S2 + (8 * k + row8) * PR2 + 2 * lane) = (uint16_t)w[0][k];
+        *reinterpret_cast<stage_u16 *>(st + S2 + (8 * (3 + k) + row8) * PR2 + 2 * lane) = (uint16_t)(w[0][k] >> 16);
+        *reinterpret_cast<stage_u16 *>(st + S2 + (8 * (6 + k) + row8) * PR2 + 2 * lane) = (uint16_t)w[1][k];
       }
     }
-    __syncthreads();  // st consumed
+    if (row == 3) flush(i >> 2);  // wave-uniform
+  };
+  // the distance to an atom and a shell's table entry, fetched a shell ahead
+  struct { double dx, dy, dz, s2, rinv, s; } geo = {};
+  struct { dbl4 c, e; double dd; } rad;
+  int atom = -1;
+  auto fetch = [&](int k) {
+    const int at = __builtin_amdgcn_readlane(m_atom, k);
+    if (at != atom) {
+      atom = at;
+      geo.dx = px - lane_f64(m_ax, k);
+      geo.dy = py - lane_f64(m_ay, k);
+      geo.dz = pz - lane_f64(m_az, k);
+      const double s2 = geo.s2 = geo.dx * geo.dx + geo.dy * geo.dy + geo.dz * geo.dz;
+      geo.rinv = geo.s = 0.0;
+      if (s2 > 0.0) {
+        geo.rinv = __builtin_amdgcn_rsq(s2);
+        geo.rinv = geo.rinv * (1.5 - 0.5 * s2 * geo.rinv * geo.rinv);
+        geo.s = s2 * geo.rinv;
+      }
+    }
+    const double rc = lane_f64(m_rc, k);
+    rad.c = rad.e = dbl4{0.0, 0.0, 0.0, 0.0};
+    rad.dd = 0.0;
+    if (live && geo.s2 < rc * rc) {
+      const int j = radial_interval(geo.s, __builtin_amdgcn_readlane(m_nint, k), lane_f64(m_k1, k), lane_f64(m_k2, k),
+                                    rad.dd);
+      rad.c = *reinterpret_cast<const dbl4 *>(d.coef + lane_i64(m_coef, k) + 4 * (int64_t)j);
+      if (KIND == PK_HS) rad.e = *reinterpret_cast<const dbl4 *>(d.ucoef + lane_i64(m_u, k) + 4 * (int64_t)j);
+    }
+  };
+  if (rn > r0) fetch(0);
+  for (int i = i_first; i < rn;) {  // the shells (wave-uniform)
+    const int ls = __builtin_amdgcn_readlane(m_l, i > r0 ? i - r0 : 0);
+    const double dx = geo.dx, dy = geo.dy, dz = geo.dz, rinv = geo.rinv, dd = rad.dd;
+    const dbl4 c = rad.c, e = rad.e;
+    if (i + 2 * ls + 1 < rn) fetch(i + 2 * ls + 1 - r0);
+    // Rt and Rt' / s, or (H/S) Rt and u / 2
+    const double R = ((c[3] * dd + c[2]) * dd + c[1]) * dd + c[0];
+    const double q = KIND == PK_HS ? 0.5 * (((e[3] * dd + e[2]) * dd + e[1]) * dd + e[0])
+                                   : ((3.0 * c[3] * dd + 2.0 * c[2]) * dd + c[1]) * rinv;
+    auto shell = [&](auto lc) {
+      constexpr int l = decltype(lc)::value;
+      // an opaque copy: the harmonics of every l would otherwise be hoisted
+      // out of the loop over the shells and held in registers
+      double x = dx, y = dy, z = dz;
+      asm volatile("" : "+v"(x), "+v"(y), "+v"(z));
+      static_for<0, 2 * l + 1>([&](auto mc) {
+        constexpr int m = decltype(mc)::value;
+        double S, gx, gy, gz;
+        solid_harmonic(l * l + m, x, y, z, S, gx, gy, gz);
+        const double f = R * S;
+        if (KIND == PK_HS)
+          put(i + m, f, q * f, 0.0, 0.0);
+        else
+          put(i + m, f, q * x * S + R * gx, q * y * S + R * gy, q * z * S + R * gz);
+      });
+      i += 2 * l + 1;
+    };
+    switch (ls) {
+      case 0: shell(std::integral_constant<int, 0>{}); break;
+      case 1: shell(std::integral_constant<int, 1>{}); break;
+      case 2: shell(std::integral_constant<int, 2>{}); break;
+      case 3: shell(std::integral_constant<int, 3>{}); break;
+      default: shell(std::integral_constant<int, 4>{}); break;
+    }
   }
+  for (int i = rn; i < r1; ++i) put(i, 0.0, 0.0, 0.0, 0.0);
 }
 
 // V alone (the V part of F32 and SPLIT_F32, and V-only calls): one MFMA per
@@ -1383,6 +1476,19 @@ static void launch_work(K kernel_p, K kernel_1, unsigned grid, bool persistent, 
     hipLaunchKernelGGL(kernel_1, dim3(grid), dim3(NT), 0, s, dp, work, order, w0, nw, om, panel, staging, tickets);
 }
 
+// The panels of a pass: one workgroup per slot of its batches.
+template <typename K>
+static void launch_panel(K kernel, const q4c_plan *p, const Pass &ps, double *panel, hipStream_t s) {
+  const int64_t nt = ps.t1 - ps.t0;
+  const int npb = (ps.p_max + 63) / 64;
+  // quarter tiles while whole ones would not even give each of the 1024 SIMDs a
+  // wave: 256 waves (3 atoms) take 22 us whole and 16 us in quarters, 6100 (17
+  // atoms) 100 and 115 us (a shell cut by a tile's edge is looked up twice)
+  const int sub = nt * npb <= 1024 ? 4 : 1;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(nt * sub * npb)), dim3(64), 0, s, p->dp, p->d_ptile, ps.t0, nt, sub, npb,
+                     panel, (const double *)p->d_om);
+}
+
 int launch_integrate(const q4c_plan *p, const double *v, int precision, uint32_t parts, uint32_t flags,
                      double *store, double *spin_w, double *spin_v, hipStream_t s) {
   const int accumulate = (flags & Q4C_ACCUMULATE) ? 1 : 0;
@@ -1424,17 +1530,13 @@ int launch_integrate(const q4c_plan *p, const double *v, int precision, uint32_t
       {
         TimedLaunch tl_(p, Q4C_TIMER_TABULATE, s);
         if (kind == PK_F64)
-          hipLaunchKernelGGL(k_panel<PK_F64>, dim3((unsigned)nt), dim3(256), 0, s, p->dp, p->d_ptile, ps.t0, nt, panel,
-                           (const double *)nullptr);
+          launch_panel(k_panel<PK_F64>, p, ps, panel, s);
         else if (kind == PK_BF16)
-          hipLaunchKernelGGL(k_panel<PK_BF16>, dim3((unsigned)nt), dim3(256), 0, s, p->dp, p->d_ptile, ps.t0, nt,
-                             panel, (const double *)p->d_om);
+          launch_panel(k_panel<PK_BF16>, p, ps, panel, s);
         else if (kind == PK_SPLIT)
-          hipLaunchKernelGGL(k_panel<PK_SPLIT>, dim3((unsigned)nt), dim3(256), 0, s, p->dp, p->d_ptile, ps.t0, nt,
-                             panel, (const double *)nullptr);
+          launch_panel(k_panel<PK_SPLIT>, p, ps, panel, s);
         else
-          hipLaunchKernelGGL(k_panel<PK_F32>, dim3((unsigned)nt), dim3(256), 0, s, p->dp, p->d_ptile, ps.t0, nt, panel,
-                             (const double *)p->d_om);
+          launch_panel(k_panel<PK_F32>, p, ps, panel, s);
       }
       if ((rc = check_launch("k_panel")) != Q4C_OK) return rc;
     }
@@ -1522,8 +1624,7 @@ int launch_integrate_hs(const q4c_plan *p, const double *v, uint32_t flags, doub
     if (nt > 0) {
       {
         TimedLaunch tl_(p, Q4C_TIMER_TABULATE, s);
-        hipLaunchKernelGGL(k_panel<PK_HS>, dim3((unsigned)nt), dim3(256), 0, s, p->dp, p->d_ptile, ps.t0, nt, panel,
-                           (const double *)nullptr);
+        launch_panel(k_panel<PK_HS>, p, ps, panel, s);
       }
       if ((rc = check_launch("k_panel<hs>")) != Q4C_OK) return rc;
     }
@@ -1586,8 +1687,7 @@ int launch_density(const q4c_plan *p, const double *coef, uint32_t terms, int pr
     if (nt > 0) {
       {
         TimedLaunch tl_(p, Q4C_TIMER_TABULATE, s);
-        hipLaunchKernelGGL(k_panel<PK_F64>, dim3((unsigned)nt), dim3(256), 0, s, p->dp, p->d_ptile, ps.t0, nt, panel,
-                           (const double *)nullptr);
+        launch_panel(k_panel<PK_F64>, p, ps, panel, s);
       }
       if ((rc = check_launch("k_panel")) != Q4C_OK) return rc;
     }
@@ -1613,8 +1713,7 @@ int launch_density_grad(const q4c_plan *p, const double *coef, double *out, hipS
     if (nt > 0) {
       {
         TimedLaunch tl_(p, Q4C_TIMER_TABULATE, s);
-        hipLaunchKernelGGL(k_panel<PK_F64>, dim3((unsigned)nt), dim3(256), 0, s, p->dp, p->d_ptile, ps.t0, nt, panel,
-                           (const double *)nullptr);
+        launch_panel(k_panel<PK_F64>, p, ps, panel, s);
       }
       if ((rc = check_launch("k_panel")) != Q4C_OK) return rc;
     }

@@ -701,6 +701,9 @@ int build_device(q4c_plan *p) {
       for (size_t i = i0; i < v.size(); ++i) out[i0 + at[top - cost(v[i])]++] = v[i];
     };
     for (q4c::Pass &ps : p->passes) {
+      ps.p_max = 0;
+      for (int64_t b = ps.b0; b < ps.b1; ++b)
+        ps.p_max = std::max(ps.p_max, (int32_t)(p->batch_pt_off[b + 1] - p->batch_pt_off[b]));
       ps.bi0 = (int64_t)fwd.size();
       ps.di0 = (int64_t)den.size();
       for (int64_t b = ps.b0; b < ps.b1; ++b) {
