@@ -223,6 +223,81 @@ __device__ __forceinline__ void stage_store(double *staging, const SlotInfo &si,
   }
 }
 
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+
+// MFMA 16x16x4 lane layouts (lane l, l16 = l % 16, lk = l / 16):
+//   A[i][k]: lane i + 16 k;  B[k][j]: lane j + 16 k;
+//   D (f64_16x16x4): register r of lane l holds D[lk + 4 r][l16];
+//   D (f32_16x16x4): register r of lane l holds D[4 lk + r][l16].
+__device__ __forceinline__ int d_row_f64(int lk, int r) { return lk + 4 * r; }
+__device__ __forceinline__ int d_row_f32(int lk, int r) { return 4 * lk + r; }
+
+// stage_store for the FP64 16 x 16 blocks of one block row rb of a batch (the
+// MFMA's D layout), with 32-bit offsets from the staging of the row's first
+// function and no branches: elements that are not stored get an offset past
+// the buffer's end, which drops the store.  Vector instructions take time from
+// the matrix pipe, and the 64-bit addresses of stage_store cost more of them
+// than the rest of an item outside its MFMAs: the dense slab's forward took
+// 29.5 ms with it and 28.9 so, the 120-atom cluster's 9.67 and 9.52 ms.
+struct StageRows {
+  __amdgpu_buffer_rsrc_t rs;
+  uint32_t a[4], b[4];     // bytes: row_off - 5 nfn fnoff (relative), 5 nfn
+  int row[4], fo[4], nf[4], slot[4];  // row within its atom, the atom's first function, functions, slot
+};
+__device__ __forceinline__ StageRows stage_rows(const DevPlan &d, int f0, int n, int rb, int lk, double *staging) {
+  StageRows s;
+  const int64_t base = uniform_i64(d.loc_rowoff[f0 + 16 * rb]);  // the rows' atoms are stored from here on in slot order
+  s.rs = __builtin_amdgcn_make_buffer_rsrc((void *)(staging + base), (short)0, (int)0x7ffffff8, 0x00020000);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int li = 16 * rb + d_row_f64(lk, r), lc = li < n ? li : n - 1;
+    const int64_t v = d.loc_info[f0 + lc];
+    const int fo = (int)((v >> 20) & 0xFFFFF), nf = (int)(v >> 40);
+    s.slot[r] = li < n ? (int)(v & 0xFFFFF) : 0x7fffffff;
+    s.fo[r] = fo;
+    s.nf[r] = nf;
+    s.row[r] = li - fo;
+    s.b[r] = 40u * nf;
+    s.a[r] = 8u * (uint32_t)(d.loc_rowoff[f0 + lc] - base) - s.b[r] * (uint32_t)fo;
+  }
+  return s;
+}
+// parts 0 .. NQ - 1 of the block's rows r: val(r, q)
+template <int NQ, typename F>
+__device__ __forceinline__ void stage_block(const StageRows &s, const DevPlan &d, int f0, int n, int rb, int cb, int l16,
+                                            F val) {
+  constexpr uint32_t kDrop = 0xfffffff0u;
+  const int lj = 16 * cb + l16;
+  const int64_t v = d.loc_info[f0 + (lj < n ? lj : n - 1)];
+  const int slot = lj < n ? (int)(v & 0xFFFFF) : -1, fo = (int)((v >> 20) & 0xFFFFF), nf = (int)(v >> 40);
+  bool same = false;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const bool drop = s.slot[r] > slot;  // lower atom-block triangle, or padding
+    const uint32_t pq = drop ? 0u : 8u * (uint32_t)(s.nf[r] * nf);
+    const uint32_t e = drop ? kDrop : s.a[r] + s.b[r] * (uint32_t)fo + 8u * (uint32_t)(s.row[r] * nf + (lj - fo));
+    same |= s.slot[r] == slot;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, val(r, q)), s.rs,
+                                            e + q * pq, 0, 0);
+  }
+  // the mirrored elements of atom blocks within one atom lie in a block that
+  // is never computed
+  if (rb < cb && __any(same)) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const bool drop = s.slot[r] != slot;
+      const uint32_t pq = drop ? 0u : 8u * (uint32_t)(s.nf[r] * nf);
+      const uint32_t e = drop ? kDrop : s.a[r] + s.b[r] * (uint32_t)fo + 8u * (uint32_t)((lj - fo) * nf + s.row[r]);
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, mirror_sign(q) * val(r, q)), s.rs,
+                                              e + q * pq, 0, 0);
+    }
+  }
+}
+
 // As stage_store, adding to the staged element (and its mirror) instead.
 template <int Q0, int Q1>
 __device__ __forceinline__ void stage_add(double *staging, const SlotInfo &si, const SlotInfo &sj, int li, int lj,
@@ -239,14 +314,6 @@ __device__ __forceinline__ void stage_add(double *staging, const SlotInfo &si, c
     for (int q = Q0; q < Q1; ++q) staging[blk + q * pq + em] += mirror_sign(q) * v[q - Q0];
   }
 }
-
-// MFMA 16x16x4 lane layouts (lane l, l16 = l % 16, lk = l / 16):
-//   A[i][k]: lane i + 16 k;  B[k][j]: lane j + 16 k;
-//   D (f64_16x16x4): register r of lane l holds D[lk + 4 r][l16];
-//   D (f32_16x16x4): register r of lane l holds D[4 lk + r][l16].
-__device__ __forceinline__ int d_row_f64(int lk, int r) { return lk + 4 * r; }
-__device__ __forceinline__ int d_row_f32(int lk, int r) { return 4 * lk + r; }
-
 
 // LDS image of one 16-point chunk of a 64-function tile, in the panel's own
 // order: row (q, u) holds component q at points 2u and 2u+1 of the chunk,

@@ -40,8 +40,8 @@ struct Operand {
 // never wait for each other.
 //
 // Bound: FP64 matrix pipe.  120-atom cluster (1.9M points, 171 functions per
-// batch on average) 14.5 -> 10.0 ms, dense 300-atom slab (319 per batch) 43.3
-// -> 29.5 ms against ten products from 64 x 64 tiles in LDS with a barrier
+// batch on average) 14.5 -> 9.5 ms, dense 300-atom slab (319 per batch) 43.3
+// -> 28.9 ms against ten products from 64 x 64 tiles in LDS with a barrier
 // every 8 points; the seven MFMAs alone take 6.7 and 21.3 ms at their peak
 // rate (76% of the active cycles on the slab, the FP64 vector instructions 5%
 // more).
@@ -57,6 +57,8 @@ __device__ __forceinline__ void forward_item(const DevPlan &d, int f0, int n, in
   off[0] = ((uint32_t)(lk >> 1) * np + 16 * rb + l16) * 32u + 16u * (lk & 1);
 #pragma unroll
   for (int c = 0; c < NB; ++c) off[1 + c] = ((uint32_t)(lk >> 1) * np + 16 * (cb + c) + l16) * 32u + 16u * (lk & 1);
+  // w v of the batch's points; reads past them give 0
+  const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc((void *)(om + g0), (short)0, P * 8, 0x00020000);
   auto load = [&](int k, Operand (&o)[1 + NB], dbl2 &w) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -68,11 +70,9 @@ __device__ __forceinline__ void forward_item(const DevPlan &d, int f0, int n, in
       for (int x = 0; x < 1 + NB; ++x)
         o[x].v[q] = __builtin_bit_cast(dbl2, __builtin_amdgcn_raw_buffer_load_b128(rs, off[x], 0, 0));
     }
-    // w v at the lane's two points, zero past the batch (the entries there
-    // belong to the next batch, or are the zeros past the array's end)
-    const int pt = k + 2 * lk;
-    const double w0 = om[g0 + pt], w1 = om[g0 + pt + 1];
-    w = dbl2{pt < P ? w0 : 0.0, pt + 1 < P ? w1 : 0.0};
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      w[h] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(ro, 16 * lk + 8 * h, 8 * k, 0));
   };
   dbl4 acc[NB][7];
 #pragma unroll
@@ -114,29 +114,17 @@ __device__ __forceinline__ void forward_item(const DevPlan &d, int f0, int n, in
   }
   // write the blocks to the staged atom-pair blocks
   const double cp = d.cprime;
-  SlotInfo si[4];
+  const StageRows sr = stage_rows(d, f0, n, rb, lk, staging);
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int li = 16 * rb + d_row_f64(lk, r);
-    const int64_t v = li < n ? d.loc_info[f0 + li] : 0;
-    si[r] = SlotInfo{(int)(v & 0xFFFFF), (int)((v >> 20) & 0xFFFFF), (int)(v >> 40), li < n ? d.loc_rowoff[f0 + li] : 0};
-  }
-#pragma unroll
-  for (int c = 0; c < NB; ++c) {
-    const int lj = 16 * (cb + c) + l16;
-    if (lj >= n) continue;
-    const int64_t v = d.loc_info[f0 + lj];
-    const SlotInfo sj{(int)(v & 0xFFFFF), (int)((v >> 20) & 0xFFFFF), (int)(v >> 40), 0};
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int li = 16 * rb + d_row_f64(lk, r);
-      if (li >= n) continue;
+  for (int c = 0; c < NB; ++c)
+    stage_block<5>(sr, d, f0, n, rb, cb + c, l16, [&](int r, int q) {
       const double dx = acc[c][1][r], dy = acc[c][2][r], dz = acc[c][3][r];
-      const double vals[5] = {acc[c][0][r], cp * ((dx + dy) + dz), cp * (acc[c][4][r] - (dy - dz)),
-                              cp * (acc[c][5][r] - (dz - dx)), cp * (acc[c][6][r] - (dx - dy))};
-      stage_store<0, 5>(staging, si[r], sj, li, lj, rb < cb + c, vals);
-    }
-  }
+      return q == 0   ? acc[c][0][r]
+             : q == 1 ? cp * ((dx + dy) + dz)
+             : q == 2 ? cp * (acc[c][4][r] - (dy - dz))
+             : q == 3 ? cp * (acc[c][5][r] - (dz - dx))
+                      : cp * (acc[c][6][r] - (dx - dy));
+    });
 }
 
 // A workgroup is four independent waves with one item each (item 4 x + wave

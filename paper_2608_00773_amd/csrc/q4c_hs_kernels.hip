@@ -3,6 +3,7 @@
 // tabulation, batch sums and launches around it are in q4c_kernels.hip.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "q4c_internal.h"
@@ -11,155 +12,139 @@
 namespace q4c {
 namespace {
 
+// phi and psi of one 16-function block at one K pair (8 points): points 2 lk
+// and 2 lk + 1 of the 8, function l16 of the block.
+struct OperandHS {
+  dbl2 v[2];
+};
+
 // H and S of one component (the Q4C integrand of Eq. 19 in the scalar form
 // of Eq. 29, symmetrised), from panels of phi and psi = u phi / 2:
 //   H = Phi^T diag(w) (v Phi + Psi) + Psi^T diag(w) Phi,   S = Phi^T diag(w) Phi
 // i.e. per 16 x 16 block and K step of 4 points three FP64 MFMAs: the row
-// operands phi_i, psi_i against the column operands w v phi_j + w psi_j and
-// w phi_j (shared by the psi_i phi_j part of H and by S).  Same tiles, wave
-// slots and staging as the forward contraction; chunks of 16 points in two
-// LDS buffers (two components), the next chunk's DMA and weights in flight
-// while this one is multiplied.
-template <bool PERSIST>
-__global__ __launch_bounds__(NT, 2) void k_contract_hs(DevPlan d, const WorkItem *work, const int32_t *order,
-                                                       int64_t w0, int64_t nw, const double *om,
-                                                       const double *panel, double *staging, unsigned *tickets) {
-  constexpr int CH = 16, RPQ = CH / 2, NQ = 2;
-  constexpr int BUFD = NQ * RPQ * DROW;  // doubles per chunk image
-  __shared__ double sa[2 * BUFD], sb[2 * BUFD];
-  __shared__ int64_t s_pos;
-  // slot data of the tile's 64 rows and 64 columns for the epilogue, loaded
-  // when the work item starts (slot -1: beyond n)
-  __shared__ int s_fslot[2 * T], s_ffn[2 * T], s_fnf[2 * T];
-  __shared__ int64_t s_frow[2 * T];
-  int64_t pos = PERSIST ? next_item(tickets, nw, order != nullptr, &s_pos)
-                        : (order ? (int64_t)blockIdx.x : xcd_map(blockIdx.x, nw));
-  while (!PERSIST || pos < nw) {
-  const int64_t wi = w0 + (order ? order[w0 + pos] : pos);
-  const WorkItem it = work[wi];
-  const int b = it.batch;
-  const int g0 = d.batch_pt_off[b], P = d.batch_pt_off[b + 1] - g0;
-  const int f0 = d.batch_fn_off[b], n = d.batch_fn_off[b + 1] - f0;
-  const int r0 = it.ti * T, c0 = it.tj * T;
+// operands w phi_i and w v phi_i + w psi_i, formed once for the item's
+// columns, against phi_j and psi_j.  The wave's item, loads and epilogue are
+// those of the FP64 forward contraction: blocks (rb, cb .. cb + NB - 1), no
+// LDS, no barriers, operands read from the panel a K pair ahead.
+//
+// Bound: FP64 matrix pipe.  60 atoms, both components (163 and 353 functions
+// per batch on average) 8.6 -> 7.1 ms against 64 x 64 tiles in LDS with a
+// barrier every 16 points; the MFMAs alone take 4.7 ms at their peak rate, 5.3
+// at the clock of this kernel (75% of the active cycles; the other vector
+// instructions, 1.4 per MFMA, 8% more).
+template <int NB>
+__device__ __forceinline__ void hs_item(const DevPlan &d, int f0, int n, int g0, int P, const double *pb, int rb, int cb,
+                                        const double *om, double *staging) {
+  const int lane = threadIdx.x & 63, l16 = lane & 15, lk = lane >> 4;
   const int Pp = (int)pad16(P), np = (int)pad16(n);
-  const double *pb = panel + d.panel_off[b];
   const int64_t plane = (int64_t)Pp * np;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int li16 = lane & 15, lk = lane >> 4;
-  int brow[4], bcol[4];
-  bool act[4];
-  wave_blocks(r0, c0, n, wave, brow, bcol, act);
-  dbl4 acc[4][3];  // H (v phi + psi part), S, H (psi phi part)
+  uint32_t off[1 + NB];
+  off[0] = ((uint32_t)(lk >> 1) * np + 16 * rb + l16) * 32u + 16u * (lk & 1);
 #pragma unroll
-  for (int sl = 0; sl < 4; ++sl)
+  for (int c = 0; c < NB; ++c) off[1 + c] = ((uint32_t)(lk >> 1) * np + 16 * (cb + c) + l16) * 32u + 16u * (lk & 1);
+  // w v and w of the batch's points; reads past them give 0
+  const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc((void *)(om + g0), (short)0, P * 8, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void *)(d.pw + g0), (short)0, P * 8, 0x00020000);
+  auto load = [&](int k, OperandHS (&o)[1 + NB], dbl2 &wv, dbl2 &w) {
 #pragma unroll
-    for (int q = 0; q < 3; ++q) acc[sl][q] = dbl4{0.0, 0.0, 0.0, 0.0};
-  // K steps in pairs over 8 points (K index lk: point 2 lk of the 8, then
-  // 2 lk + 1), one 16-byte LDS read per operand for both; weights at the
-  // points this lane's K index visits in the next chunk: w v and w
-  double omn[CH / 4], wn[CH / 4];
-  auto load_w = [&](int k) {
+    for (int q = 0; q < 2; ++q) {
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+          (void *)(pb + (int64_t)q * plane + (int64_t)(k >> 2) * np * 4), (short)0, np * 64, 0x00020000);
 #pragma unroll
-    for (int ks = 0; ks < CH / 4; ++ks) {
-      const int pt = k + 8 * (ks >> 1) + 2 * lk + (ks & 1);
-      omn[ks] = pt < P ? om[g0 + pt] : 0.0;
-      wn[ks] = pt < P ? d.pw[g0 + pt] : 0.0;
+      for (int x = 0; x < 1 + NB; ++x)
+        o[x].v[q] = __builtin_bit_cast(dbl2, __builtin_amdgcn_raw_buffer_load_b128(rs, off[x], 0, 0));
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      wv[h] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(ro, 16 * lk + 8 * h, 8 * k, 0));
+      w[h] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rw, 16 * lk + 8 * h, 8 * k, 0));
     }
   };
-  load_w(0);
-  dma_chunk<NT, CH, T, DROW, NQ>(pb, plane, np, r0, 0, sa);
-  dma_chunk<NT, CH, T, DROW, NQ>(pb, plane, np, c0, 0, sb);
-  if (tid < 2 * T) {  // visible from the first chunk's barrier on
-    const int lf = tid < T ? r0 + tid : c0 + tid - T;
-    int64_t v = 0, ro = 0;
-    if (lf < n) {
-      v = d.loc_info[f0 + lf];
-      ro = d.loc_rowoff[f0 + lf];
-    }
-    s_fslot[tid] = lf < n ? (int)(v & 0xFFFFF) : -1;
-    s_ffn[tid] = (int)((v >> 20) & 0xFFFFF);
-    s_fnf[tid] = (int)(v >> 40);
-    s_frow[tid] = ro;
-  }
-  for (int k0 = 0; k0 < Pp; k0 += CH) {
-    const int bo = ((k0 / CH) & 1) * BUFD;
-    double omv[CH / 4], wv[CH / 4];
-    __builtin_amdgcn_s_waitcnt(0);  // this thread's loads of this chunk have landed
-    __syncthreads();                // ... everyone's; the previous chunk is consumed
+  dbl4 acc[NB][3];  // H (w v phi + w psi, phi), S, H (w phi, psi)
 #pragma unroll
-    for (int ks = 0; ks < CH / 4; ++ks) {
-      omv[ks] = omn[ks];
-      wv[ks] = wn[ks];
-    }
-    if (k0 + CH < Pp) {
-      const int nbo = BUFD - bo;
-      load_w(k0 + CH);
-      dma_chunk<NT, CH, T, DROW, NQ>(pb, plane, np, r0, (k0 + CH) >> 2, sa + nbo);
-      dma_chunk<NT, CH, T, DROW, NQ>(pb, plane, np, c0, (k0 + CH) >> 2, sb + nbo);
-    }
-    const double *ca = sa + bo, *cb = sb + bo;
+  for (int c = 0; c < NB; ++c)
 #pragma unroll
-    for (int kp = 0; kp < CH / 8; ++kp) {
-      const int row = 4 * kp + lk;  // image row: points 8 kp + 2 lk, + 1
+    for (int q = 0; q < 3; ++q) acc[c][q] = dbl4{0.0, 0.0, 0.0, 0.0};
+  auto multiply = [&](const OperandHS (&o)[1 + NB], const dbl2 &wv, const dbl2 &w) {
 #pragma unroll
-      for (int sl = 0; sl < 4; ++sl) {
-        if (!act[sl]) continue;  // wave-uniform
-        const dbl2 fi2 = *reinterpret_cast<const dbl2 *>(&ca[row * DROW + 2 * (brow[sl] + li16)]);
-        const dbl2 pi2 = *reinterpret_cast<const dbl2 *>(&ca[(RPQ + row) * DROW + 2 * (brow[sl] + li16)]);
-        const dbl2 fj2 = *reinterpret_cast<const dbl2 *>(&cb[row * DROW + 2 * (bcol[sl] + li16)]);
-        const dbl2 pj2 = *reinterpret_cast<const dbl2 *>(&cb[(RPQ + row) * DROW + 2 * (bcol[sl] + li16)]);
+    for (int h = 0; h < 2; ++h) {
+      const double as = w[h] * o[0].v[0][h];                               // w phi_i
+      const double ah = fma(wv[h], o[0].v[0][h], w[h] * o[0].v[1][h]);     // w v phi_i + w psi_i
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int ks = 2 * kp + h;
-          const double bw = wv[ks] * fj2[h];                    // w phi_j
-          const double bh = omv[ks] * fj2[h] + wv[ks] * pj2[h];  // w v phi_j + w psi_j
-          acc[sl][0] = mfma64(fi2[h], bh, acc[sl][0]);
-          acc[sl][1] = mfma64(fi2[h], bw, acc[sl][1]);
-          acc[sl][2] = mfma64(pi2[h], bw, acc[sl][2]);
-        }
+      for (int c = 0; c < NB; ++c) {
+        acc[c][0] = mfma64(ah, o[1 + c].v[0][h], acc[c][0]);
+        acc[c][1] = mfma64(as, o[1 + c].v[0][h], acc[c][1]);
+        acc[c][2] = mfma64(as, o[1 + c].v[1][h], acc[c][2]);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
+  };
+  OperandHS oa[1 + NB], ob[1 + NB];
+  dbl2 va, vb, wa, wb;
+  load(0, oa, va, wa);
+  for (int k = 0; k < Pp; k += 16) {  // Pp is a multiple of 16: two K pairs per turn
+    load(k + 8, ob, vb, wb);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(oa, va, wa);
+    __builtin_amdgcn_sched_barrier(0);
+    if (k + 16 < Pp) load(k + 16, oa, va, wa);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(ob, vb, wb);
+    __builtin_amdgcn_sched_barrier(0);
   }
-  // write the computed blocks (H, S) to the staged atom-pair blocks
+  // write the blocks (H, S) to the staged atom-pair blocks
+  const StageRows sr = stage_rows(d, f0, n, rb, lk, staging);
 #pragma unroll
-  for (int sl = 0; sl < 4; ++sl) {
-    if (!act[sl]) continue;
-    const int cb = c0 + bcol[sl];
-    const int lj = cb + li16;
-    if (lj >= n) continue;
-    const int cj = T + bcol[sl] + li16;
-    const SlotInfo sj{s_fslot[cj], s_ffn[cj], s_fnf[cj], s_frow[cj]};
-    const int rb = r0 + brow[sl];
-    const bool upper = rb < cb;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int li = rb + d_row_f64(lk, r);
-      if (li < n) {
-        const int ri = li - r0;
-        const SlotInfo si{s_fslot[ri], s_ffn[ri], s_fnf[ri], s_frow[ri]};
-        double vals[2];
-        vals[0] = acc[sl][0][r] + acc[sl][2][r];
-        vals[1] = acc[sl][1][r];
-        stage_store<0, 2>(staging, si, sj, li, lj, upper, vals);
-      }
-    }
-  }
-  if (!PERSIST) break;
-  pos = next_item(tickets, nw, order != nullptr, &s_pos);
+  for (int c = 0; c < NB; ++c)
+    stage_block<2>(sr, d, f0, n, rb, cb + c, l16,
+                   [&](int r, int q) { return q ? acc[c][1][r] : acc[c][0][r] + acc[c][2][r]; });
+}
+
+// Four independent waves per workgroup, one item each (as k_forward).
+// tickets != NULL: a persistent launch, every wave draws items until none is
+// left.
+template <bool PERSIST>
+__global__ __launch_bounds__(256, 3) void k_contract_hs(DevPlan d, const BlockItem *items, int64_t ni, int global_queue,
+                                                        const double *om, const double *panel, double *staging,
+                                                        unsigned *tickets) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool gq = global_queue != 0;
+  auto draw = [&]() -> int64_t {
+    int64_t p = 0;
+    if ((threadIdx.x & 63) == 0) p = ticket_pos(tickets, ni, gq, draw_ticket(tickets, gq));
+    return uniform_i64(p);
+  };
+  int64_t pos = PERSIST ? draw()
+                        : 4 * (gq ? (int64_t)blockIdx.x : xcd_map(blockIdx.x, (ni + 3) / 4)) + wave;
+  while (pos < ni) {
+    const BlockItem it = items[pos];
+    const int b = it.batch;
+    const int g0 = d.batch_pt_off[b], P = d.batch_pt_off[b + 1] - g0;
+    const int f0 = d.batch_fn_off[b], n = d.batch_fn_off[b + 1] - f0;
+    const double *pb = panel + d.panel_off[b];
+    if (it.wide)
+      hs_item<2>(d, f0, n, g0, P, pb, it.rb, it.cb, om, staging);
+    else
+      hs_item<1>(d, f0, n, g0, P, pb, it.rb, it.cb, om, staging);
+    if (!PERSIST) return;
+    pos = draw();
   }
 }
 
 }  // namespace
 
-int launch_contract_hs(const q4c_plan *p, int64_t w0, int64_t nw, const int32_t *order, const double *panel,
-                       unsigned *tickets, unsigned grid, hipStream_t s) {
+int launch_contract_hs(const q4c_plan *p, const Pass &ps, const double *panel, unsigned *tickets, hipStream_t s) {
+  const LaunchCfg cfg = p->cfg_hs;
+  const BlockItem *items = (cfg.order ? p->d_blocks_cost : p->d_blocks) + ps.bi0;
+  const int64_t ni = ps.bi1 - ps.bi0;
+  if (ni <= 0) return Q4C_OK;
+  const int64_t groups = (ni + 3) / 4;
   if (tickets)
-    hipLaunchKernelGGL(k_contract_hs<true>, dim3(grid), dim3(NT), 0, s, p->dp, p->d_work, order, w0, nw, p->d_om,
-                       panel, p->d_staging, tickets);
+    hipLaunchKernelGGL(k_contract_hs<true>, dim3((unsigned)std::min<int64_t>(cfg.persistent, groups)), dim3(256), 0, s,
+                       p->dp, items, ni, (int)cfg.order, (const double *)p->d_om, panel, p->d_staging, tickets);
   else
-    hipLaunchKernelGGL(k_contract_hs<false>, dim3(grid), dim3(NT), 0, s, p->dp, p->d_work, order, w0, nw, p->d_om,
-                       panel, p->d_staging, tickets);
+    hipLaunchKernelGGL(k_contract_hs<false>, dim3((unsigned)groups), dim3(256), 0, s, p->dp, items, ni, (int)cfg.order,
+                       (const double *)p->d_om, panel, p->d_staging, tickets);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "k_contract_hs");
   return Q4C_OK;

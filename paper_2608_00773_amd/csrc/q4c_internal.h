@@ -340,9 +340,8 @@ int launch_spinor_to_scalar(const q4c_plan *pl, const double *d_spin, double *c_
 // scalar -> spinor transformation of two H/S stores (q4c_spinor_kernels.hip)
 int launch_spinor_transform(const q4c_plan *pl, const double *hs_large, const double *hs_small, double *h_out,
                             double *s_out, hipStream_t s);
-// k_contract_hs over work items [w0, w0 + nw) of a pass (q4c_hs_kernels.hip)
-int launch_contract_hs(const q4c_plan *p, int64_t w0, int64_t nw, const int32_t *order, const double *panel,
-                       unsigned *tickets, unsigned grid, hipStream_t s);
+// H and S over the block items of a pass (q4c_hs_kernels.hip)
+int launch_contract_hs(const q4c_plan *p, const Pass &ps, const double *panel, unsigned *tickets, hipStream_t s);
 // FP64 contraction of all five parts over the block items of a pass (q4c_forward_kernels.hip)
 int launch_forward(const q4c_plan *p, const Pass &ps, const double *panel, unsigned *tickets, hipStream_t s);
 // the adjoint's folded coefficients of a call, and one pass of its items and

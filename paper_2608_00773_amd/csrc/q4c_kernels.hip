@@ -1609,7 +1609,6 @@ int launch_integrate_hs(const q4c_plan *p, const double *v, uint32_t flags, doub
   }
   if ((rc = check_launch("k_om")) != Q4C_OK) return rc;
   const LaunchCfg cfg = p->cfg_hs;
-  const int32_t *order = cfg.order ? p->d_order : nullptr;
   if (cfg.persistent > 0) {
     hipLaunchKernelGGL(k_zero_u32, dim3(8), dim3(256), 0, s, p->d_tickets,
                        (int64_t)p->passes.size() * kTicketsPerLaunch);
@@ -1619,7 +1618,6 @@ int launch_integrate_hs(const q4c_plan *p, const double *v, uint32_t flags, doub
     const Pass &ps = p->passes[ip];
     const int64_t nw = ps.w1 - ps.w0, nt = ps.t1 - ps.t0, nr = ps.r1 - ps.r0;
     unsigned *tickets = cfg.persistent > 0 ? p->d_tickets + ip * kTicketsPerLaunch : nullptr;
-    const unsigned grid = (unsigned)(cfg.persistent > 0 ? std::min<int64_t>(cfg.persistent, nw) : nw);
     double *panel = p->d_staging + ps.staging_len + ps.partial_len;
     if (nt > 0) {
       {
@@ -1631,7 +1629,7 @@ int launch_integrate_hs(const q4c_plan *p, const double *v, uint32_t flags, doub
     if (nw > 0) {
       {
         TimedLaunch tl_(p, Q4C_TIMER_CONTRACT, s);
-        rc = launch_contract_hs(p, ps.w0, nw, order, panel, tickets, grid, s);
+        rc = launch_contract_hs(p, ps, panel, tickets, s);
       }
       if (rc != Q4C_OK) return rc;
     }
