@@ -260,7 +260,7 @@ __global__ __launch_bounds__(NTD, 3) void k_density_items(DevPlan d, const Block
   __shared__ DenShared<F32W> sh;
   __shared__ int64_t s_pos;
   const bool gq = global_queue != 0;
-  int64_t pos = PERSIST ? next_item(tickets, ni, gq, &s_pos) : (gq ? (int64_t)blockIdx.x : xcd_map(blockIdx.x, ni));
+  int64_t pos = PERSIST ? next_item(tickets, ni, gq, &s_pos) : (gq ? (int64_t)blockIdx.x : xcd_map_runs(blockIdx.x, ni, 128));
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   while (pos < ni) {  // workgroup-uniform
     const BlockItem it = items[pos];

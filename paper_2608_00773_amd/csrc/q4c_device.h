@@ -30,6 +30,16 @@ __device__ __forceinline__ int64_t xcd_map(int64_t bid, int64_t n) {
   return x * q + (x < r ? x : r) + k;
 }
 
+// The same in rounds: every XCD takes runs of `run` items in turn, so that work
+// whose cost varies slowly along the items is spread evenly (8 molecules of
+// different density: the adjoint 2.82 -> 2.57 ms).
+__device__ __forceinline__ int64_t xcd_map_runs(int64_t bid, int64_t n, int64_t run) {
+  const int64_t whole = n / (8 * run) * (8 * run);
+  if (bid >= whole) return whole + xcd_map(bid - whole, n - whole);
+  const int64_t x = bid % 8, k = bid / 8;
+  return (k / run * 8 + x) * run + k % run;
+}
+
 // Persistent launches: workgroups loop over work items drawn from ticket
 // counters (zeroed before the launch).  Without an order map the items are
 // split into 8 contiguous ranges, one queue per XCD (workgroup x runs on XCD

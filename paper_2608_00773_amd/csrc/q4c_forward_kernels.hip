@@ -40,8 +40,8 @@ struct Operand {
 // never wait for each other.
 //
 // Bound: FP64 matrix pipe.  120-atom cluster (1.9M points, 171 functions per
-// batch on average) 14.5 -> 9.5 ms, dense 300-atom slab (319 per batch) 43.3
-// -> 28.9 ms against ten products from 64 x 64 tiles in LDS with a barrier
+// batch on average) 14.5 -> 9.15 ms, dense 300-atom slab (319 per batch) 43.3
+// -> 27.9 ms against ten products from 64 x 64 tiles in LDS with a barrier
 // every 8 points; the seven MFMAs alone take 6.7 and 21.3 ms at their peak
 // rate (76% of the active cycles on the slab, the FP64 vector instructions 5%
 // more).
@@ -59,13 +59,17 @@ __device__ __forceinline__ void forward_item(const DevPlan &d, int f0, int n, in
   for (int c = 0; c < NB; ++c) off[1 + c] = ((uint32_t)(lk >> 1) * np + 16 * (cb + c) + l16) * 32u + 16u * (lk & 1);
   // w v of the batch's points; reads past them give 0
   const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc((void *)(om + g0), (short)0, P * 8, 0x00020000);
+  // past the last point an empty buffer: nothing is read, and no branch makes
+  // the waits of the next K pairs count for both of its sides (with one, every
+  // other K pair waited for loads just issued: 9.52 instead of 9.15 ms)
   auto load = [&](int k, Operand (&o)[1 + NB], dbl2 &w) {
+    const int nr = k < Pp ? np * 64 : 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       // the K pair's two point quads of component q: a wave-uniform base, so
       // that no vector instruction computes an address
       const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-          (void *)(pb + (int64_t)q * plane + (int64_t)(k >> 2) * np * 4), (short)0, np * 64, 0x00020000);
+          (void *)(pb + (int64_t)q * plane + (int64_t)(k >> 2) * np * 4), (short)0, nr, 0x00020000);
 #pragma unroll
       for (int x = 0; x < 1 + NB; ++x)
         o[x].v[q] = __builtin_bit_cast(dbl2, __builtin_amdgcn_raw_buffer_load_b128(rs, off[x], 0, 0));
@@ -107,7 +111,7 @@ __device__ __forceinline__ void forward_item(const DevPlan &d, int f0, int n, in
     __builtin_amdgcn_sched_barrier(0);
     multiply(oa, wa);
     __builtin_amdgcn_sched_barrier(0);
-    if (k + 16 < Pp) load(k + 16, oa, wa);
+    load(k + 16, oa, wa);
     __builtin_amdgcn_sched_barrier(0);
     multiply(ob, wb);
     __builtin_amdgcn_sched_barrier(0);
@@ -142,7 +146,7 @@ __global__ __launch_bounds__(256, 2) void k_forward(DevPlan d, const BlockItem *
     return uniform_i64(p);
   };
   int64_t pos = PERSIST ? draw()
-                        : 4 * (gq ? (int64_t)blockIdx.x : xcd_map(blockIdx.x, (ni + 3) / 4)) + wave;
+                        : 4 * (gq ? (int64_t)blockIdx.x : xcd_map_runs(blockIdx.x, (ni + 3) / 4, 128)) + wave;
   while (pos < ni) {
     const BlockItem it = items[pos];
     const int b = it.batch;

@@ -45,11 +45,14 @@ __device__ __forceinline__ void hs_item(const DevPlan &d, int f0, int n, int g0,
   // w v and w of the batch's points; reads past them give 0
   const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc((void *)(om + g0), (short)0, P * 8, 0x00020000);
   const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void *)(d.pw + g0), (short)0, P * 8, 0x00020000);
+  // past the last point an empty buffer: nothing is read, and no branch makes
+  // the waits of the next K pairs count for both of its sides
   auto load = [&](int k, OperandHS (&o)[1 + NB], dbl2 &wv, dbl2 &w) {
+    const int nr = k < Pp ? np * 64 : 0;
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-          (void *)(pb + (int64_t)q * plane + (int64_t)(k >> 2) * np * 4), (short)0, np * 64, 0x00020000);
+          (void *)(pb + (int64_t)q * plane + (int64_t)(k >> 2) * np * 4), (short)0, nr, 0x00020000);
 #pragma unroll
       for (int x = 0; x < 1 + NB; ++x)
         o[x].v[q] = __builtin_bit_cast(dbl2, __builtin_amdgcn_raw_buffer_load_b128(rs, off[x], 0, 0));
@@ -87,7 +90,7 @@ __device__ __forceinline__ void hs_item(const DevPlan &d, int f0, int n, int g0,
     __builtin_amdgcn_sched_barrier(0);
     multiply(oa, va, wa);
     __builtin_amdgcn_sched_barrier(0);
-    if (k + 16 < Pp) load(k + 16, oa, va, wa);
+    load(k + 16, oa, va, wa);
     __builtin_amdgcn_sched_barrier(0);
     multiply(ob, vb, wb);
     __builtin_amdgcn_sched_barrier(0);
@@ -115,7 +118,7 @@ __global__ __launch_bounds__(256, 3) void k_contract_hs(DevPlan d, const BlockIt
     return uniform_i64(p);
   };
   int64_t pos = PERSIST ? draw()
-                        : 4 * (gq ? (int64_t)blockIdx.x : xcd_map(blockIdx.x, (ni + 3) / 4)) + wave;
+                        : 4 * (gq ? (int64_t)blockIdx.x : xcd_map_runs(blockIdx.x, (ni + 3) / 4, 128)) + wave;
   while (pos < ni) {
     const BlockItem it = items[pos];
     const int b = it.batch;
