@@ -9,11 +9,10 @@
 // block).  So per batch one product Y = M Phi (2 P n^2 flops, on FP64 MFMA)
 // and lane-local dot products of Y with phi and grad phi.
 //   k_grad_cdense  M of every batch of a pass, dense (np x np, zero padding);
-//   k_grad_gemm    one workgroup per (batch, 64-point tile, 64-function tile
-//                  i): Y_i(pt) = sum_j phi_j(pt) M_ji over 16-function K
-//                  chunks (phi slice and M slice by LDS DMA, double
-//                  buffered), then n and grad n partials over its functions;
-//   k_grad_points  the partials of a point over the function tiles, in order.
+//   k_grad_gemm    one wave per (batch, point chunk, function chunk i) of at
+//                  most 64 x 64: Y_i(pt) = sum_j phi_j(pt) M_ji, then n and
+//                  grad n partials over its functions;
+//   k_grad_points  the partials of a point over the function chunks, in order.
 // (Gathering the M slices from the store inside the product instead of
 // materialising M was slower: two dependent memory round trips per 16
 // functions do not hide behind 16 MFMAs.)
@@ -21,6 +20,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "q4c_internal.h"
 #include "q4c_device.h"
@@ -28,9 +28,7 @@
 namespace q4c {
 namespace {
 
-constexpr int GT = 64;    // points and functions per output tile
-constexpr int GK = 16;    // functions per K chunk
-constexpr int GS = 1024;  // doubles per slice image (64 x 16)
+constexpr int GT = 64;  // most points and functions of an item
 
 
 // packed slot data of a batch function: slot, the slot's first function and
@@ -79,214 +77,212 @@ __global__ __launch_bounds__(256) void k_grad_cdense(DevPlan d, const int32_t *i
   if (po_lds)
     for (int t = threadIdx.x; t < nrs * ncs; t += blockDim.x) s_po[t] = stored_po(rs0 + t / ncs, cs0 + t % ncs);
   __syncthreads();  // pair offsets visible
-  // the tile's elements with r <= c (all of them off the diagonal), four per
-  // thread at a time, loads unconditional (element 0 of the store stands in
-  // for an absent one) and in flight together
-  for (int x0 = threadIdx.x; x0 < CD_T * CD_T; x0 += 4 * blockDim.x) {
-    int64_t a1[4], a2[4];
-    bool live[4], self[4];
+  // Lane l holds column c0 + l, wave w takes rows w, w + 4, .. of the tile, so
+  // the row's data are wave-uniform and an element costs a table lookup, one
+  // multiply-add and its load.  Eight rows at a time, loads unconditional
+  // (element 0 of the store stands in for an absent one) and in flight
+  // together; elements below the diagonal come from their mirror.
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c = c0 + lane;
+  const int64_t ci = s_ci[lane];
+  const int cs = fslot(ci), ic = c - ffirst(ci), cn = fcount(ci);
+  const bool self_tile = rs1 >= cs0;  // workgroup-uniform: some row and column of one atom
+  for (int i0 = 0; i0 < CD_T / 4; i0 += 8) {
+    int64_t a1[8], a2[8];
+    bool live[8];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int x = x0 + u * blockDim.x;
-      const int rl = x / CD_T, cl = x % CD_T;
-      const int r = r0 + rl, c = c0 + cl;
+    for (int u = 0; u < 8; ++u) {
+      const int rl = 4 * (i0 + u) + wave, r = r0 + rl;
+      const int64_t ri = uniform_i64(s_ri[rl]);
+      const int rs = fslot(ri), ir = r - ffirst(ri);
       const bool in = r < n && c < n && r <= c;
-      const int64_t ri = s_ri[rl], ci = s_ci[cl];
-      const int rs = fslot(ri), cs = fslot(ci);
       const int64_t po = !in ? -1 : (po_lds ? s_po[(rs - rs0) * ncs + cs - cs0] : stored_po(rs, cs));
-      const int ir = r - ffirst(ri), ic = c - ffirst(ci), cn = fcount(ci);
       live[u] = po >= 0;
-      self[u] = rs == cs;
-      a1[u] = live[u] ? po + (int64_t)ir * cn + ic : 0;                // rs <= cs here
-      a2[u] = live[u] && self[u] ? po + (int64_t)ic * cn + ir : 0;     // the self pair's transposed element
+      a1[u] = live[u] ? po + (uint32_t)(ir * cn + ic) : 0;              // rs <= cs here
+      a2[u] = live[u] && rs == cs ? po + (uint32_t)(ic * cn + ir) : -1;  // the self pair's transposed element
     }
-    double c1[4], c2[4];
+    double v1[8];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      c1[u] = coef[a1[u]];
-      c2[u] = coef[a2[u]];
+    for (int u = 0; u < 8; ++u) v1[u] = coef[a1[u]];
+    if (self_tile) {
+      double v2[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v2[u] = coef[a2[u] >= 0 ? a2[u] : 0];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v1[u] += a2[u] >= 0 ? v2[u] : 0.0;
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int x = x0 + u * blockDim.x;
-      s_t[x / CD_T][x % CD_T] = live[u] ? 0.5 * (c1[u] + (self[u] ? c2[u] : 0.0)) : 0.0;
+    for (int u = 0; u < 8; ++u) {
+      const int rl = 4 * (i0 + u) + wave;
+      const double v = live[u] ? 0.5 * v1[u] : 0.0;
+      s_t[rl][lane] = v;
+      if (rl < nr && lane < nc && (rt != ct || rl <= lane)) M[(int64_t)(r0 + rl) * np + c] = v;
     }
   }
   __syncthreads();  // the tile is in LDS
-  // the tile (r <= c part; on the diagonal tile the rest from its mirror) and,
-  // off the diagonal, its mirror, both along rows
-  for (int x = threadIdx.x; x < nr * nc; x += blockDim.x) {
-    const int rl = x / nc, cl = x % nc;
-    const double v = (rt == ct && rl > cl) ? s_t[cl][rl] : s_t[rl][cl];
-    M[(int64_t)(r0 + rl) * np + c0 + cl] = v;
-  }
-  if (rt != ct)
-    for (int x = threadIdx.x; x < nr * nc; x += blockDim.x) {
-      const int cl = x / nr, rl = x % nr;
-      M[(int64_t)(c0 + cl) * np + r0 + rl] = s_t[rl][cl];
-    }
+  // its mirror, along rows (on the diagonal tile the part below the diagonal)
+  for (int rl = wave; rl < nc; rl += 4)
+    if (lane < nr && (rt != ct || rl > lane)) M[(int64_t)(c0 + rl) * np + r0 + lane] = s_t[lane][rl];
 }
 
-// LDS DMA of K chunk j0: the phi slice (panel component 0, 16 groups of 4
-// points from pt0, functions j0..j0+15; image [group][function][point % 4],
-// the panel's own order) and the M slice (rows j0..j0+15, columns
-// i0..i0+63; image [row][column]).  Four wave-wide loads per wave, two rows
-// of 512 bytes each.  Groups past the batch's points and columns past np
-// load valid entries instead: they only feed tile rows and columns the
-// epilogue skips.
-__device__ __forceinline__ void gemm_dma(const double *pb, int np, int Pp, int pt0, int j0, const double *M, int i0,
-                                         double *sA, double *sB) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int half = lane >> 5, piece = lane & 31;
+// One wave's item: Y = M phi for F <= 4 blocks of 16 functions and Q <= 4
+// blocks of 16 points, then its products with phi, 2 d_x phi, 2 d_y phi and
+// 2 d_z phi summed over the item's functions, written as 4 x 16 Q partials.
+// FP64 MFMA 16x16x4 with A = M [function i][j] (M is symmetric, so its row j
+// is read along i) and B = phi [j][point].  Two blocks are read at a time, 16
+// bytes per lane: lane l16 holds functions (or points) 2 l16 and 2 l16 + 1 of
+// the 32, one of either block, so a K step of 4 functions is at most four
+// loads for 16 MFMAs, with no vector instruction beside them; an odd last
+// block takes 8-byte loads.  No LDS, no barriers: operands go to registers
+// three K steps ahead, and the waves of a workgroup (items of one batch) share
+// them in L1 and L2.
+//
+// Bound: the matrix pipe two thirds of the time, and L2 misses: an item reads
+// 512 n bytes each of M and phi per 64 x 64 outputs, and a batch's M (0.9 MB at
+// n = 335) leaves an XCD's L2 between the waves that share it.  40 atoms, both
+// components (155 and 335 functions per batch on average) 4.17 -> 3.31 ms
+// against 64 x 64 tiles in LDS with a barrier every 16 functions; the MFMAs
+// alone take 1.7 ms at their peak rate.  Chunks of at most 48 points with
+// three waves per SIMD took the same time.
+template <int F, int Q>
+__device__ __forceinline__ void grad_item(int np, int Pp, int i0, int q0, const double *M, const double *pb,
+                                          double *part) {
+  constexpr int FP = F / 2, QP = Q / 2, NS = 4;  // block pairs; operand sets
+  const int lane = threadIdx.x & 63, l16 = lane & 15, lk = lane >> 4;
+  const int64_t plane = (int64_t)Pp * np;
+  // lane offsets (bytes) of the operands: M row lk, function; quad, function lk, point of the quad
+  const uint32_t am = (uint32_t)lk * np * 8u + 16u * l16, am1 = (uint32_t)lk * np * 8u + 8u * (16 * (F - 1) + l16);
+  uint32_t bp[QP + 1];
 #pragma unroll
-  for (int k = wave; k < 8; k += 4) {
-    const int g = min((pt0 >> 2) + 2 * k + half, (Pp >> 2) - 1);
-    __builtin_amdgcn_global_load_lds(
-        (const void *)(pb + ((int64_t)g * np + j0 + (piece >> 1)) * 4 + 2 * (piece & 1)),
-        (lds_void *)(sA + k * 128), 16, 0, 0);
-    const int col = min(i0 + 2 * piece, np - 2);
-    __builtin_amdgcn_global_load_lds((const void *)(M + (int64_t)(j0 + 2 * k + half) * np + col),
-                                     (lds_void *)(sB + k * 128), 16, 0, 0);
+  for (int q = 0; q < QP; ++q) bp[q] = ((uint32_t)(8 * q + (l16 >> 1)) * np + lk) * 32u + 16u * (l16 & 1);
+  bp[QP] = ((uint32_t)(4 * (Q - 1) + (l16 >> 2)) * np + lk) * 32u + 8u * (l16 & 3);
+  const double *Mi = M + i0, *pq = pb + (int64_t)q0 * np;  // q0: the item's first point (np doubles per point)
+  struct Set {
+    double a[F], b[Q];
+  } st[NS];
+  // past the last function an empty buffer: nothing is read, and no branch
+  // makes the waits of the next K steps count for both of its sides
+  auto load = [&](Set &s, int j) {
+    const int nr = j < np ? 0x7ffffff0 : 0;
+    const __amdgpu_buffer_rsrc_t ra =
+        __builtin_amdgcn_make_buffer_rsrc((void *)(Mi + (int64_t)j * np), (short)0, nr, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rb =
+        __builtin_amdgcn_make_buffer_rsrc((void *)(pq + 4 * (int64_t)j), (short)0, nr, 0x00020000);
+#pragma unroll
+    for (int f = 0; f < FP; ++f) {
+      const dbl2 v = __builtin_bit_cast(dbl2, __builtin_amdgcn_raw_buffer_load_b128(ra, am + 256 * f, 0, 0));
+      s.a[2 * f] = v[0];
+      s.a[2 * f + 1] = v[1];
+    }
+    if (F & 1) s.a[F - 1] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(ra, am1, 0, 0));
+#pragma unroll
+    for (int q = 0; q < QP; ++q) {
+      const dbl2 v = __builtin_bit_cast(dbl2, __builtin_amdgcn_raw_buffer_load_b128(rb, bp[q], 0, 0));
+      s.b[2 * q] = v[0];
+      s.b[2 * q + 1] = v[1];
+    }
+    if (Q & 1) s.b[Q - 1] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rb, bp[QP], 0, 0));
+  };
+  dbl4 acc[F][Q];
+#pragma unroll
+  for (int f = 0; f < F; ++f)
+#pragma unroll
+    for (int q = 0; q < Q; ++q) acc[f][q] = dbl4{0.0, 0.0, 0.0, 0.0};
+  load(st[0], 0);
+  load(st[1], 4);
+  load(st[2], 8);
+  for (int j = 0; j < np; j += 16) {  // np is a multiple of 16
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+      load(st[(u + 3) % NS], j + 4 * u + 12);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int f = 0; f < F; ++f)
+#pragma unroll
+        for (int q = 0; q < Q; ++q) acc[f][q] = mfma64(st[u].a[f], st[u].b[q], acc[f][q]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  // register r of block (f, q): Y at row R = lk + 4 r, i.e. function 2 R + f % 2
+  // of the block pair (R of an odd last block), and the point of column l16
+  double s[Q][4];
+#pragma unroll
+  for (int q = 0; q < Q; ++q)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) s[q][c] = 0.0;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(pq + c * plane + 4 * (int64_t)i0), (short)0, 0x7ffffff0, 0x00020000);
+#pragma unroll
+    for (int f = 0; f < F; ++f)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const bool pair = f < 2 * FP;
+        // bytes from function lk of the quad to the row's function
+        const uint32_t fo = (pair ? (uint32_t)(32 * (f >> 1) + 8 * r + (f & 1)) + lk : (uint32_t)(16 * f + 4 * r)) * 32u;
+#pragma unroll
+        for (int q = 0; q < QP; ++q) {
+          const dbl2 e = __builtin_bit_cast(dbl2, __builtin_amdgcn_raw_buffer_load_b128(rs, bp[q] + fo, 0, 0));
+          s[2 * q][c] += acc[f][2 * q][r] * e[0];
+          s[2 * q + 1][c] += acc[f][2 * q + 1][r] * e[1];
+        }
+        if (Q & 1) {
+          const double e = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, bp[QP] + fo, 0, 0));
+          s[Q - 1][c] += acc[f][Q - 1][r] * e;
+        }
+      }
+    __builtin_amdgcn_sched_barrier(0);  // one component's loads at a time
+  }
+  // over the rows of the four lane groups; group lk writes component lk
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    double mine = 0.0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      double v = s[q][c];
+      v += __shfl_xor(v, 16);
+      v += __shfl_xor(v, 32);
+      if (lk == c) mine = c ? 2.0 * v : v;
+    }
+    const int pt = q < 2 * QP ? 32 * (q >> 1) + 2 * l16 + (q & 1) : 16 * q + l16;
+    part[(int64_t)lk * Pp + q0 + pt] = mine;
   }
 }
 
-// The 16 MFMA operands of one K chunk of a wave, A[mb][ks] at pa + 2048 mb +
-// 128 ks and B[nb][ks] at pb + 2048 ks + 128 nb (bytes), read in one asm
-// block that also waits for them.  Issued by hand so that the compiler, which
-// cannot tell these reads from the LDS DMA still in flight into the other
-// buffers, does not wait for that DMA first.
-__device__ __forceinline__ void read_operands(uint32_t pa, uint32_t pb, double (&a)[2][4], double (&b)[2][4]) {
-  asm volatile(
-      "ds_read_b64 %0, %16\n"
-      "ds_read_b64 %1, %16 offset:128\n"
-      "ds_read_b64 %2, %16 offset:256\n"
-      "ds_read_b64 %3, %16 offset:384\n"
-      "ds_read_b64 %4, %16 offset:2048\n"
-      "ds_read_b64 %5, %16 offset:2176\n"
-      "ds_read_b64 %6, %16 offset:2304\n"
-      "ds_read_b64 %7, %16 offset:2432\n"
-      "ds_read_b64 %8, %17\n"
-      "ds_read_b64 %9, %17 offset:2048\n"
-      "ds_read_b64 %10, %17 offset:4096\n"
-      "ds_read_b64 %11, %17 offset:6144\n"
-      "ds_read_b64 %12, %17 offset:128\n"
-      "ds_read_b64 %13, %17 offset:2176\n"
-      "ds_read_b64 %14, %17 offset:4224\n"
-      "ds_read_b64 %15, %17 offset:6272\n"
-      "s_waitcnt lgkmcnt(0)"
-      : "=&v"(a[0][0]), "=&v"(a[0][1]), "=&v"(a[0][2]), "=&v"(a[0][3]), "=&v"(a[1][0]), "=&v"(a[1][1]),
-        "=&v"(a[1][2]), "=&v"(a[1][3]), "=&v"(b[0][0]), "=&v"(b[0][1]), "=&v"(b[0][2]), "=&v"(b[0][3]),
-        "=&v"(b[1][0]), "=&v"(b[1][1]), "=&v"(b[1][2]), "=&v"(b[1][3])
-      : "v"(pa), "v"(pb)
-      : "memory");
-}
-
-// One output tile: 4 waves, wave w owns points 32 (w & 1) .. +31 and functions
-// 32 (w >> 1) .. +31 of the tile as 2 x 2 blocks of 16 x 16 (FP64 MFMA
-// 16x16x4: A = phi [point][j], B = M [j][i]).  Three buffers: while chunk kc
-// is multiplied, chunk kc + 1 may still be in flight and chunk kc + 2 is
-// issued.  Per K chunk each wave reads its 16 operands into registers, issues
-// the DMA of chunk kc + 2, then its 16 MFMAs.  Epilogue: per
-// (point, function) of the wave the products with phi, 2 d_x phi, 2 d_y phi,
-// 2 d_z phi, summed over the wave's functions (lane shuffles) and over the two
-// waves of a point range (LDS), written as 4 x 64 partials of the tile.
+// Four independent waves per workgroup, one item each: items (batch, point
+// chunk, function chunk) where the batch's 16-blocks are divided evenly into as
+// many chunks of at most four as they need (no padding beyond the blocks).
 __global__ __launch_bounds__(256, 2) void k_grad_gemm(DevPlan d, const int32_t *items, int64_t it0, int64_t nit,
                                                       const int64_t *cd_off, const int64_t *part_off,
                                                       const double *cd, const double *panel, double *part) {
-  __shared__ double sA[3][GS], sB[3][GS];
-  __shared__ double s_red[2][GT][4];
-  const int64_t it = it0 + xcd_map(blockIdx.x, nit);
-  const int b = items[3 * it], tp = items[3 * it + 1], ti = items[3 * it + 2];
-  const int g0 = d.batch_pt_off[b], P = d.batch_pt_off[b + 1] - g0;
-  const int n = d.batch_fn_off[b + 1] - d.batch_fn_off[b];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t pos = 4 * xcd_map_runs(blockIdx.x, (nit + 3) / 4, 16) + wave;
+  if (pos >= nit) return;
+  const int64_t it = it0 + pos;
+  const int b = __builtin_amdgcn_readfirstlane(items[3 * it]), tp = __builtin_amdgcn_readfirstlane(items[3 * it + 1]),
+            ti = __builtin_amdgcn_readfirstlane(items[3 * it + 2]);
+  const int P = d.batch_pt_off[b + 1] - d.batch_pt_off[b], n = d.batch_fn_off[b + 1] - d.batch_fn_off[b];
   const int Pp = (int)pad16(P), np = (int)pad16(n);
-  const int pt0 = GT * tp, i0 = GT * ti;
-  const double *pb = panel + d.panel_off[b];
-  const int64_t plane = (int64_t)Pp * np;
-  const double *M = cd + cd_off[b];
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l16 = lane & 15, lk = lane >> 4;
-  const int mq = wave & 1, nq = wave >> 1;
-  dbl4 acc[2][2];
-#pragma unroll
-  for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = dbl4{0.0, 0.0, 0.0, 0.0};
-  const int nk = np / GK;
-  // this lane's operand addresses within a buffer (A: point block 0, K step 0;
-  // B: function block 0, K step 0), bytes
-  const uint32_t oa = 8u * (uint32_t)((8 * mq + (l16 >> 2)) * 64 + 4 * lk + (l16 & 3));
-  const uint32_t ob = 8u * (uint32_t)(lk * GT + 32 * nq + l16);
-  gemm_dma(pb, np, Pp, pt0, 0, M, i0, sA[0], sB[0]);
-  if (nk > 1) gemm_dma(pb, np, Pp, pt0, GK, M, i0, sA[1], sB[1]);
-  for (int kc = 0; kc < nk; ++kc) {
-    const int buf = kc % 3;
-    // chunk kc has landed everywhere (chunk kc + 1, four loads per wave, may
-    // still be in flight); every wave has read chunk kc - 1
-    if (kc + 1 < nk)
-      barrier_vm<4>();
-    else
-      barrier_vm<0>();
-    double a[2][4], bb[2][4];
-    read_operands(lds_addr(sA[buf]) + oa, lds_addr(sB[buf]) + ob, a, bb);
-    if (kc + 2 < nk) gemm_dma(pb, np, Pp, pt0, GK * (kc + 2), M, i0, sA[(kc + 2) % 3], sB[(kc + 2) % 3]);
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = mfma64(a[mb][ks], bb[nb][ks], acc[mb][nb]);
-  }
-  // epilogue: lane (l16, lk) register r of block (mb, nb) holds Y at point
-  // 32 mq + 16 mb + lk + 4 r of the tile and function 32 nq + 16 nb + l16
-  double o[2][4][4];  // [mb][r][n, d_x n, d_y n, d_z n]
-#pragma unroll
-  for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int pg = pt0 + 32 * mq + 16 * mb + d_row_f64(lk, r);
-#pragma unroll
-      for (int c = 0; c < 4; ++c) o[mb][r][c] = 0.0;
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb) {
-        const int fi = i0 + 32 * nq + 16 * nb + l16;
-        if (pg < P && fi < n) {
-          const double y = acc[mb][nb][r];
-          const double *e = pb + ((int64_t)(pg >> 2) * np + fi) * 4 + (pg & 3);
-          o[mb][r][0] += y * e[0];
-          o[mb][r][1] += 2.0 * y * e[plane];
-          o[mb][r][2] += 2.0 * y * e[2 * plane];
-          o[mb][r][3] += 2.0 * y * e[3 * plane];
-        }
-      }
+  const int mf = np >> 4, mq = Pp >> 4, nf = (mf + 3) >> 2, nq = (mq + 3) >> 2;
+  const int fb = (int)((int64_t)ti * mf / nf), qb = (int)((int64_t)tp * mq / nq);
+  const int F = (int)((int64_t)(ti + 1) * mf / nf) - fb, Q = (int)((int64_t)(tp + 1) * mq / nq) - qb;
+  const double *pb = panel + d.panel_off[b], *M = cd + cd_off[b];
+  double *pt = part + part_off[b] + (int64_t)ti * 4 * Pp;
+  auto go = [&](auto f, auto q) { grad_item<decltype(f)::value, decltype(q)::value>(np, Pp, 16 * fb, 16 * qb, M, pb, pt); };
+  auto with_q = [&](auto f) {
+    switch (Q) {
+      case 1: go(f, std::integral_constant<int, 1>{}); break;
+      case 2: go(f, std::integral_constant<int, 2>{}); break;
+      case 3: go(f, std::integral_constant<int, 3>{}); break;
+      default: go(f, std::integral_constant<int, 4>{}); break;
     }
-  // over the 16 functions of a block (the lanes l16 of a lane row)
-#pragma unroll
-  for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        double v = o[mb][r][c];
-        v += __shfl_xor(v, 1);
-        v += __shfl_xor(v, 2);
-        v += __shfl_xor(v, 4);
-        v += __shfl_xor(v, 8);
-        o[mb][r][c] = v;
-      }
-  if (l16 == 0) {
-#pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) s_red[nq][32 * mq + 16 * mb + d_row_f64(lk, r)][c] = o[mb][r][c];
-  }
-  barrier_vm<63>();  // the waves' sums are visible
-  {
-    const int pt = tid >> 2, c = tid & 3;
-    if (pt0 + pt < Pp)
-      part[part_off[b] + ((int64_t)ti * 4 + c) * Pp + pt0 + pt] = s_red[0][pt][c] + s_red[1][pt][c];
+  };
+  switch (F) {
+    case 1: with_q(std::integral_constant<int, 1>{}); break;
+    case 2: with_q(std::integral_constant<int, 2>{}); break;
+    case 3: with_q(std::integral_constant<int, 3>{}); break;
+    default: with_q(std::integral_constant<int, 4>{}); break;
   }
 }
 
@@ -325,7 +321,7 @@ int launch_grad_pass(const q4c_plan *p, size_t ip, const double *coef, const dou
   if (nw > 0) {
     {
       TimedLaunch tl_(p, Q4C_TIMER_DENSITY_TILES, s);
-      hipLaunchKernelGGL(k_grad_gemm, dim3((unsigned)nw), dim3(256), 0, s, p->dp, p->d_gr_items, w0, nw,
+      hipLaunchKernelGGL(k_grad_gemm, dim3((unsigned)((nw + 3) / 4)), dim3(256), 0, s, p->dp, p->d_gr_items, w0, nw,
                          p->d_gr_cd_off, p->d_gr_part_off, (const double *)p->d_gr_cd, panel, p->d_gr_part);
     }
     hipError_t e = hipGetLastError();
