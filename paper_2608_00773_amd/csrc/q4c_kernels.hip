@@ -23,6 +23,7 @@
 // The adjoint (density_on_grid) is in q4c_density_kernels.hip.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <type_traits>
 
@@ -113,56 +114,8 @@ __device__ __forceinline__ void solid_harmonic(int lm, double x, double y, doubl
 // ---------------------------------------------------------------------------
 
 // ---------------------------------------------------------------------------
-// Tile tabulation: the metadata of a tile's functions is staged in LDS, so
-// the per-(function, point) work touches global memory only for the point
-// and the four radial coefficients of its interval.
+// Tabulation: one wave walks the shells of up to 64 functions at 64 points.
 // ---------------------------------------------------------------------------
-
-struct TileMeta {
-  double ax[T], ay[T], az[T];  // centres
-  double rc[T];                // cutoffs (0 for padding)
-  double k1[T], k2[T];         // nint^2 / rcut, rcut / nint^2
-  int64_t coef[T];             // offset of the shell's table
-  int nint[T], lm[T];
-  int order[T];                // tile functions sorted by lm
-};
-
-// Stage metadata of the tile's functions (threads 0 .. T-1) and an ordering
-// by lm, so that lanes working on neighbouring items mostly take the same
-// solid-harmonic branch.
-__device__ __forceinline__ void load_tile_meta(const DevPlan &d, TileMeta &M, int f0, int n, int r0) {
-  const int tid = threadIdx.x;
-  if (tid < T) {
-    const int lf = r0 + tid;
-    if (lf < n) {
-      const int fn = d.loc_fn[f0 + lf];
-      const int a = d.fn_atom[fn], shlm = d.fn_shlm[fn], sh = shlm >> 5;
-      M.ax[tid] = d.R[3 * a];
-      M.ay[tid] = d.R[3 * a + 1];
-      M.az[tid] = d.R[3 * a + 2];
-      M.rc[tid] = d.shell_rcut[sh];
-      M.k1[tid] = d.shell_knot[2 * sh];
-      M.k2[tid] = d.shell_knot[2 * sh + 1];
-      M.coef[tid] = d.shell_coef_off[sh];
-      M.nint[tid] = d.shell_nint[sh];
-      M.lm[tid] = shlm & 31;
-    } else {
-      M.ax[tid] = M.ay[tid] = M.az[tid] = 0.0;
-      M.rc[tid] = 0.0;
-      M.k1[tid] = M.k2[tid] = 0.0;
-      M.coef[tid] = 0;
-      M.nint[tid] = 0;
-      M.lm[tid] = 32;  // padding sorts last
-    }
-  }
-  __syncthreads();
-  if (tid < T) {
-    const int mine = M.lm[tid];
-    int rank = 0;
-    for (int o = 0; o < T; ++o) rank += (M.lm[o] < mine) || (M.lm[o] == mine && o < tid);
-    M.order[rank] = tid;
-  }
-}
 
 // Radial interval of a shell (cutoff > s) at distance s: index j and s - r_j.
 // The index comes from an approximate square root corrected against the exact
@@ -183,95 +136,184 @@ __device__ __forceinline__ int radial_interval(double s, int n, double k1, doubl
   return j;
 }
 
-// phi and grad phi of tile function m at point (px, py, pz).  1/s comes from a
-// Newton-refined reciprocal square root.
-__device__ __forceinline__ void tab_meta(const DevPlan &d, const TileMeta &M, int m, double px, double py,
-                                         double pz, double &f, double &fx, double &fy, double &fz) {
-  const double dx = px - M.ax[m], dy = py - M.ay[m], dz = pz - M.az[m];
-  const double s2 = dx * dx + dy * dy + dz * dz;
-  const double rc = M.rc[m];
-  if (!(s2 < rc * rc)) {
-    f = fx = fy = fz = 0.0;
-    return;
+// lane k's value of a vector register as a scalar
+__device__ __forceinline__ int64_t lane_i64(int64_t v, int k) {
+  const uint32_t lo = __builtin_amdgcn_readlane((int)v, k), hi = __builtin_amdgcn_readlane((int)(v >> 32), k);
+  return (int64_t)((uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ double lane_f64(double v, int k) {
+  return __builtin_bit_cast(double, lane_i64(__builtin_bit_cast(int64_t, v), k));
+}
+
+// The data of up to 64 functions of a batch: lane k holds function r0 + k.
+struct FnData {
+  int atom, l, nint;
+  int i_first;  // the first function of function r0's shell, which may begin before r0 (wave-uniform)
+  double ax, ay, az, rc, k1, k2;
+  int64_t coef, u;
+};
+template <bool HS>
+__device__ __forceinline__ FnData fn_data(const DevPlan &d, int f0, int n, int r0) {
+  const int lane = threadIdx.x & 63;
+  const int mine = r0 + lane < n ? r0 + lane : n - 1;
+  const int fn = d.loc_fn[f0 + mine], shlm = d.fn_shlm[fn], sh = shlm >> 5, lm = shlm & 31;
+  FnData m;
+  m.atom = d.fn_atom[fn];
+  m.l = (lm >= 1) + (lm >= 4) + (lm >= 9) + (lm >= 16);
+  m.ax = d.R[3 * m.atom];
+  m.ay = d.R[3 * m.atom + 1];
+  m.az = d.R[3 * m.atom + 2];
+  m.rc = d.shell_rcut[sh];
+  m.k1 = d.shell_knot[2 * sh];
+  m.k2 = d.shell_knot[2 * sh + 1];
+  m.nint = d.shell_nint[sh];
+  m.coef = d.shell_coef_off[sh];
+  m.u = HS ? d.shell_u_off[sh] : 0;
+  m.i_first = r0 - __builtin_amdgcn_readlane(lm - m.l * m.l, 0);
+  return m;
+}
+
+// Functions r0 .. rn - 1 (at most 64) of a batch at this lane's point, by
+// shells: put(i, phi, d/dx, d/dy, d/dz) or (HS) put(i, phi, psi = u phi / 2, 0,
+// 0) for every function of every shell that has one in the range, in order (so
+// a first or last shell's functions outside the range too).  All lanes work on
+// the same function; lanes that are not live get zeros.
+template <bool HS, typename Put>
+__device__ __forceinline__ void walk_shells(const DevPlan &d, const FnData &m, int r0, int rn, double px, double py,
+                                            double pz, bool live, Put put) {
+  // the distance to an atom and a shell's table entry, fetched a shell ahead
+  struct { double dx, dy, dz, s2, rinv, s; } geo = {};
+  struct { dbl4 c, e; double dd; } rad;
+  int atom = -1;
+  auto fetch = [&](int k) {
+    const int at = __builtin_amdgcn_readlane(m.atom, k);
+    if (at != atom) {
+      atom = at;
+      geo.dx = px - lane_f64(m.ax, k);
+      geo.dy = py - lane_f64(m.ay, k);
+      geo.dz = pz - lane_f64(m.az, k);
+      const double s2 = geo.s2 = geo.dx * geo.dx + geo.dy * geo.dy + geo.dz * geo.dz;
+      geo.rinv = geo.s = 0.0;
+      if (s2 > 0.0) {
+        geo.rinv = __builtin_amdgcn_rsq(s2);
+        geo.rinv = geo.rinv * (1.5 - 0.5 * s2 * geo.rinv * geo.rinv);
+        geo.s = s2 * geo.rinv;
+      }
+    }
+    const double rc = lane_f64(m.rc, k);
+    rad.c = rad.e = dbl4{0.0, 0.0, 0.0, 0.0};
+    rad.dd = 0.0;
+    if (live && geo.s2 < rc * rc) {
+      const int j = radial_interval(geo.s, __builtin_amdgcn_readlane(m.nint, k), lane_f64(m.k1, k), lane_f64(m.k2, k),
+                                    rad.dd);
+      rad.c = *reinterpret_cast<const dbl4 *>(d.coef + lane_i64(m.coef, k) + 4 * (int64_t)j);
+      if (HS) rad.e = *reinterpret_cast<const dbl4 *>(d.ucoef + lane_i64(m.u, k) + 4 * (int64_t)j);
+    }
+  };
+  if (rn > r0) fetch(0);
+  for (int i = m.i_first; i < rn;) {  // the shells (wave-uniform)
+    const int ls = __builtin_amdgcn_readlane(m.l, i > r0 ? i - r0 : 0);
+    const double dx = geo.dx, dy = geo.dy, dz = geo.dz, rinv = geo.rinv, dd = rad.dd;
+    const dbl4 c = rad.c, e = rad.e;
+    if (i + 2 * ls + 1 < rn) fetch(i + 2 * ls + 1 - r0);
+    // Rt and Rt' / s, or (H/S) Rt and u / 2
+    const double R = ((c[3] * dd + c[2]) * dd + c[1]) * dd + c[0];
+    const double q = HS ? 0.5 * (((e[3] * dd + e[2]) * dd + e[1]) * dd + e[0])
+                                   : ((3.0 * c[3] * dd + 2.0 * c[2]) * dd + c[1]) * rinv;
+    auto shell = [&](auto lc) {
+      constexpr int l = decltype(lc)::value;
+      // an opaque copy: the harmonics of every l would otherwise be hoisted
+      // out of the loop over the shells and held in registers
+      double x = dx, y = dy, z = dz;
+      asm volatile("" : "+v"(x), "+v"(y), "+v"(z));
+      static_for<0, 2 * l + 1>([&](auto mc) {
+        constexpr int mm = decltype(mc)::value;
+        double S, gx, gy, gz;
+        solid_harmonic(l * l + mm, x, y, z, S, gx, gy, gz);
+        const double f = R * S;
+        if (HS)
+          put(i + mm, f, q * f, 0.0, 0.0);
+        else
+          put(i + mm, f, q * x * S + R * gx, q * y * S + R * gy, q * z * S + R * gz);
+      });
+      i += 2 * l + 1;
+    };
+    switch (ls) {
+      case 0: shell(std::integral_constant<int, 0>{}); break;
+      case 1: shell(std::integral_constant<int, 1>{}); break;
+      case 2: shell(std::integral_constant<int, 2>{}); break;
+      case 3: shell(std::integral_constant<int, 3>{}); break;
+      default: shell(std::integral_constant<int, 4>{}); break;
+    }
   }
-  double rinv = 0.0, s = 0.0;
-  if (s2 > 0.0) {
-    rinv = __builtin_amdgcn_rsq(s2);
-    rinv = rinv * (1.5 - 0.5 * s2 * rinv * rinv);
-    s = s2 * rinv;
-  }
-  double dd;
-  const int j = radial_interval(s, M.nint[m], M.k1[m], M.k2[m], dd);
-  const dbl4 c = *reinterpret_cast<const dbl4 *>(d.coef + M.coef[m] + 4 * (int64_t)j);
-  const double R = ((c[3] * dd + c[2]) * dd + c[1]) * dd + c[0];
-  const double q = ((3.0 * c[3] * dd + 2.0 * c[2]) * dd + c[1]) * rinv;  // Rt'(s) / s
-  double S, gx, gy, gz;
-  solid_harmonic(M.lm[m], dx, dy, dz, S, gx, gy, gz);
-  f = R * S;
-  fx = q * dx * S + R * gx;
-  fy = q * dy * S + R * gy;
-  fz = q * dz * S + R * gz;
 }
 
 // ---------------------------------------------------------------------------
-// nao_tabulate: one workgroup per (batch, 64-function tile) of the requested
-// batch range, the same tabulation as the panels (tile metadata in LDS,
-// functions taken in lm order), staged in LDS per 8 points and written as
-// runs of the tile's functions: out is [ncomp][P][n] per batch (FP64), or
-// [ncomp][2][P][n] floats with the hi and lo planes (F32_HILO).
+// nao_tabulate: out is [ncomp][P][n] per batch (FP64), or [ncomp][2][P][n]
+// floats with the hi and lo planes (F32_HILO).  One workgroup per (batch,
+// 64-function tile, 64 points): each wave walks the shells of 8 functions, two
+// components at a time (67 KB of LDS, so that two workgroups share a CU), and
+// the values leave as runs of the tile's 64 functions per point.
+//
+// Bound: the latency of the shells' table reads, with four waves per SIMD to
+// cover it (0.16 ms of stores alone, 0.25 ms without the stores).  30 atoms
+// (0.79 GB, 0.12 ms at the rate of a fill) 0.31 ms with every function looked
+// up on its own by one workgroup per tile, 0.28 ms with that split over the
+// points, 0.26 ms so; 16 functions per wave 0.30 ms; one wave per 64 functions
+// with runs of 16, as the panels, 0.37 ms (lines shared by two runs).
 // ---------------------------------------------------------------------------
 
 template <bool HILO>
-__global__ __launch_bounds__(256) void k_tabulate(DevPlan d, const WorkItem *tiles, int64_t t0, int64_t b0, int deriv,
-                                                  void *out) {
-  constexpr int CP = 8;
+__global__ __launch_bounds__(512, 4) void k_tabulate(DevPlan d, const WorkItem *tiles, int64_t t0, int64_t nt, int npb,
+                                                     int64_t b0, int deriv, void *out) {
   constexpr int SR = T + 1;
-  __shared__ TileMeta M;
-  __shared__ double st[4 * CP * SR];
-  const WorkItem it = tiles[t0 + blockIdx.x];
+  __shared__ double st[2][64 * SR];
+  const int64_t bid = xcd_map(blockIdx.x + (int64_t)blockIdx.y * gridDim.x, nt * npb);  // as in k_panel
+  const WorkItem it = tiles[t0 + bid / npb];
   const int b = it.batch;
   const int g0 = d.batch_pt_off[b], P = d.batch_pt_off[b + 1] - g0;
   const int f0 = d.batch_fn_off[b], n = d.batch_fn_off[b + 1] - f0;
   const int r0 = it.ti * T;
   const int nrow = n - r0 < T ? n - r0 : T;
-  const int nq = deriv ? 4 : 1;
   const int64_t plane = (int64_t)P * n;
-  const int64_t base = (int64_t)nq * (d.tab_off[b] - d.tab_off[b0]);  // values before this batch
-  load_tile_meta(d, M, f0, n, r0);
-  __syncthreads();
-  for (int g8 = 0; g8 < P; g8 += CP) {
-    for (int e = threadIdx.x; e < T * CP; e += 256) {
-      const int k = e / CP, pt = e % CP;
-      const int fl = M.order[k];
-      double f = 0.0, fx = 0.0, fy = 0.0, fz = 0.0;
-      const int g = g8 + pt;
-      if (M.nint[fl] > 0 && g < P) tab_meta(d, M, fl, d.px[g0 + g], d.py[g0 + g], d.pz[g0 + g], f, fx, fy, fz);
-      st[(0 * CP + pt) * SR + fl] = f;
-      st[(1 * CP + pt) * SR + fl] = fx;
-      st[(2 * CP + pt) * SR + fl] = fy;
-      st[(3 * CP + pt) * SR + fl] = fz;
-    }
-    __syncthreads();
-    // (component, point) rows of the tile's functions: 256 threads = 4 rows x 64 functions
-    for (int e = threadIdx.x; e < nq * CP * T; e += 256) {
-      const int fl = e % T, row = e / T;
-      const int q = row / CP, pt = row % CP;
-      const int g = g8 + pt;
-      if (fl < nrow && g < P) {
-        const double x = st[(q * CP + pt) * SR + fl];
-        const int64_t o = (int64_t)g * n + r0 + fl;
-        if (HILO) {
-          float *of = static_cast<float *>(out) + 2 * (base + q * plane);
-          const float hi = (float)x;
-          of[o] = hi;
-          of[plane + o] = (float)(x - (double)hi);
-        } else {
-          static_cast<double *>(out)[base + q * plane + o] = x;
+  const int64_t base = (deriv ? 4 : 1) * (d.tab_off[b] - d.tab_off[b0]);  // values before this batch
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int p0 = 64 * (int)(bid % npb);
+  if (p0 >= P) return;  // workgroup-uniform
+  const int w0 = r0 + 8 * wave, wn = w0 + 8 < n ? w0 + 8 : n;  // this wave's functions
+  const FnData fd = fn_data<false>(d, f0, n, w0 < n ? w0 : n - 1);
+  const int npt = P - p0 < 64 ? P - p0 : 64;
+  const bool live = lane < npt;
+  const int g = g0 + p0 + (live ? lane : 0);
+  const double px = d.px[g], py = d.py[g], pz = d.pz[g];
+  auto pass = [&](auto qc) {  // components q and q + 1
+    constexpr int q = decltype(qc)::value;
+    if (w0 < n)
+      walk_shells<false>(d, fd, w0, wn, px, py, pz, live, [&](int i, double f, double fx, double fy, double fz) {
+        if (i < w0 || i >= wn) return;  // of a shell that another wave shares
+        st[0][lane * SR + i - r0] = q ? fy : f;
+        st[1][lane * SR + i - r0] = q ? fz : fx;
+      });
+    __syncthreads();  // staged
+    if (lane < nrow)
+      for (int c = 0; c < (deriv ? 2 : 1); ++c)
+#pragma unroll 8
+        for (int pt = wave; pt < npt; pt += 8) {
+          const double x = st[c][pt * SR + lane];
+          const int64_t o = (int64_t)(p0 + pt) * n + r0 + lane;
+          if (HILO) {
+            float *of = static_cast<float *>(out) + 2 * (base + (q + c) * plane);
+            const float hi = (float)x;
+            of[o] = hi;
+            of[plane + o] = (float)(x - (double)hi);
+          } else {
+            static_cast<double *>(out)[base + (q + c) * plane + o] = x;
+          }
         }
-      }
-    }
-    __syncthreads();  // st consumed
-  }
+    __syncthreads();  // read
+  };
+  pass(std::integral_constant<int, 0>{});
+  if (deriv) pass(std::integral_constant<int, 2>{});
 }
 
 // ---------------------------------------------------------------------------
@@ -365,21 +407,12 @@ constexpr int panel_stage(int kind) {           // staged bytes per wave: four r
          : kind == PK_SPLIT ? 4 * PR8 + 48 * PR4
                             : 4 * PR8 + 72 * PR2;
 }
-// lane k's value of a vector register as a scalar
-__device__ __forceinline__ int64_t lane_i64(int64_t v, int k) {
-  const uint32_t lo = __builtin_amdgcn_readlane((int)v, k), hi = __builtin_amdgcn_readlane((int)(v >> 32), k);
-  return (int64_t)((uint64_t)hi << 32 | lo);
-}
-__device__ __forceinline__ double lane_f64(double v, int k) {
-  return __builtin_bit_cast(double, lane_i64(__builtin_bit_cast(int64_t, v), k));
-}
-
 template <int KIND>
 __global__ __launch_bounds__(64, 3) void k_panel(DevPlan d, const WorkItem *tiles, int64_t t0, int64_t nt,
                                                              int sub, int npb, double *panel, const double *om) {
   __shared__ __attribute__((aligned(16))) unsigned char st[panel_stage(KIND)];
   // neighbouring waves (of one batch) on one XCD
-  const int64_t bid = xcd_map(blockIdx.x, nt * sub * npb), pos = bid / npb;
+  const int64_t bid = xcd_map(blockIdx.x + (int64_t)blockIdx.y * gridDim.x, nt * sub * npb), pos = bid / npb;
   const int p0 = 64 * (int)(bid % npb);
   const WorkItem it = tiles[t0 + pos / sub];
   const int b = it.batch, rows = T / sub;
@@ -390,19 +423,10 @@ __global__ __launch_bounds__(64, 3) void k_panel(DevPlan d, const WorkItem *tile
   if (r0 >= np || p0 >= Pp) return;
   const int r1 = r0 + rows < np ? r0 + rows : np, rn = r1 < n ? r1 : n;  // rows written; of functions
   const int lane = threadIdx.x;
-  // lane k: function r0 + k
-  const int mine = r0 + lane < n ? r0 + lane : n - 1;
-  const int fn = d.loc_fn[f0 + mine], m_atom = d.fn_atom[fn], m_shlm = d.fn_shlm[fn], m_sh = m_shlm >> 5;
-  const int m_lm = m_shlm & 31, m_l = (m_lm >= 1) + (m_lm >= 4) + (m_lm >= 9) + (m_lm >= 16);
-  const double m_ax = d.R[3 * m_atom], m_ay = d.R[3 * m_atom + 1], m_az = d.R[3 * m_atom + 2];
-  const double m_rc = d.shell_rcut[m_sh], m_k1 = d.shell_knot[2 * m_sh], m_k2 = d.shell_knot[2 * m_sh + 1];
-  const int m_nint = d.shell_nint[m_sh];
-  const int64_t m_coef = d.shell_coef_off[m_sh], m_u = KIND == PK_HS ? d.shell_u_off[m_sh] : 0;
-  // the first function's shell may begin before r0
-  const int i_first = r0 - __builtin_amdgcn_readlane(m_lm - m_l * m_l, 0);
   double *pb = panel + d.panel_off[b];
   const int64_t plane = (int64_t)Pp * np;
   constexpr int NQ = KIND == PK_HS ? 2 : KIND == PK_F64 ? 4 : 1;  // FP64 planes
+  const FnData fd = fn_data<KIND == PK_HS>(d, f0, n, r0);
   const int pt = p0 + lane;
   const bool live = pt < P;
   const int g = g0 + (live ? pt : 0);
@@ -492,71 +516,7 @@ __global__ __launch_bounds__(64, 3) void k_panel(DevPlan d, const WorkItem *tile
     }
     if (row == 3) flush(i >> 2);  // wave-uniform
   };
-  // the distance to an atom and a shell's table entry, fetched a shell ahead
-  struct { double dx, dy, dz, s2, rinv, s; } geo = {};
-  struct { dbl4 c, e; double dd; } rad;
-  int atom = -1;
-  auto fetch = [&](int k) {
-    const int at = __builtin_amdgcn_readlane(m_atom, k);
-    if (at != atom) {
-      atom = at;
-      geo.dx = px - lane_f64(m_ax, k);
-      geo.dy = py - lane_f64(m_ay, k);
-      geo.dz = pz - lane_f64(m_az, k);
-      const double s2 = geo.s2 = geo.dx * geo.dx + geo.dy * geo.dy + geo.dz * geo.dz;
-      geo.rinv = geo.s = 0.0;
-      if (s2 > 0.0) {
-        geo.rinv = __builtin_amdgcn_rsq(s2);
-        geo.rinv = geo.rinv * (1.5 - 0.5 * s2 * geo.rinv * geo.rinv);
-        geo.s = s2 * geo.rinv;
-      }
-    }
-    const double rc = lane_f64(m_rc, k);
-    rad.c = rad.e = dbl4{0.0, 0.0, 0.0, 0.0};
-    rad.dd = 0.0;
-    if (live && geo.s2 < rc * rc) {
-      const int j = radial_interval(geo.s, __builtin_amdgcn_readlane(m_nint, k), lane_f64(m_k1, k), lane_f64(m_k2, k),
-                                    rad.dd);
-      rad.c = *reinterpret_cast<const dbl4 *>(d.coef + lane_i64(m_coef, k) + 4 * (int64_t)j);
-      if (KIND == PK_HS) rad.e = *reinterpret_cast<const dbl4 *>(d.ucoef + lane_i64(m_u, k) + 4 * (int64_t)j);
-    }
-  };
-  if (rn > r0) fetch(0);
-  for (int i = i_first; i < rn;) {  // the shells (wave-uniform)
-    const int ls = __builtin_amdgcn_readlane(m_l, i > r0 ? i - r0 : 0);
-    const double dx = geo.dx, dy = geo.dy, dz = geo.dz, rinv = geo.rinv, dd = rad.dd;
-    const dbl4 c = rad.c, e = rad.e;
-    if (i + 2 * ls + 1 < rn) fetch(i + 2 * ls + 1 - r0);
-    // Rt and Rt' / s, or (H/S) Rt and u / 2
-    const double R = ((c[3] * dd + c[2]) * dd + c[1]) * dd + c[0];
-    const double q = KIND == PK_HS ? 0.5 * (((e[3] * dd + e[2]) * dd + e[1]) * dd + e[0])
-                                   : ((3.0 * c[3] * dd + 2.0 * c[2]) * dd + c[1]) * rinv;
-    auto shell = [&](auto lc) {
-      constexpr int l = decltype(lc)::value;
-      // an opaque copy: the harmonics of every l would otherwise be hoisted
-      // out of the loop over the shells and held in registers
-      double x = dx, y = dy, z = dz;
-      asm volatile("" : "+v"(x), "+v"(y), "+v"(z));
-      static_for<0, 2 * l + 1>([&](auto mc) {
-        constexpr int m = decltype(mc)::value;
-        double S, gx, gy, gz;
-        solid_harmonic(l * l + m, x, y, z, S, gx, gy, gz);
-        const double f = R * S;
-        if (KIND == PK_HS)
-          put(i + m, f, q * f, 0.0, 0.0);
-        else
-          put(i + m, f, q * x * S + R * gx, q * y * S + R * gy, q * z * S + R * gz);
-      });
-      i += 2 * l + 1;
-    };
-    switch (ls) {
-      case 0: shell(std::integral_constant<int, 0>{}); break;
-      case 1: shell(std::integral_constant<int, 1>{}); break;
-      case 2: shell(std::integral_constant<int, 2>{}); break;
-      case 3: shell(std::integral_constant<int, 3>{}); break;
-      default: shell(std::integral_constant<int, 4>{}); break;
-    }
-  }
+  walk_shells<KIND == PK_HS>(d, fd, r0, rn, px, py, pz, live, put);
   for (int i = rn; i < r1; ++i) put(i, 0.0, 0.0, 0.0, 0.0);
 }
 
@@ -1451,15 +1411,25 @@ static int check_launch(const char *what) {
   return Q4C_OK;
 }
 
+// Waves per 64-function tile: quarter tiles while whole ones would not even give
+// each of the 1024 SIMDs a wave: 256 waves (3 atoms) take 22 us whole and 16 us
+// in quarters, 6100 (17 atoms) 100 and 115 us (a shell cut by a tile's edge is
+// looked up twice).
+static int panel_sub(int64_t waves) { return waves <= 1024 ? 4 : 1; }
+
 int launch_tabulate(const q4c_plan *p, int64_t b0, int64_t b1, int deriv, int dtype, void *out, hipStream_t s) {
   const int64_t t0 = p->batch_tile_off[b0], nt = p->batch_tile_off[b1] - t0;
   if (nt <= 0) return Q4C_OK;
+  int pmax = 0;
+  for (int64_t b = b0; b < b1; ++b) pmax = std::max(pmax, (int)(p->batch_pt_off[b + 1] - p->batch_pt_off[b]));
+  const int npb = (pmax + 63) / 64;
+  const dim3 grid((unsigned)nt, (unsigned)npb);
   {
     TimedLaunch tl_(p, Q4C_TIMER_TABULATE, s);
     if (dtype == Q4C_DTYPE_F32_HILO)
-      hipLaunchKernelGGL(k_tabulate<true>, dim3((unsigned)nt), dim3(256), 0, s, p->dp, p->d_ptile, t0, b0, deriv, out);
+      hipLaunchKernelGGL(k_tabulate<true>, grid, dim3(512), 0, s, p->dp, p->d_ptile, t0, nt, npb, b0, deriv, out);
     else
-      hipLaunchKernelGGL(k_tabulate<false>, dim3((unsigned)nt), dim3(256), 0, s, p->dp, p->d_ptile, t0, b0, deriv, out);
+      hipLaunchKernelGGL(k_tabulate<false>, grid, dim3(512), 0, s, p->dp, p->d_ptile, t0, nt, npb, b0, deriv, out);
   }
   return check_launch("k_tabulate");
 }
@@ -1481,11 +1451,8 @@ template <typename K>
 static void launch_panel(K kernel, const q4c_plan *p, const Pass &ps, double *panel, hipStream_t s) {
   const int64_t nt = ps.t1 - ps.t0;
   const int npb = (ps.p_max + 63) / 64;
-  // quarter tiles while whole ones would not even give each of the 1024 SIMDs a
-  // wave: 256 waves (3 atoms) take 22 us whole and 16 us in quarters, 6100 (17
-  // atoms) 100 and 115 us (a shell cut by a tile's edge is looked up twice)
-  const int sub = nt * npb <= 1024 ? 4 : 1;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)(nt * sub * npb)), dim3(64), 0, s, p->dp, p->d_ptile, ps.t0, nt, sub, npb,
+  const int sub = panel_sub(nt * npb);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(nt * sub), (unsigned)npb), dim3(64), 0, s, p->dp, p->d_ptile, ps.t0, nt, sub, npb,
                      panel, (const double *)p->d_om);
 }
 

@@ -1,6 +1,7 @@
 """GPU: the operand panels of every precision where shells cross the edges of
 the tiles that one wave tabulates (64 functions, 16 on small plans) and points
-the edges of its 64 lanes, through H and H/S against the oracle.
+the edges of its 64 lanes, through H and H/S against the oracle; tables of
+values at the same edges.
 
 Bars: the FP64 bar 1e-12 of each value's own scale (the spin-orbit parts with
 the D terms of the six-product form, twice the scale of Ws); the stated bounds
@@ -30,7 +31,7 @@ def workload(ls, P, seed):
 # (points, largest batch): one batch of 65 or 129 points in quarter tiles; 560
 # batches of one point, whole tiles
 @pytest.mark.parametrize("P, p_max", [(65, 1000), (129, 1000), (560, 1)])
-@pytest.mark.parametrize("ls", [[3, 1, 4, 0], [4, 3, 2, 3, 1, 3, 4, 0, 2]], ids=["20", "53"])
+@pytest.mark.parametrize("ls", [[3, 1, 4, 0], [4, 3, 2, 3, 1, 3, 4, 0, 2]], ids=["40", "106"])
 def test_panels_against_oracle(P, p_max, ls):
     if not gpu_available():
         pytest.skip("no GPU")
@@ -62,3 +63,26 @@ def test_panels_against_oracle(P, p_max, ls):
     for k, (a, b) in enumerate(pairs):
         g = hs.cpu().numpy()[:, po[k]:po[k + 1]].reshape(2, nfn[a], nfn[b])
         assert per_point_worst(g, rh[k], sh[k], 1e-300) <= 1e-12
+
+
+@pytest.mark.parametrize("P", [1, 64, 65, 130])
+@pytest.mark.parametrize("ls", [[0], [3, 1, 4, 0], [4, 3, 2, 3, 1, 3, 4, 0, 2]], ids=["2", "40", "106"])
+def test_tabulate_at_tile_edges(P, ls):
+    if not gpu_available():
+        pytest.skip("no GPU")
+    import paper_2608_00773_amd as q
+    import torch
+    wl = workload(ls, P, 7 * P + len(ls))
+    plan = q.Plan(wl, p_max=1000)
+    _, pidx, _, fidx = plan.batches()
+    n = plan.info["n_fn"]
+    assert plan.info["n_batches"] == 1 and len(fidx) == n
+    print("n %d P %d" % (n, P), flush=True)
+    phi, grad, aphi, agrad = oracle.tabulate(wl, wl.x[pidx], wl.y[pidx], wl.z[pidx], with_abs=True)
+    ref = np.concatenate([phi[None], np.moveaxis(grad, 2, 0)])[:, :, fidx]
+    sref = np.concatenate([aphi[None], np.moveaxis(agrad, 2, 0)])[:, :, fidx]
+    for nq in (4, 1):
+        out = torch.full((nq * P * n + 1,), -7.0, dtype=torch.float64, device="cuda")
+        q.nao_tabulate(plan, 0, 1, int(nq == 4), out[:-1])
+        assert float(out[-1]) == -7.0  # nothing past the table
+        assert per_point_worst(out[:-1].cpu().numpy().reshape(nq, P, n), ref[:nq], sref[:nq], 1e-300) <= 1e-12
