@@ -242,8 +242,8 @@ typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ int d_row_f64(int lk, int r) { return lk + 4 * r; }
 __device__ __forceinline__ int d_row_f32(int lk, int r) { return 4 * lk + r; }
 
-// stage_store for the FP64 16 x 16 blocks of one block row rb of a batch (the
-// MFMA's D layout), with 32-bit offsets from the staging of the row's first
+// stage_store for the 16 x 16 blocks of one block row rb of a batch (in the D
+// layout of the FP64 or, F32, the FP32 MFMA), with 32-bit offsets from the staging of the row's first
 // function and no branches: elements that are not stored get an offset past
 // the buffer's end, which drops the store.  Vector instructions take time from
 // the matrix pipe, and the 64-bit addresses of stage_store cost more of them
@@ -254,13 +254,14 @@ struct StageRows {
   uint32_t a[4], b[4];     // bytes: row_off - 5 nfn fnoff (relative), 5 nfn
   int row[4], fo[4], nf[4], slot[4];  // row within its atom, the atom's first function, functions, slot
 };
+template <bool F32 = false>
 __device__ __forceinline__ StageRows stage_rows(const DevPlan &d, int f0, int n, int rb, int lk, double *staging) {
   StageRows s;
   const int64_t base = uniform_i64(d.loc_rowoff[f0 + 16 * rb]);  // the rows' atoms are stored from here on in slot order
   s.rs = __builtin_amdgcn_make_buffer_rsrc((void *)(staging + base), (short)0, (int)0x7ffffff8, 0x00020000);
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int li = 16 * rb + d_row_f64(lk, r), lc = li < n ? li : n - 1;
+    const int li = 16 * rb + (F32 ? d_row_f32(lk, r) : d_row_f64(lk, r)), lc = li < n ? li : n - 1;
     const int64_t v = d.loc_info[f0 + lc];
     const int fo = (int)((v >> 20) & 0xFFFFF), nf = (int)(v >> 40);
     s.slot[r] = li < n ? (int)(v & 0xFFFFF) : 0x7fffffff;
@@ -272,8 +273,8 @@ __device__ __forceinline__ StageRows stage_rows(const DevPlan &d, int f0, int n,
   }
   return s;
 }
-// parts 0 .. NQ - 1 of the block's rows r: val(r, q)
-template <int NQ, typename F>
+// parts Q0 .. Q1 - 1 of the block's rows r: val(r, q)
+template <int Q0, int Q1, typename F>
 __device__ __forceinline__ void stage_block(const StageRows &s, const DevPlan &d, int f0, int n, int rb, int cb, int l16,
                                             F val) {
   constexpr uint32_t kDrop = 0xfffffff0u;
@@ -288,7 +289,7 @@ __device__ __forceinline__ void stage_block(const StageRows &s, const DevPlan &d
     const uint32_t e = drop ? kDrop : s.a[r] + s.b[r] * (uint32_t)fo + 8u * (uint32_t)(s.row[r] * nf + (lj - fo));
     same |= s.slot[r] == slot;
 #pragma unroll
-    for (int q = 0; q < NQ; ++q)
+    for (int q = Q0; q < Q1; ++q)
       __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, val(r, q)), s.rs,
                                             e + q * pq, 0, 0);
   }
@@ -301,7 +302,7 @@ __device__ __forceinline__ void stage_block(const StageRows &s, const DevPlan &d
       const uint32_t pq = drop ? 0u : 8u * (uint32_t)(s.nf[r] * nf);
       const uint32_t e = drop ? kDrop : s.a[r] + s.b[r] * (uint32_t)fo + 8u * (uint32_t)((lj - fo) * nf + s.row[r]);
 #pragma unroll
-      for (int q = 0; q < NQ; ++q)
+      for (int q = Q0; q < Q1; ++q)
         __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, mirror_sign(q) * val(r, q)), s.rs,
                                               e + q * pq, 0, 0);
     }

@@ -121,7 +121,7 @@ __device__ __forceinline__ void forward_item(const DevPlan &d, int f0, int n, in
   const StageRows sr = stage_rows(d, f0, n, rb, lk, staging);
 #pragma unroll
   for (int c = 0; c < NB; ++c)
-    stage_block<5>(sr, d, f0, n, rb, cb + c, l16, [&](int r, int q) {
+    stage_block<0, 5>(sr, d, f0, n, rb, cb + c, l16, [&](int r, int q) {
       const double dx = acc[c][1][r], dy = acc[c][2][r], dz = acc[c][3][r];
       return q == 0   ? acc[c][0][r]
              : q == 1 ? cp * ((dx + dy) + dz)

@@ -99,7 +99,7 @@ __device__ __forceinline__ void hs_item(const DevPlan &d, int f0, int n, int g0,
   const StageRows sr = stage_rows(d, f0, n, rb, lk, staging);
 #pragma unroll
   for (int c = 0; c < NB; ++c)
-    stage_block<2>(sr, d, f0, n, rb, cb + c, l16,
+    stage_block<0, 2>(sr, d, f0, n, rb, cb + c, l16,
                    [&](int r, int q) { return q ? acc[c][1][r] : acc[c][0][r] + acc[c][2][r]; });
 }
 

@@ -539,7 +539,7 @@ __global__ __launch_bounds__(NT, 4) void k_contract_v(
   __shared__ double sa[2 * BUFD], sb[2 * BUFD];
   __shared__ int64_t s_pos;
   int64_t pos = PERSIST ? next_item(tickets, nw, order != nullptr, &s_pos)
-                        : (order ? (int64_t)blockIdx.x : xcd_map(blockIdx.x, nw));
+                        : (order ? (int64_t)blockIdx.x : xcd_map_runs(blockIdx.x, nw, 64));
   while (!PERSIST || pos < nw) {
   const int64_t wi = w0 + (order ? order[w0 + pos] : pos);
   const WorkItem it = work[wi];
@@ -607,26 +607,13 @@ __global__ __launch_bounds__(NT, 4) void k_contract_v(
       }
     }
   }
-  // write the computed blocks to the staged atom-pair blocks (slot data
-  // looked up here: tables loaded into LDS up front compiled to 256 VGPRs
-  // instead of 148 and ran 45% slower)
+  // write the computed blocks to the staged atom-pair blocks
 #pragma unroll
   for (int sl = 0; sl < 4; ++sl) {
-    if (!act[sl]) continue;
-    const int cbk = c0 + bcol[sl];
-    const int lj = cbk + li16;
-    if (lj >= n) continue;
-    const SlotInfo sj = slot_of(d, f0, d.batch_slot_off[b], lj);
-    const int rb = r0 + brow[sl];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      // FP64 MFMA rows lk + 4 r
-      const int li = rb + d_row_f64(lk, r);
-      if (li < n) {
-        const double v = acc[sl][r];
-        stage_store<0, 1>(staging, slot_of(d, f0, d.batch_slot_off[b], li), sj, li, lj, rb < cbk, &v);
-      }
-    }
+    if (!act[sl]) continue;  // wave-uniform
+    const int rb = (r0 + brow[sl]) >> 4;
+    stage_block<0, 1>(stage_rows(d, f0, n, rb, lk, staging), d, f0, n, rb, (c0 + bcol[sl]) >> 4, li16,
+                      [&](int r, int) { return acc[sl][r]; });
   }
   if (!PERSIST) break;
   pos = next_item(tickets, nw, order != nullptr, &s_pos);
@@ -790,12 +777,8 @@ __global__ __launch_bounds__(NT, 2) void k_contract_w(DevPlan d, const WorkItem 
   constexpr int FLUSH = 16;                    // points per FP32 partial sum
   __shared__ __attribute__((aligned(16))) float fa[2 * BUFF], fb[2 * BUFF];
   __shared__ int64_t s_pos;
-  // slot data of the tile's 64 rows and 64 columns for the epilogue, loaded
-  // when the work item starts (slot -1: beyond n)
-  __shared__ int s_fslot[2 * T], s_ffn[2 * T], s_fnf[2 * T];
-  __shared__ int64_t s_frow[2 * T];
   int64_t pos = PERSIST ? next_item(tickets, nw, order != nullptr, &s_pos)
-                        : (order ? (int64_t)blockIdx.x : xcd_map(blockIdx.x, nw));
+                        : (order ? (int64_t)blockIdx.x : xcd_map_runs(blockIdx.x, nw, 64));
   while (!PERSIST || pos < nw) {
   const int64_t wi = w0 + (order ? order[w0 + pos] : pos);
   const WorkItem it = work[wi];
@@ -852,18 +835,6 @@ __global__ __launch_bounds__(NT, 2) void k_contract_w(DevPlan d, const WorkItem 
   load_om(0);
   dma(r0, 0, fa);
   dma(c0, 0, fb);
-  if (tid < 2 * T) {  // visible from the first chunk's barrier on
-    const int lf = tid < T ? r0 + tid : c0 + tid - T;
-    int64_t v = 0, ro = 0;
-    if (lf < n) {
-      v = d.loc_info[f0 + lf];
-      ro = d.loc_rowoff[f0 + lf];
-    }
-    s_fslot[tid] = lf < n ? (int)(v & 0xFFFFF) : -1;
-    s_ffn[tid] = (int)((v >> 20) & 0xFFFFF);
-    s_fnf[tid] = (int)(v >> 40);
-    s_frow[tid] = ro;
-  }
   for (int k0 = 0; k0 < Pp; k0 += CH) {
     const int bo = ((k0 / CH) & 1) * BUFF;
     __builtin_amdgcn_s_waitcnt(0);  // this thread's loads of this chunk have landed
@@ -968,27 +939,10 @@ __global__ __launch_bounds__(NT, 2) void k_contract_w(DevPlan d, const WorkItem 
   const double cp = d.cprime;
 #pragma unroll
   for (int sl = 0; sl < 4; ++sl) {
-    if (!act[sl]) continue;
-    const int cbk = c0 + bcol[sl];
-    const int lj = cbk + li16;
-    if (lj >= n) continue;
-    const int cj = T + bcol[sl] + li16;
-    const SlotInfo sj{s_fslot[cj], s_ffn[cj], s_fnf[cj], s_frow[cj]};
-    const int rb = r0 + brow[sl];
-    const bool upper = rb < cbk;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      // FP32 MFMA rows 4 lk + r
-      const int lf = rb + d_row_f32(lk, r);
-      if (lf < n) {
-        const int ri = lf - r0;
-        const SlotInfo sf{s_fslot[ri], s_ffn[ri], s_fnf[ri], s_frow[ri]};
-        double w[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) w[q] = cp * accw[sl][q][r];
-        stage_store<1, 5>(staging, sf, sj, lf, lj, upper, w);
-      }
-    }
+    if (!act[sl]) continue;  // wave-uniform
+    const int rb = (r0 + brow[sl]) >> 4;
+    stage_block<1, 5>(stage_rows<true>(d, f0, n, rb, lk, staging), d, f0, n, rb, (c0 + bcol[sl]) >> 4, li16,
+                      [&](int r, int q) { return cp * accw[sl][q - 1][r]; });
   }
   if (!PERSIST) break;
   pos = next_item(tickets, nw, order != nullptr, &s_pos);
@@ -1013,6 +967,13 @@ __global__ __launch_bounds__(NT, 2) void k_contract_w(DevPlan d, const WorkItem 
 // negative products in separate FP32 sums (no operand is negated).  Each
 // chunk's FP32 sums start from zero and are added into FP64 running sums
 // (the spin-orbit pair as their FP32 difference).
+//
+// Bound: LDS, 33 KB of operand reads per wave and chunk for 62 MFMAs (1.0 of
+// their 1.4 thousand cycles, the barrier aside): 120 atoms 8.6 ms, the MFMAs
+// alone 2.6.  Results staged in LDS for coalesced stores took 1700 vector
+// instructions per item, 9.2 ms.  Row operands straight to registers, with
+// half of the LDS reads, were no faster at two waves per SIMD (8.6 ms,
+// prefetched, 8.8 not): latency takes over.
 template <bool PERSIST>
 __global__ __launch_bounds__(NT, 2) void k_contract_b3(DevPlan d, const WorkItem *work, const int32_t *order,
                                                        int64_t w0, int64_t nw, const double *om,
@@ -1023,8 +984,7 @@ __global__ __launch_bounds__(NT, 2) void k_contract_b3(DevPlan d, const WorkItem
   constexpr int RD = 8 * DROW;      // doubles of the row phi image: 8 point pairs x 64 functions x 2
   constexpr int CDW = 2 * 32;       // doubles per row of the column phi image
   constexpr int CD = 8 * CDW;
-  // chunk images (double-buffered), reused after the last chunk to stage the
-  // half tile's results for coalesced writes
+  // chunk images (double-buffered)
   constexpr int IMG_BYTES = 2 * 16 * (RBF + CBF) + 2 * 8 * (RD + CD);
   __shared__ __attribute__((aligned(16))) unsigned char smem[IMG_BYTES];
   u32x4(*sr)[RBF] = reinterpret_cast<u32x4(*)[RBF]>(smem);
@@ -1033,12 +993,9 @@ __global__ __launch_bounds__(NT, 2) void k_contract_b3(DevPlan d, const WorkItem
   double(*dc)[CD] = reinterpret_cast<double(*)[CD]>(smem + 2 * 16 * (RBF + CBF) + 2 * 8 * RD);
   __shared__ double som[2][CH];
   __shared__ int64_t s_pos;
-  // slot data of the tile's 64 rows and the half's 32 columns (slot -1: beyond n)
-  __shared__ int s_rslot[T], s_rfn[T], s_rnf[T], s_cslot[T / 2], s_cfn[T / 2], s_cnf[T / 2];
-  __shared__ int64_t s_rrow[T];
   const int64_t npos = 2 * nw;
   int64_t pos = PERSIST ? next_item(tickets, npos, order != nullptr, &s_pos)
-                        : (order ? (int64_t)blockIdx.x : xcd_map(blockIdx.x, npos));
+                        : (order ? (int64_t)blockIdx.x : xcd_map_runs(blockIdx.x, npos, 64));
   while (!PERSIST || pos < npos) {
   const int half = (int)(pos & 1);
   const int64_t wi = w0 + (order ? order[w0 + (pos >> 1)] : (pos >> 1));
@@ -1109,25 +1066,6 @@ __global__ __launch_bounds__(NT, 2) void k_contract_b3(DevPlan d, const WorkItem
   }
   double omr = tid < CH ? om[g0 + tid] : 0.0;  // om holds 16 zeros past its end
   dma(0, 0);
-  if (tid < T + T / 2) {
-    const bool row = tid < T;
-    const int lf = row ? r0 + tid : c0 + tid - T;
-    SlotInfo si{-1, 0, 0, 0};
-    if (lf < n) {
-      const int64_t v = d.loc_info[f0 + lf];
-      si = SlotInfo{(int)(v & 0xFFFFF), (int)((v >> 20) & 0xFFFFF), (int)(v >> 40), row ? d.loc_rowoff[f0 + lf] : 0};
-    }
-    if (row) {
-      s_rslot[tid] = si.slot;
-      s_rfn[tid] = si.fnoff;
-      s_rnf[tid] = si.nfn;
-      s_rrow[tid] = si.row_off;
-    } else {
-      s_cslot[tid - T] = si.slot;
-      s_cfn[tid - T] = si.fnoff;
-      s_cnf[tid - T] = si.nfn;
-    }
-  }
   __builtin_amdgcn_s_waitcnt(0);
   if (tid < CH) som[0][tid] = omr;
   const int slot = lk >> 1, oc = lk & 1;
@@ -1231,47 +1169,17 @@ __global__ __launch_bounds__(NT, 2) void k_contract_b3(DevPlan d, const WorkItem
     __builtin_amdgcn_s_waitcnt(0);  // the next chunk's images and w v have landed
     if (k0 + CH < Pp && tid < CH) som[bi ^ 1][tid] = omr;
   }
-  // the half tile's results go through LDS (parts 0..2, then 3..4; rows of
-  // 33 doubles), then every thread writes whole runs of staged rows: element
-  // (i, j) of the half by thread (i 32 + j) mod 256, the mirrored element of a
-  // strictly upper block of one atom as well
-  const double cp = d.cprime;
-  double *E = reinterpret_cast<double *>(smem);
-  constexpr int ES = 33;
-#pragma unroll
-  for (int round = 0; round < 2; ++round) {
-    const int q0 = round ? 3 : 0, nq = round ? 2 : 3;
-    __syncthreads();  // the images (or the previous round) are consumed
+  // write the computed blocks to the staged atom-pair blocks
+  if (act[0] || act[1]) {
+    const double cp = d.cprime;
+    const int rbk = (r0 + rb) >> 4;
+    const StageRows s8 = stage_rows(d, f0, n, rbk, lk, staging), s4 = stage_rows<true>(d, f0, n, rbk, lk, staging);
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
       if (!act[c]) continue;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int j = 16 * c + l16;
-        if (round == 0) E[(0 * T + rb + d_row_f64(lk, r)) * ES + j] = accv[c][r];
-#pragma unroll
-        for (int q = 1; q < 5; ++q)
-          if (q >= q0 && q < q0 + nq) E[((q - q0) * T + rb + d_row_f32(lk, r)) * ES + j] = cp * accw[c][q - 1][r];
-      }
-    }
-    __syncthreads();
-    for (int e = tid; e < T * (T / 2); e += NT) {
-      const int i = e >> 5, j = e & 31;
-      const int li = r0 + i, lj = c0 + j;
-      if (!block_active(r0 + (i & ~15), c0 + (j & ~15), n) || li >= n || lj >= n) continue;
-      const int si = s_rslot[i], sj = s_cslot[j];
-      if (si > sj) continue;  // lower atom-block triangle: not stored
-      const int nfi = s_rnf[i], nfj = s_cnf[j], fi = s_rfn[i], fj = s_cfn[j];
-      const int64_t blk = s_rrow[i] + 5 * (int64_t)nfi * (fj - fi);
-      const int64_t pq = (int64_t)nfi * nfj;
-      const int64_t el = (int64_t)(li - fi) * nfj + (lj - fj);
-      const bool mirror = si == sj && r0 + (i & ~15) < c0 + (j & ~15);
-      const int64_t em = (int64_t)(lj - fi) * nfj + (li - fj);
-      for (int qq = 0; qq < nq; ++qq) {
-        const double x = E[(qq * T + i) * ES + j];
-        staging[blk + (q0 + qq) * pq + el] = x;
-        if (mirror) staging[blk + (q0 + qq) * pq + em] = mirror_sign(q0 + qq) * x;
-      }
+      const int cbk = (c0 >> 4) + c;
+      stage_block<0, 1>(s8, d, f0, n, rbk, cbk, l16, [&](int r, int) { return accv[c][r]; });
+      stage_block<1, 5>(s4, d, f0, n, rbk, cbk, l16, [&](int r, int q) { return cp * accw[c][q - 1][r]; });
     }
   }
   }  // the half has columns
