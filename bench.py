@@ -37,38 +37,17 @@ PREC = {"f64": 0, "split": 1, "f32": 2, "bf16x3": 3, "f64valu": 4}
 # the timed launches, and per launch shape the autotuner's trial launches of
 # the same runs (persistent sizes 512 and 1024 read the same bytes).  Keyed by
 # kernel, the SHA-256 of the kernel sources the counters were taken on
-# (q4c_kernels.hip and q4c_device.h), the precision, the workload and the
-# launch shape: work order (0: batch order, which keeps a batch's tiles on one
-# L2; 1: the cost-sorted queue, which does not) and whether the launch is
-# persistent (None for kernels without either).  Any change to those sources
-# makes the figure unknown, and it is then reported as null.
-_KS = "3988041ce98d2cefbd3169767ac3a161f0c36e4d4c5bb94ed602b3de360c368c"
-TRAFFIC = {
-    ("k_contract", _KS, "f64", "cluster-120", (0, False)): 21.63e9 + 7.44e9,
-    ("k_contract", _KS, "f64", "cluster-120", (0, True)): 23.25e9 + 7.64e9,
-    ("k_contract", _KS, "f64", "cluster-120", (1, False)): 42.81e9 + 7.65e9,
-    ("k_contract", _KS, "f64", "cluster-120", (1, True)): 39.92e9 + 7.96e9,
-    ("k_density_tiles", _KS, "f64", "cluster-120", (0, False)): 19.97e9 + 0.21e9,
-    ("k_density_tiles", _KS, "f64", "cluster-120", (0, True)): 21.51e9 + 0.21e9,
-    ("k_density_tiles", _KS, "f64", "cluster-120", (1, False)): 70.18e9 + 0.21e9,
-    ("k_density_tiles", _KS, "f64", "cluster-120", (1, True)): 67.96e9 + 0.21e9,
-    ("k_panel", _KS, "f64", "cluster-120", None): 0.17e9 + 11.49e9,
-    ("k_reduce", _KS, "f64", "cluster-120", None): 7.41e9 + 0.03e9,
-    ("k_contract", _KS, "bf16x3", "cluster-120", (0, False)): 9.44e9 + 6.95e9,
-    ("k_contract", _KS, "bf16x3", "cluster-120", (0, True)): 9.69e9 + 7.15e9,
-    ("k_contract", _KS, "bf16x3", "cluster-120", (1, False)): 52.62e9 + 7.84e9,
-    ("k_contract", _KS, "bf16x3", "cluster-120", (1, True)): 47.97e9 + 7.79e9,
-    ("k_panel", _KS, "bf16x3", "cluster-120", None): 0.16e9 + 9.34e9,
-    ("k_reduce", _KS, "bf16x3", "cluster-120", None): 7.41e9 + 0.03e9,
-}
-
+# (KERNEL_SOURCES), the precision, the workload and the launch shape: work order
+# (0: batch order, which keeps a batch's blocks on one L2; 1: the cost-sorted
+# queue, which does not) and whether the launch is persistent (None for kernels
+# without either).  Any change to those sources makes a figure unknown: it is
+# then reported as null, as it is for the present sources, whose counters have
+# not been taken.
+KERNEL_SOURCES = ("q4c_kernels.hip", "q4c_forward_kernels.hip", "q4c_density_kernels.hip", "q4c_device.h")
+TRAFFIC = {}
 # The same for k_contract_hs (q4c_integrate_HS) per component and launch shape,
 # keyed by the SHA-256 of q4c_hs_kernels.hip and q4c_device.h.
-_HS = "07c101f6ce1cacc7d5df8cc7267adc142c8576d56c73f0659b9e0b7c9665fe60"
-HS_TRAFFIC = {
-    (_HS, "large", 120, (0, True)): 6.854e9 + 2.994e9,
-    (_HS, "small", 120, (0, True)): 7.143e9 + 7.043e9,
-}
+HS_TRAFFIC = {}
 
 
 def source_sha(*names):
@@ -584,7 +563,7 @@ def main():
     plan.profile(False)
     info = plan.info
     n_act = info["n_active"]
-    ksha = source_sha("q4c_kernels.hip", "q4c_device.h")
+    ksha = source_sha(*KERNEL_SOURCES)
     c_launch = plan.get_launch(q.KERNEL_CONTRACT)
     d_launch = plan.get_launch(q.KERNEL_DENSITY)
     c_shape = (c_launch[0], c_launch[1] > 0)  # work order, persistent
@@ -604,10 +583,15 @@ def main():
                 "alg_per_launch": work, "avg_launch_ms": t * 1e3, "launches_per_step": per_step,
                 "ms_per_step": tim[timer][0] / a.steps}
 
+    # the kernel of the W parts (split and f32 time V's k_contract_v with it)
+    fwd_kernel = {"f64": "k_forward", "f64valu": "k_contract_valu", "bf16x3": "k_contract_b3"}.get(
+        a.precision, "k_contract_w")
     rl = [
-        kernel_roofline("k_contract", "contract", "mfma", info["flops_alg"], contraction_peak(a.precision),
-                        "TFLOP/s", c_shape),
-        kernel_roofline("k_density_tiles", "density_tiles", "mfma", info["flops_alg"], PEAK_F64, "TFLOP/s",
+        # the FP64 kernels form the ten products of flops_alg from seven: the work
+        # is those seven, so that frac is a fraction of what the matrix cores do
+        kernel_roofline(fwd_kernel, "contract", "mfma", info["flops_alg"] * (0.7 if a.precision == "f64" else 1.0),
+                        contraction_peak(a.precision), "TFLOP/s", c_shape),
+        kernel_roofline("k_density_items", "density_tiles", "mfma", 0.7 * info["flops_alg"], PEAK_F64, "TFLOP/s",
                         d_shape),
         # tabulation: 32 B (phi and its gradient, FP64) per (point, relevant function) per
         # tabulation of all passes; the adjoint tabulates only passes whose panels are not resident

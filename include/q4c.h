@@ -501,12 +501,13 @@ int q4c_plan_profile(q4c_plan *plan, int enable);
 
 int q4c_plan_timers(q4c_plan *plan, double *ms, int64_t *launches);
 
-/* Launch shape of the contraction kernels (k_contract of q4c_integrate_H,
- * k_density_tiles of density_on_grid, k_contract_hs of q4c_integrate_HS), per
- * plan (the autotuner covers the first two):
+/* Launch shape of the contraction kernels (k_forward and k_contract_* of
+ * q4c_integrate_H, k_density_items of density_on_grid, k_contract_hs of
+ * q4c_integrate_HS), per plan (the autotuner covers the first two):
  *   order      0: work items in batch order, consecutive items on one XCD;
  *              1: largest items first (estimated cost), longest-first scheduling;
- *   persistent 0: one workgroup per work item;
+ *   persistent 0: one workgroup per work item (four items of the FP64 forward
+ *              and H/S kernels);
  *              k > 0: k workgroups loop over the items, taking them from
  *              ticket queues (one per XCD with stealing for order 0, one global
  *              queue for order 1).
