@@ -102,17 +102,6 @@ __device__ __forceinline__ int64_t ticket_pos(unsigned *tickets, int64_t nw, boo
   return nw;
 }
 
-// lane exchange within rows of 16 lanes by DPP (no LDS traffic): lane i reads
-// lane 15 - i (row mirror), 8 (i / 8) + 7 - i % 8 (half-row mirror), i ^ 2 or
-// i ^ 1 (quad permutes); a double moves as its two 32-bit halves
-constexpr int DPP_QUAD_XOR1 = 0xB1, DPP_QUAD_XOR2 = 0x4E, DPP_ROW_MIRROR = 0x140, DPP_ROW_HALF_MIRROR = 0x141;
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, false);
-  return __hiloint2double(hi, lo);
-}
-
 __device__ __forceinline__ dbl4 mfma64(double a, double b, dbl4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
@@ -138,15 +127,6 @@ struct SlotInfo {
   int slot, fnoff, nfn;
   int64_t row_off;
 };
-
-__device__ __forceinline__ SlotInfo slot_of(const DevPlan &d, int fbase, int sbase, int lf) {
-  SlotInfo s;
-  s.slot = d.loc_slot[fbase + lf];
-  s.fnoff = d.slot_fnoff[sbase + s.slot];
-  s.nfn = d.slot_nfn[sbase + s.slot];
-  s.row_off = d.slot_row_off[sbase + s.slot];
-  return s;
-}
 
 // A value every lane holds alike, as a scalar (wave-uniform) one.
 __device__ __forceinline__ int64_t uniform_i64(int64_t v) {
@@ -309,23 +289,6 @@ __device__ __forceinline__ void stage_block(const StageRows &s, const DevPlan &d
   }
 }
 
-// As stage_store, adding to the staged element (and its mirror) instead.
-template <int Q0, int Q1>
-__device__ __forceinline__ void stage_add(double *staging, const SlotInfo &si, const SlotInfo &sj, int li, int lj,
-                                          bool upper, const double *v) {
-  if (si.slot > sj.slot) return;
-  const int64_t blk = si.row_off + 5 * (int64_t)si.nfn * (sj.fnoff - si.fnoff);
-  const int64_t pq = (int64_t)si.nfn * sj.nfn;
-  const int64_t e = (int64_t)(li - si.fnoff) * sj.nfn + (lj - sj.fnoff);
-#pragma unroll
-  for (int q = Q0; q < Q1; ++q) staging[blk + q * pq + e] += v[q - Q0];
-  if (upper && si.slot == sj.slot) {
-    const int64_t em = (int64_t)(lj - si.fnoff) * sj.nfn + (li - sj.fnoff);
-#pragma unroll
-    for (int q = Q0; q < Q1; ++q) staging[blk + q * pq + em] += mirror_sign(q) * v[q - Q0];
-  }
-}
-
 // LDS image of one 16-point chunk of a 64-function tile, in the panel's own
 // order: row (q, u) holds component q at points 2u and 2u+1 of the chunk,
 // the two points of function f as consecutive doubles, so element (q, pt, f)
@@ -335,23 +298,6 @@ __device__ __forceinline__ void stage_add(double *staging, const SlotInfo &si, c
 // once.
 constexpr int DROW = 2 * T;  // doubles per LDS row
 typedef __attribute__((address_space(3))) void lds_void;
-
-// Workgroup barrier after this wave's LDS operations have completed and at
-// most VM of its vector-memory operations remain outstanding (s_waitcnt
-// vmcnt(VM) lgkmcnt(0)).  The LDS DMA loads count in vmcnt.  __syncthreads
-// would also fence global memory; the memory clobber keeps the compiler from
-// moving memory accesses across the barrier.
-template <int VM>
-__device__ __forceinline__ void barrier_vm() {
-  static_assert(VM >= 0 && VM < 64, "vmcnt field");
-  __builtin_amdgcn_s_waitcnt((VM & 15) | ((VM >> 4) << 14) | (0x7 << 4));
-  asm volatile("s_barrier" ::: "memory");
-}
-
-// LDS byte address of a __shared__ array element
-__device__ __forceinline__ uint32_t lds_addr(const double *p) {
-  return (uint32_t)(uintptr_t)(const lds_void *)(const void *)p;
-}
 
 // Calls f(std::integral_constant<int, K>) for K = K0, K0 + S, ... < K1, as
 // straight-line code with K a constant expression in f.
