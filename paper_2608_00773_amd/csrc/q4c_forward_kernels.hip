@@ -57,13 +57,15 @@ __device__ __forceinline__ void forward_item(const DevPlan &d, int f0, int n, in
   off[0] = ((uint32_t)(lk >> 1) * np + 16 * rb + l16) * 32u + 16u * (lk & 1);
 #pragma unroll
   for (int c = 0; c < NB; ++c) off[1 + c] = ((uint32_t)(lk >> 1) * np + 16 * (cb + c) + l16) * 32u + 16u * (lk & 1);
-  // w v of the batch's points; reads past them give 0
-  const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc((void *)(om + g0), (short)0, P * 8, 0x00020000);
   // past the last point an empty buffer: nothing is read, and no branch makes
   // the waits of the next K pairs count for both of its sides (with one, every
   // other K pair waited for loads just issued: 9.52 instead of 9.15 ms)
   auto load = [&](int k, Operand (&o)[1 + NB], dbl2 &w) {
     const int nr = k < Pp ? np * 64 : 0;
+    // w v from point k on; past the batch's points 0: the buffer ends there and
+    // the lanes' offsets alone are checked against it (no scalar offset)
+    const __amdgpu_buffer_rsrc_t ro =
+        __builtin_amdgcn_make_buffer_rsrc((void *)(om + g0 + k), (short)0, k < P ? (P - k) * 8 : 0, 0x00020000);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       // the K pair's two point quads of component q: a wave-uniform base, so
@@ -76,7 +78,7 @@ __device__ __forceinline__ void forward_item(const DevPlan &d, int f0, int n, in
     }
 #pragma unroll
     for (int h = 0; h < 2; ++h)
-      w[h] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(ro, 16 * lk + 8 * h, 8 * k, 0));
+      w[h] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(ro, 16 * lk + 8 * h, 0, 0));
   };
   dbl4 acc[NB][7];
 #pragma unroll

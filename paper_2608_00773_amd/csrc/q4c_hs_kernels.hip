@@ -42,13 +42,16 @@ __device__ __forceinline__ void hs_item(const DevPlan &d, int f0, int n, int g0,
   off[0] = ((uint32_t)(lk >> 1) * np + 16 * rb + l16) * 32u + 16u * (lk & 1);
 #pragma unroll
   for (int c = 0; c < NB; ++c) off[1 + c] = ((uint32_t)(lk >> 1) * np + 16 * (cb + c) + l16) * 32u + 16u * (lk & 1);
-  // w v and w of the batch's points; reads past them give 0
-  const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc((void *)(om + g0), (short)0, P * 8, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void *)(d.pw + g0), (short)0, P * 8, 0x00020000);
   // past the last point an empty buffer: nothing is read, and no branch makes
   // the waits of the next K pairs count for both of its sides
   auto load = [&](int k, OperandHS (&o)[1 + NB], dbl2 &wv, dbl2 &w) {
     const int nr = k < Pp ? np * 64 : 0;
+    // w v and w from point k on, 0 past the batch's points (as in k_forward)
+    const int nw = k < P ? (P - k) * 8 : 0;
+    const __amdgpu_buffer_rsrc_t ro =
+        __builtin_amdgcn_make_buffer_rsrc((void *)(om + g0 + k), (short)0, nw, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rw =
+        __builtin_amdgcn_make_buffer_rsrc((void *)(d.pw + g0 + k), (short)0, nw, 0x00020000);
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
@@ -59,8 +62,8 @@ __device__ __forceinline__ void hs_item(const DevPlan &d, int f0, int n, int g0,
     }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      wv[h] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(ro, 16 * lk + 8 * h, 8 * k, 0));
-      w[h] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rw, 16 * lk + 8 * h, 8 * k, 0));
+      wv[h] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(ro, 16 * lk + 8 * h, 0, 0));
+      w[h] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rw, 16 * lk + 8 * h, 0, 0));
     }
   };
   dbl4 acc[NB][3];  // H (w v phi + w psi, phi), S, H (w phi, psi)

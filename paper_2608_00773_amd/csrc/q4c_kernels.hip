@@ -660,7 +660,7 @@ __global__ __launch_bounds__(NT, 1) void k_contract_valu(DevPlan d, const WorkIt
     for (int a = 0; a < 4; ++a)
 #pragma unroll
       for (int c = 0; c < 4; ++c) acc[q][a][c] = 0.0;
-  double omr = tid < CH ? om[g0 + tid] : 0.0;  // om holds 16 zeros past its end
+  double omr = tid < CH && tid < P ? om[g0 + tid] : 0.0;  // 0 past the batch's points
   dma_chunk<NT, CH, T, DROW, NQ>(pb, plane, np, r0, 0, sa);
   dma_chunk<NT, CH, T, DROW, NQ>(pb, plane, np, c0, 0, sb);
   if (tid < 2 * T) {  // visible from the first chunk's barrier on
@@ -681,7 +681,7 @@ __global__ __launch_bounds__(NT, 1) void k_contract_valu(DevPlan d, const WorkIt
     const int bi = (k0 / CH) & 1;
     __syncthreads();  // this chunk visible; the previous one consumed
     if (k0 + CH < Pp) {
-      omr = tid < CH ? om[g0 + k0 + CH + tid] : 0.0;
+      omr = tid < CH && k0 + CH + tid < P ? om[g0 + k0 + CH + tid] : 0.0;
       dma_chunk<NT, CH, T, DROW, NQ>(pb, plane, np, r0, (k0 + CH) >> 2, sa + (bi ^ 1) * BUFD);
       dma_chunk<NT, CH, T, DROW, NQ>(pb, plane, np, c0, (k0 + CH) >> 2, sb + (bi ^ 1) * BUFD);
     }
@@ -1064,7 +1064,7 @@ __global__ __launch_bounds__(NT, 2) void k_contract_b3(DevPlan d, const WorkItem
     for (int q = 0; q < 4; ++q) accw[c][q] = dbl4{0.0, 0.0, 0.0, 0.0};
     accv[c] = dbl4{0.0, 0.0, 0.0, 0.0};
   }
-  double omr = tid < CH ? om[g0 + tid] : 0.0;  // om holds 16 zeros past its end
+  double omr = tid < CH && tid < P ? om[g0 + tid] : 0.0;  // 0 past the batch's points
   dma(0, 0);
   __builtin_amdgcn_s_waitcnt(0);
   if (tid < CH) som[0][tid] = omr;
@@ -1076,7 +1076,7 @@ __global__ __launch_bounds__(NT, 2) void k_contract_b3(DevPlan d, const WorkItem
     const int bi = (k0 / CH) & 1;
     __syncthreads();  // this chunk's images and w v visible; the previous chunk is consumed
     if (k0 + CH < Pp) {
-      omr = tid < CH ? om[g0 + k0 + CH + tid] : 0.0;
+      omr = tid < CH && k0 + CH + tid < P ? om[g0 + k0 + CH + tid] : 0.0;
       dma(k0 + CH, bi ^ 1);
     }
     // the chunk's products for the active column blocks (a compile-time set:
