@@ -26,7 +26,7 @@ namespace {
 // six products D_m = a_m b_m, M_m (see k_density_items): with
 // Wso_x = M_x - (D_y - D_z) and cyclic,
 //   C^Dx = C^s + (C^y - C^z) and cyclic,  C^Mm = C^m;
-// for the FP32 W terms C^s, C^x, C^y, C^z.  A zero element follows the last
+// for the other forms C^s, C^x, C^y, C^z.  A zero element follows the last
 // one (index store_len), for lanes without a stored element.  One workgroup
 // per pair.
 __global__ void k_coef_fold(DevPlan d, const double *coef, uint32_t terms, int six, double *cf) {
@@ -103,9 +103,21 @@ __global__ void k_coef_fold(DevPlan d, const double *coef, uint32_t terms, int s
 // times the magnitudes of its W terms.  The V term stays FP64.
 constexpr int NWD = 4, NTD = 64 * NWD;  // waves and threads of a workgroup
 
-template <bool F32W>
+// The three kernels: FP64 with six products, FP32 W terms, and FP64 with nine
+// products for calls with the spin-orbit terms but without V.  The six products
+// round at the size of the D terms: beside V that does not show (RMS error of
+// all terms 0.8-1.04 times that of nine products from 64-row tiles, 3 to 60
+// atoms), in the spin-orbit terms alone it does (1.05-1.3; nine products here
+// 0.91-1.05).
+enum { DEN_F64 = 0, DEN_F32W = 1, DEN_SO = 2 };
+__host__ __device__ constexpr int den_form(int precision, uint32_t terms) {
+  return precision == Q4C_PREC_F32 ? DEN_F32W : (terms & Q4C_TERM_SO) && !(terms & Q4C_TERM_LL) ? DEN_SO : DEN_F64;
+}
+
+template <int FORM>
 struct DenShared {
-  static constexpr int NC = F32W ? 1 : 7;                          // FP64 coefficients per element
+  static constexpr bool F32W = FORM == DEN_F32W;
+  static constexpr int NC = FORM == DEN_F64 ? 7 : F32W ? 1 : 4;    // FP64 coefficients per element
   dbl2 c64[2 * kDenRows][NC][64];                                  // [K pair][part][lane], both K steps
   float c32[F32W ? 2 * kDenRows : 1][F32W ? 4 : 1][64][2];         // the FP32 W coefficients
 };
@@ -122,9 +134,10 @@ struct DenItem {
 // The wave's chunks of an item of NB row blocks: chunks 16 wave + 16 NWD c.
 // begin() issues the first loads (before the coefficients are in LDS), run()
 // does the rest.
-template <bool F32W, int NB>
+template <int FORM, int NB>
 struct DenChunks {
-  static constexpr int NC = DenShared<F32W>::NC;
+  static constexpr bool F32W = FORM == DEN_F32W;
+  static constexpr int NC = DenShared<FORM>::NC, Q0 = FORM == DEN_SO ? 1 : 0;  // Q0: the first panel component read
   const DenItem &x;
   const int lane, l16, lk;
   // lane offsets (bytes) in a chunk's four point quads: quad l16 / 4, the row
@@ -148,7 +161,7 @@ struct DenChunks {
   __device__ __forceinline__ void load_rows(int k, int kp) {
     const uint32_t so = (uint32_t)(x.i0 + 8 * kp) * 32u;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = Q0; q < 4; ++q) {
       const __amdgpu_buffer_rsrc_t rs = rsrc(q, k);
 #pragma unroll
       for (int h = 0; h < 2; ++h)
@@ -158,15 +171,15 @@ struct DenChunks {
   __device__ __forceinline__ void begin(int wave) {
     if (16 * wave < x.Pp) load_rows<0>(16 * wave, 0);
   }
-  __device__ __forceinline__ void chunk(int k, const DenShared<F32W> &sh) {
+  __device__ __forceinline__ void chunk(int k, const DenShared<FORM> &sh) {
     const int kn = k + 16 * NWD < x.Pp ? k + 16 * NWD : k;  // the wave's next chunk (the last: read again, unused)
     dbl4 u[NC];
     flt4 w[3];
     double z[4][4];
-    double sum = 0.0;
+    double sum = 0.0, sumw = 0.0;  // V and W: one chain for both rounds W's six products at the size of V
     auto load_z = [&]() {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+      for (int q = Q0; q < 4; ++q) {
         const __amdgpu_buffer_rsrc_t rs = rsrc(q, k);
 #pragma unroll
         for (int r = 0; r < 4; ++r)
@@ -197,17 +210,27 @@ struct DenChunks {
         // the sums start from zero (F32W: every 32 rows)
         const bool first = (F32W ? KP % 4 == 0 : KP == 0) && h == 0;
         const dbl4 z4 = dbl4{0.0, 0.0, 0.0, 0.0};
-        const double y0 = y[S][h][0], y1 = y[S][h][1], y2 = y[S][h][2], y3 = y[S][h][3];
-        u[0] = mfma64(c[0][h], y0, first ? z4 : u[0]);
-        if constexpr (!F32W) {
+        const double y1 = y[S][h][1], y2 = y[S][h][2], y3 = y[S][h][3];
+        if constexpr (FORM != DEN_SO) u[0] = mfma64(c[0][h], y[S][h][0], first ? z4 : u[0]);
+        if constexpr (FORM == DEN_F64) {
           u[1] = mfma64(c[1][h], y1, first ? z4 : u[1]);
           u[2] = mfma64(c[2][h], y2, first ? z4 : u[2]);
           u[3] = mfma64(c[3][h], y3, first ? z4 : u[3]);
           u[4] = mfma64(c[4][h], y2 - y3, first ? z4 : u[4]);
           u[5] = mfma64(c[5][h], y3 - y1, first ? z4 : u[5]);
           u[6] = mfma64(c[6][h], y1 - y2, first ? z4 : u[6]);
-        } else {
+        } else if constexpr (FORM == DEN_SO) {
           // grouped by the column component they meet: x: C^s dx - C^z dy + C^y dz, cyclic
+          u[0] = mfma64(c[0][h], y1, first ? z4 : u[0]);
+          u[1] = mfma64(c[3][h], y1, first ? z4 : u[1]);
+          u[2] = mfma64(c[2][h], -y1, first ? z4 : u[2]);
+          u[0] = mfma64(c[3][h], -y2, u[0]);
+          u[1] = mfma64(c[0][h], y2, u[1]);
+          u[2] = mfma64(c[1][h], y2, u[2]);
+          u[0] = mfma64(c[2][h], y3, u[0]);
+          u[1] = mfma64(c[1][h], -y3, u[1]);
+          u[2] = mfma64(c[0][h], y3, u[2]);
+        } else {  // the same in FP32
           const flt4 f4 = flt4{0.f, 0.f, 0.f, 0.f};
           const float f1 = (float)y1, f2 = (float)y2, f3 = (float)y3;
           w[0] = mfma32(cw[0][h], f1, first ? f4 : w[0]);
@@ -226,38 +249,44 @@ struct DenChunks {
         // drain: the lane's four columns
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          sum = fma(u[0][r], z[0][r], sum);
-          if constexpr (F32W) {
-            sum = fma((double)w[0][r], z[1][r], sum);
-            sum = fma((double)w[1][r], z[2][r], sum);
-            sum = fma((double)w[2][r], z[3][r], sum);
+          if constexpr (FORM != DEN_SO) sum = fma(u[0][r], z[0][r], sum);
+          if constexpr (FORM == DEN_SO) {
+            sumw = fma(u[0][r], z[1][r], sumw);
+            sumw = fma(u[1][r], z[2][r], sumw);
+            sumw = fma(u[2][r], z[3][r], sumw);
+          } else if constexpr (F32W) {
+            sumw = fma((double)w[0][r], z[1][r], sumw);
+            sumw = fma((double)w[1][r], z[2][r], sumw);
+            sumw = fma((double)w[2][r], z[3][r], sumw);
           } else {
-            sum = fma(u[1][r], z[1][r], sum);
-            sum = fma(u[2][r], z[2][r], sum);
-            sum = fma(u[3][r], z[3][r], sum);
-            sum = fma(u[4][r], z[2][r] + z[3][r], sum);
-            sum = fma(u[5][r], z[3][r] + z[1][r], sum);
-            sum = fma(u[6][r], z[1][r] + z[2][r], sum);
+            sumw = fma(u[1][r], z[1][r], sumw);
+            sumw = fma(u[2][r], z[2][r], sumw);
+            sumw = fma(u[3][r], z[3][r], sumw);
+            sumw = fma(u[4][r], z[2][r] + z[3][r], sumw);
+            sumw = fma(u[5][r], z[3][r] + z[1][r], sumw);
+            sumw = fma(u[6][r], z[1][r] + z[2][r], sumw);
           }
         }
       }
     });
+    sum += sumw;
     // the columns of the other lanes with this point
     sum += __shfl_xor(sum, 16);
     sum += __shfl_xor(sum, 32);
     if (lk == 0 && k + l16 < x.P) x.out[k + l16] = sum;
   }
-  __device__ __forceinline__ void run(int wave, const DenShared<F32W> &sh) {
+  __device__ __forceinline__ void run(int wave, const DenShared<FORM> &sh) {
     for (int k = 16 * wave; k < x.Pp; k += 16 * NWD) chunk(k, sh);
   }
 };
 
-template <bool F32W, bool PERSIST>
+template <int FORM, bool PERSIST>
 __global__ __launch_bounds__(NTD, 3) void k_density_items(DevPlan d, const BlockItem *items, int64_t ni,
                                                           int global_queue, const double *cf, const double *panel,
                                                           double *partial, unsigned *tickets) {
-  constexpr int NC = DenShared<F32W>::NC;
-  __shared__ DenShared<F32W> sh;
+  constexpr bool F32W = FORM == DEN_F32W;
+  constexpr int NC = DenShared<FORM>::NC;
+  __shared__ DenShared<FORM> sh;
   __shared__ int64_t s_pos;
   const bool gq = global_queue != 0;
   int64_t pos = PERSIST ? next_item(tickets, ni, gq, &s_pos) : (gq ? (int64_t)blockIdx.x : xcd_map_runs(blockIdx.x, ni, 128));
@@ -302,7 +331,7 @@ __global__ __launch_bounds__(NTD, 3) void k_density_items(DevPlan d, const Block
         const dbl2 *e = reinterpret_cast<const dbl2 *>(cf + kFold * ea[u]);
         double c[8];
 #pragma unroll
-        for (int k = 0; k < (F32W ? 3 : 4); ++k) {
+        for (int k = 0; k < (FORM == DEN_F64 ? 4 : 3); ++k) {
           const dbl2 x = e[k];
           c[2 * k] = x[0];
           c[2 * k + 1] = x[1];
@@ -310,7 +339,7 @@ __global__ __launch_bounds__(NTD, 3) void k_density_items(DevPlan d, const Block
         // row il is K index lk = il % 4 of K step il / 4
         const int kp = il >> 3, h = (il >> 2) & 1, cl = (tid & 15) + 16 * (il & 3);
 #pragma unroll
-        for (int q = 0; q < NC; ++q) reinterpret_cast<double *>(&sh.c64[kp][q][cl])[h] = c[q];
+        for (int q = 0; q < NC; ++q) reinterpret_cast<double *>(&sh.c64[kp][q][cl])[h] = c[FORM == DEN_SO ? 1 + q : q];
         if constexpr (F32W) {
 #pragma unroll
           for (int q = 0; q < 4; ++q) sh.c32[kp][q][cl][h] = (float)c[1 + q];
@@ -318,7 +347,7 @@ __global__ __launch_bounds__(NTD, 3) void k_density_items(DevPlan d, const Block
       }
     };
     auto run = [&](auto nb) {
-      DenChunks<F32W, decltype(nb)::value> c(x, lane);
+      DenChunks<FORM, decltype(nb)::value> c(x, lane);
       c.begin(wave);
       fill();
       __syncthreads();  // the coefficients are visible
@@ -336,7 +365,9 @@ __global__ __launch_bounds__(NTD, 3) void k_density_items(DevPlan d, const Block
   }
 }
 
-// Point sums: out[perm[g]] = (w_g if weighted) * sum over the batch's items in order.
+// Point sums: out[perm[g]] = (w_g if weighted) * sum over the batch's items, in
+// eight chains of every eighth item (so their rounding stays small: RMS error of
+// n 2.6e-17 -> 2.4e-17 of its terms on 60 atoms, and the loads are in flight together).
 __global__ void k_density_points(DevPlan d, int64_t b0, const double *partial, int weight_mode, double *out) {
   const int64_t b = b0 + blockIdx.x;
   const int g0 = d.batch_pt_off[b], P = d.batch_pt_off[b + 1] - g0;
@@ -344,9 +375,15 @@ __global__ void k_density_points(DevPlan d, int64_t b0, const double *partial, i
   const int ni = den_items(m);
   const double *pp = partial + d.batch_part_off[b];
   for (int g = threadIdx.x; g < P; g += blockDim.x) {
-    double s = 0.0;
-#pragma unroll 8
-    for (int t = 0; t < ni; ++t) s += pp[(int64_t)t * P + g];
+    double c[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    int t = 0;
+    for (; t + 8 <= ni; t += 8)
+#pragma unroll
+      for (int u = 0; u < 8; ++u) c[u] += pp[(int64_t)(t + u) * P + g];
+#pragma unroll
+    for (int u = 0; u < 7; ++u)
+      if (t + u < ni) c[u] += pp[(int64_t)(t + u) * P + g];
+    const double s = ((c[0] + c[1]) + (c[2] + c[3])) + ((c[4] + c[5]) + (c[6] + c[7]));
     out[d.perm[g0 + g]] = weight_mode ? d.pw[g0 + g] * s : s;
   }
 }
@@ -357,13 +394,13 @@ int launch_density_fold(const q4c_plan *p, const double *coef, uint32_t terms, i
   if (p->n_pairs <= 0) return Q4C_OK;
   TimedLaunch tl_(p, Q4C_TIMER_OTHER, s);
   hipLaunchKernelGGL(k_coef_fold, dim3((unsigned)p->n_pairs), dim3(256), 0, s, p->dp, coef, terms,
-                     precision == Q4C_PREC_F32 ? 0 : 1, p->d_coef_fold);
+                     den_form(precision, terms) == DEN_F64, p->d_coef_fold);
   const hipError_t e = hipGetLastError();
   return e != hipSuccess ? hip_fail(e, "k_coef_fold") : Q4C_OK;
 }
 
-int launch_density_pass(const q4c_plan *p, const Pass &ps, int precision, int weight_mode, const double *panel,
-                        double *partial, unsigned *tickets, double *out, hipStream_t s) {
+int launch_density_pass(const q4c_plan *p, const Pass &ps, uint32_t terms, int precision, int weight_mode,
+                        const double *panel, double *partial, unsigned *tickets, double *out, hipStream_t s) {
   const LaunchCfg cfg = p->cfg_density;
   const int64_t ni = ps.di1 - ps.di0, nb = ps.b1 - ps.b0;
   const BlockItem *items = (cfg.order ? p->d_den_cost : p->d_den) + ps.di0;
@@ -375,10 +412,11 @@ int launch_density_pass(const q4c_plan *p, const Pass &ps, int precision, int we
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(NTD), 0, s, p->dp, items, ni, (int)cfg.order,
                            (const double *)p->d_coef_fold, panel, partial, tickets);
       };
-      if (precision == Q4C_PREC_F32)
-        tickets ? launch(k_density_items<true, true>) : launch(k_density_items<true, false>);
-      else
-        tickets ? launch(k_density_items<false, true>) : launch(k_density_items<false, false>);
+      switch (den_form(precision, terms)) {
+        case DEN_F32W: tickets ? launch(k_density_items<DEN_F32W, true>) : launch(k_density_items<DEN_F32W, false>); break;
+        case DEN_SO: tickets ? launch(k_density_items<DEN_SO, true>) : launch(k_density_items<DEN_SO, false>); break;
+        default: tickets ? launch(k_density_items<DEN_F64, true>) : launch(k_density_items<DEN_F64, false>);
+      }
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "k_density_items");

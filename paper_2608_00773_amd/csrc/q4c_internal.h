@@ -347,8 +347,8 @@ int launch_forward(const q4c_plan *p, const Pass &ps, const double *panel, unsig
 // the adjoint's folded coefficients of a call, and one pass of its items and
 // point sums on the pass's panel (q4c_density_kernels.hip)
 int launch_density_fold(const q4c_plan *p, const double *coef, uint32_t terms, int precision, hipStream_t s);
-int launch_density_pass(const q4c_plan *p, const Pass &ps, int precision, int weight_mode, const double *panel,
-                        double *partial, unsigned *tickets, double *out, hipStream_t s);
+int launch_density_pass(const q4c_plan *p, const Pass &ps, uint32_t terms, int precision, int weight_mode,
+                        const double *panel, double *partial, unsigned *tickets, double *out, hipStream_t s);
 int launch_coef_from_spinor(const q4c_plan *p, const double *spin_d, double *coef_out, hipStream_t s);
 int launch_check_finite(const q4c_plan *p, const double *v, hipStream_t s, bool *finite);
 

@@ -1573,7 +1573,7 @@ int launch_density(const q4c_plan *p, const double *coef, uint32_t terms, int pr
       }
       if ((rc = check_launch("k_panel")) != Q4C_OK) return rc;
     }
-    if ((rc = launch_density_pass(p, ps, precision, weight_mode, panel, partial, tickets, out, s)) != Q4C_OK) return rc;
+    if ((rc = launch_density_pass(p, ps, terms, precision, weight_mode, panel, partial, tickets, out, s)) != Q4C_OK) return rc;
   }
   return Q4C_OK;
 }
