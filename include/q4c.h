@@ -68,9 +68,9 @@ enum {
  *   Q4C_PREC_F64        FP64 MFMA, FP64 accumulation.  The nine products of
  *                       two gradients a, b come from six sums: D_m = a_m b_m
  *                       and M_x = (a_y - a_z)(b_y + b_z) (and cyclic), with
- *                       Ws = D_x + D_y + D_z, Wso_x = M_x - (D_y - D_z), so the
- *                       rounding of Wso_x is relative to the magnitudes of
- *                       the products in M_x and D_y, D_z.
+ *                       Ws = D_x + D_y + D_z, Wso_x = M_x - (D_y - D_z),
+ *                       joined every 32 points: the error of Wso_x has terms
+ *                       relative to the magnitudes of D_y and D_z of 32 points.
  *   Q4C_PREC_F32        FP32 MFMA on FP32 operands (sqrt|w v| times the
  *                       gradient, formed in FP64 and rounded once; the row
  *                       operand carries the sign of w v);

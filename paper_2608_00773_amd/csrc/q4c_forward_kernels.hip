@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <type_traits>
 
 #include "q4c_internal.h"
 #include "q4c_device.h"
@@ -18,6 +19,8 @@ namespace {
 struct Operand {
   dbl2 v[4];
 };
+
+constexpr int kJoin = 32;  // points between two joins of the D and M sums (see forward_item)
 
 // One wave's item: the 16 x 16 blocks (rb, cb .. cb + NB - 1) of a batch, all
 // its points.  With a = grad phi_i (rows, weighted by w v) and b = grad phi_j
@@ -39,12 +42,21 @@ struct Operand {
 // lines in L1 (70% of the reads hit there, 86% of the rest in L2).  Waves
 // never wait for each other.
 //
+// Wso is the difference of sums that grow with the products of D, so these run
+// over kJoin points only and then join the running Ws and Wso.  RMS error of Wso
+// against 80-bit sums relative to its own products, in units of that of the
+// nine products summed by MFMA over a whole batch, same panels: without joins
+// 1.19 (3 atoms), 1.24 (60 atoms), 2.65 (points within 0.1 bohr of the axis of
+// two atoms, where D outweighs Wso most); joined every 64 points 1.06, 0.96,
+// 1.14; every 32 points 1.01, 0.91, 1.04.  With the distances of k_panel, which
+// all parts profit from, 0.59, 0.66, 0.30 of what it was.  The joins cost 2%
+// (cluster) and 3.6% (slab below); every 64 points 0.7 and 1.9%.
+//
 // Bound: FP64 matrix pipe.  120-atom cluster (1.9M points, 171 functions per
-// batch on average) 14.5 -> 9.15 ms, dense 300-atom slab (319 per batch) 43.3
-// -> 27.9 ms against ten products from 64 x 64 tiles in LDS with a barrier
+// batch on average) 14.5 -> 9.4 ms, dense 300-atom slab (319 per batch) 43.3
+// -> 29.0 ms against ten products from 64 x 64 tiles in LDS with a barrier
 // every 8 points; the seven MFMAs alone take 6.7 and 21.3 ms at their peak
-// rate (76% of the active cycles on the slab, the FP64 vector instructions 5%
-// more).
+// rate.
 template <int NB>
 __device__ __forceinline__ void forward_item(const DevPlan &d, int f0, int n, int g0, int P, const double *pb, int rb,
                                              int cb, const double *om, double *staging) {
@@ -85,7 +97,8 @@ __device__ __forceinline__ void forward_item(const DevPlan &d, int f0, int n, in
   for (int c = 0; c < NB; ++c)
 #pragma unroll
     for (int q = 0; q < 7; ++q) acc[c][q] = dbl4{0.0, 0.0, 0.0, 0.0};
-  auto multiply = [&](const Operand (&o)[1 + NB], const dbl2 &w) {
+  // first: the D sums start from zero here
+  auto multiply = [&](const Operand (&o)[1 + NB], const dbl2 &w, auto first) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const double a0 = o[0].v[0][h] * w[h], ax = o[0].v[1][h] * w[h], ay = o[0].v[2][h] * w[h],
@@ -95,9 +108,11 @@ __device__ __forceinline__ void forward_item(const DevPlan &d, int f0, int n, in
       for (int c = 0; c < NB; ++c) {
         const double b0 = o[1 + c].v[0][h], bx = o[1 + c].v[1][h], by = o[1 + c].v[2][h], bz = o[1 + c].v[3][h];
         acc[c][0] = mfma64(a0, b0, acc[c][0]);
-        acc[c][1] = mfma64(ax, bx, acc[c][1]);
-        acc[c][2] = mfma64(ay, by, acc[c][2]);
-        acc[c][3] = mfma64(az, bz, acc[c][3]);
+        const bool z = decltype(first)::value && h == 0;
+        const dbl4 z4 = dbl4{0.0, 0.0, 0.0, 0.0};
+        acc[c][1] = mfma64(ax, bx, z ? z4 : acc[c][1]);
+        acc[c][2] = mfma64(ay, by, z ? z4 : acc[c][2]);
+        acc[c][3] = mfma64(az, bz, z ? z4 : acc[c][3]);
         acc[c][4] = mfma64(ayz, by + bz, acc[c][4]);
         acc[c][5] = mfma64(azx, bz + bx, acc[c][5]);
         acc[c][6] = mfma64(axy, bx + by, acc[c][6]);
@@ -105,18 +120,37 @@ __device__ __forceinline__ void forward_item(const DevPlan &d, int f0, int n, in
       }
     }
   };
+  dbl4 ws[NB];
+#pragma unroll
+  for (int c = 0; c < NB; ++c) ws[c] = dbl4{0.0, 0.0, 0.0, 0.0};
   Operand oa[1 + NB], ob[1 + NB];
   dbl2 wa, wb;
   load(0, oa, wa);
-  for (int k = 0; k < Pp; k += 16) {  // Pp is a multiple of 16: two K pairs per turn
+  auto turn = [&](int k, auto first) {  // two K pairs (Pp is a multiple of 16)
     load(k + 8, ob, wb);
     __builtin_amdgcn_sched_barrier(0);
-    multiply(oa, wa);
+    multiply(oa, wa, first);
     __builtin_amdgcn_sched_barrier(0);
     load(k + 16, oa, wa);
     __builtin_amdgcn_sched_barrier(0);
-    multiply(ob, wb);
+    multiply(ob, wb, std::false_type{});
     __builtin_amdgcn_sched_barrier(0);
+  };
+  for (int k0 = 0; k0 < Pp; k0 += kJoin) {
+    turn(k0, std::true_type{});
+    for (int k = k0 + 16; k < min(Pp, k0 + kJoin); k += 16) turn(k, std::false_type{});
+    // Ws and Wso of these points join the running sums (Wso in M's registers)
+#pragma unroll
+    for (int c = 0; c < NB; ++c) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double dx = acc[c][1][r], dy = acc[c][2][r], dz = acc[c][3][r];
+        ws[c][r] += (dx + dy) + dz;
+        acc[c][4][r] -= dy - dz;
+        acc[c][5][r] -= dz - dx;
+        acc[c][6][r] -= dx - dy;
+      }
+    }
   }
   // write the blocks to the staged atom-pair blocks
   const double cp = d.cprime;
@@ -124,12 +158,7 @@ __device__ __forceinline__ void forward_item(const DevPlan &d, int f0, int n, in
 #pragma unroll
   for (int c = 0; c < NB; ++c)
     stage_block<0, 5>(sr, d, f0, n, rb, cb + c, l16, [&](int r, int q) {
-      const double dx = acc[c][1][r], dy = acc[c][2][r], dz = acc[c][3][r];
-      return q == 0   ? acc[c][0][r]
-             : q == 1 ? cp * ((dx + dy) + dz)
-             : q == 2 ? cp * (acc[c][4][r] - (dy - dz))
-             : q == 3 ? cp * (acc[c][5][r] - (dz - dx))
-                      : cp * (acc[c][6][r] - (dx - dy));
+      return q == 0 ? acc[c][0][r] : cp * (q == 1 ? ws[c][r] : acc[c][q + 2][r]);
     });
 }
 
