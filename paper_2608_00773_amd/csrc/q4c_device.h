@@ -229,8 +229,13 @@ __device__ __forceinline__ int d_row_f32(int lk, int r) { return 4 * lk + r; }
 // the matrix pipe, and the 64-bit addresses of stage_store cost more of them
 // than the rest of an item outside its MFMAs: the dense slab's forward took
 // 29.5 ms with it and 28.9 so, the 120-atom cluster's 9.67 and 9.52 ms.
+// Plans with a batch whose staging may not fit a buffer (2 GiB, from ten thousand
+// functions per batch on) take stage_store; kernels that have no registers left
+// for a branch there are compiled for such plans apart (FAR; the branch cost the
+// FP32 contraction 5%).
 struct StageRows {
   __amdgpu_buffer_rsrc_t rs;
+  double *far;             // the pass's staging if rows may not fit rs, else NULL (wave-uniform)
   uint32_t a[4], b[4];     // bytes: row_off - 5 nfn fnoff (relative), 5 nfn
   int row[4], fo[4], nf[4], slot[4];  // row within its atom, the atom's first function, functions, slot
 };
@@ -238,7 +243,8 @@ template <bool F32 = false>
 __device__ __forceinline__ StageRows stage_rows(const DevPlan &d, int f0, int n, int rb, int lk, double *staging) {
   StageRows s;
   const int64_t base = uniform_i64(d.loc_rowoff[f0 + 16 * rb]);  // the rows' atoms are stored from here on in slot order
-  s.rs = __builtin_amdgcn_make_buffer_rsrc((void *)(staging + base), (short)0, (int)0x7ffffff8, 0x00020000);
+  s.rs = __builtin_amdgcn_make_buffer_rsrc((void *)(staging + base), (short)0, (int)kStageRange, 0x00020000);
+  s.far = d.stage_far ? staging : nullptr;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int li = 16 * rb + (F32 ? d_row_f32(lk, r) : d_row_f64(lk, r)), lc = li < n ? li : n - 1;
@@ -254,13 +260,27 @@ __device__ __forceinline__ StageRows stage_rows(const DevPlan &d, int f0, int n,
   return s;
 }
 // parts Q0 .. Q1 - 1 of the block's rows r: val(r, q)
-template <int Q0, int Q1, typename F>
+template <int Q0, int Q1, bool FAR = true, typename F>
 __device__ __forceinline__ void stage_block(const StageRows &s, const DevPlan &d, int f0, int n, int rb, int cb, int l16,
                                             F val) {
   constexpr uint32_t kDrop = 0xfffffff0u;
   const int lj = 16 * cb + l16;
   const int64_t v = d.loc_info[f0 + (lj < n ? lj : n - 1)];
   const int slot = lj < n ? (int)(v & 0xFFFFF) : -1, fo = (int)((v >> 20) & 0xFFFFF), nf = (int)(v >> 40);
+  if (FAR && s.far) {
+    if (lj >= n) return;
+    const SlotInfo sj{slot, fo, nf, d.loc_rowoff[f0 + lj]};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int li = s.fo[r] + s.row[r];
+      if (li >= n) continue;
+      double x[Q1 - Q0];
+#pragma unroll
+      for (int q = Q0; q < Q1; ++q) x[q - Q0] = val(r, q);
+      stage_store<Q0, Q1>(s.far, SlotInfo{s.slot[r], s.fo[r], s.nf[r], d.loc_rowoff[f0 + li]}, sj, li, lj, rb < cb, x);
+    }
+    return;
+  }
   bool same = false;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {

@@ -34,6 +34,10 @@ struct BlockItem {
 };
 static_assert(sizeof(BlockItem) == 8, "BlockItem is 8 bytes");
 
+// Bytes of the buffer that a block row's results are stored through with 32-bit
+// offsets.
+constexpr int64_t kStageRange = 0x7ffffff8;
+
 // Everything a kernel needs about the plan, as raw device pointers.
 struct DevPlan {
   // basis
@@ -59,6 +63,7 @@ struct DevPlan {
   const int32_t *batch_slot_off;    // [n_batches + 1]
   const int32_t *slot_fnoff;        // [n_slots] local function offset of the slot
   const int32_t *slot_nfn;          // [n_slots]
+  int32_t stage_far;                // some batch's staging exceeds kStageRange
   const int64_t *slot_row_off;      // [n_slots] staging offset of the slot's block row (pass relative)
   const int64_t *batch_part_off;    // [n_batches] first adjoint partial of the batch (pass relative)
   const int64_t *pair_off;          // [n_pairs + 1]
@@ -182,6 +187,7 @@ struct q4c_plan {
   // ---- work, passes, reductions
   std::vector<q4c::WorkItem> work;
   std::vector<int64_t> batch_part_off;
+  bool stage_far = false;            // some batch's staging exceeds kStageRange
   std::vector<q4c::Pass> passes;
   std::vector<int32_t> red_pair;
   std::vector<uint8_t> red_first;

@@ -531,7 +531,7 @@ __global__ __launch_bounds__(64, 3) void k_panel(DevPlan d, const WorkItem *tile
 // Work item positions 0..nw-1 of a pass map to work items w0 + order[w0 + pos]
 // (order != NULL: cost-sorted) or w0 + pos.  tickets == NULL: one workgroup
 // per position; otherwise a persistent loop (next_item).
-template <bool PERSIST>
+template <bool FAR, bool PERSIST>
 __global__ __launch_bounds__(NT, 4) void k_contract_v(
     DevPlan d, const WorkItem *work, const int32_t *order, int64_t w0, int64_t nw, const double *om,
     const double *panel, double *staging, unsigned *tickets) {
@@ -616,7 +616,7 @@ __global__ __launch_bounds__(NT, 4) void k_contract_v(
   for (int sl = 0; sl < 4; ++sl) {
     if (!act[sl]) continue;  // wave-uniform
     const int rb = (r0 + brow[sl]) >> 4;
-    stage_block<0, 1>(stage_rows(d, f0, n, rb, lk, staging), d, f0, n, rb, (c0 + bcol[sl]) >> 4, li16,
+    stage_block<0, 1, FAR>(stage_rows(d, f0, n, rb, lk, staging), d, f0, n, rb, (c0 + bcol[sl]) >> 4, li16,
                       [&](int r, int) { return acc[sl][r]; });
   }
   if (!PERSIST) break;
@@ -765,7 +765,7 @@ __global__ __launch_bounds__(NT, 1) void k_contract_valu(DevPlan d, const WorkIt
 // hi hi + hi lo + lo hi (three FP32 MFMAs): the operands' rounding drops to
 // about 2^-48, and a 16-point partial sum holds up to 144 products
 // (gamma_150).
-template <bool SPLIT, bool PERSIST>
+template <bool SPLIT, bool FAR, bool PERSIST>
 __global__ __launch_bounds__(NT, 2) void k_contract_w(DevPlan d, const WorkItem *work, const int32_t *order,
                                                       int64_t w0, int64_t nw, const double *om,
                                                       const double *panel, double *staging, unsigned *tickets) {
@@ -945,7 +945,7 @@ __global__ __launch_bounds__(NT, 2) void k_contract_w(DevPlan d, const WorkItem 
   for (int sl = 0; sl < 4; ++sl) {
     if (!act[sl]) continue;  // wave-uniform
     const int rb = (r0 + brow[sl]) >> 4;
-    stage_block<1, 5>(stage_rows<true>(d, f0, n, rb, lk, staging), d, f0, n, rb, (c0 + bcol[sl]) >> 4, li16,
+    stage_block<1, 5, FAR>(stage_rows<true>(d, f0, n, rb, lk, staging), d, f0, n, rb, (c0 + bcol[sl]) >> 4, li16,
                       [&](int r, int q) { return cp * accw[sl][q - 1][r]; });
   }
   if (!PERSIST) break;
@@ -1446,15 +1446,25 @@ int launch_integrate(const q4c_plan *p, const double *v, int precision, uint32_t
           // four V-only workgroups fit on a CU, twice the other contraction
           // kernels' two: twice the persistent workgroups
           const unsigned grid_v = (unsigned)(pers ? std::min<int64_t>(2 * (int64_t)cfg.persistent, nw) : nw);
-          launch_work(k_contract_v<true>, k_contract_v<false>, grid_v, pers, s, p->dp, p->d_work, order,
-                      ps.w0, nw, p->d_om, panel, p->d_staging, tick_a);
+          auto go = [&](auto kernel_p, auto kernel_1) {
+            launch_work(kernel_p, kernel_1, grid_v, pers, s, p->dp, p->d_work, order, ps.w0, nw, p->d_om, panel,
+                        p->d_staging, tick_a);
+          };
+          p->stage_far ? go(k_contract_v<true, true>, k_contract_v<true, false>)
+                       : go(k_contract_v<false, true>, k_contract_v<false, false>);
         }
-        if (wantW && precision == Q4C_PREC_SPLIT_F32)
-          launch_work(k_contract_w<true, true>, k_contract_w<true, false>, grid, pers, s, p->dp, p->d_work, order,
-                      ps.w0, nw, p->d_om, panel, p->d_staging, tick_w);
-        else if (wantW)
-          launch_work(k_contract_w<false, true>, k_contract_w<false, false>, grid, pers, s, p->dp, p->d_work, order,
-                      ps.w0, nw, p->d_om, panel, p->d_staging, tick_w);
+        if (wantW) {
+          auto go = [&](auto kernel_p, auto kernel_1) {
+            launch_work(kernel_p, kernel_1, grid, pers, s, p->dp, p->d_work, order, ps.w0, nw, p->d_om, panel,
+                        p->d_staging, tick_w);
+          };
+          if (precision == Q4C_PREC_SPLIT_F32)
+            p->stage_far ? go(k_contract_w<true, true, true>, k_contract_w<true, true, false>)
+                         : go(k_contract_w<true, false, true>, k_contract_w<true, false, false>);
+          else
+            p->stage_far ? go(k_contract_w<false, true, true>, k_contract_w<false, true, false>)
+                         : go(k_contract_w<false, false, true>, k_contract_w<false, false, false>);
+        }
       }
     }
     if (nw > 0 && (rc = check_launch("k_contract")) != Q4C_OK) return rc;

@@ -493,6 +493,7 @@ int build_host(q4c_plan *p, const q4c_basis *b, const q4c_grid *g, const std::ve
         off += nf;
       }
     }
+    if (8 * bstage > q4c::kStageRange) p->stage_far = true;
     int nt = (nb_fn + T - 1) / T;
     int64_t bpart = (int64_t)q4c::den_items((int)(q4c::pad16(nb_fn) >> 4)) * (g1 - g0);  // adjoint partials
     // panel: 4 FP64 planes (the largest kind)
@@ -765,6 +766,7 @@ int build_device(q4c_plan *p) {
   d.slot_nfn = snf;
   d.slot_row_off = sro;
   d.batch_part_off = bpt;
+  d.stage_far = p->stage_far;
   d.pair_off = poff;
   d.pair_na = pna;
   d.pair_nb = pnb;
