@@ -78,14 +78,15 @@ constexpr int BS_PF = 4;   // contributions whose values are loaded together
 template <int KC>
 __global__ __launch_bounds__(256, 2) void k_bloch_sum(DevPlan d, int n_parts, int64_t ncp, const int64_t *cp_off,
                                                       const int64_t *ct_off, const int32_t *ct_pair,
-                                                      const int32_t *ct_flag, int n_k, int n_grp, int kper, const double *ph,
+                                                      const int32_t *ct_flag, int64_t wg0, int n_k, int n_grp,
+                                                      int kper, const double *ph,
                                                       const double *__restrict__ store, double *__restrict__ out) {
   __shared__ int64_t s_off[BS_TB];
   __shared__ dbl2 s_ph[BS_TB][KC];
   __shared__ dbl2 s_turn[BS_EL];
   // the k-point groups of one (cell pair, part) next to each other on one XCD:
   // they read the same blocks
-  const int64_t wg = xcd_map(blockIdx.x, gridDim.x), cq = wg / n_grp;
+  const int64_t wg = wg0 + xcd_map(blockIdx.x, gridDim.x), cq = wg / n_grp;
   const int64_t c = cq / n_parts;
   const int q = (int)(cq - c * n_parts);
   const int k0 = (int)(wg - cq * n_grp) * kper, nk = min(kper, n_k - k0);
@@ -120,7 +121,7 @@ __global__ __launch_bounds__(256, 2) void k_bloch_sum(DevPlan d, int n_parts, in
         }
         __syncthreads();  // the batch is visible
         // BS_PF contributions at a time, the next ones' values loaded while
-        // these are added (past the last one: it again, with zero phases)
+        // these are added (past the last one: it again, not added)
         double v[2][BS_PF][BS_EPT];
         auto load = [&](int tt, double (&w)[BS_PF][BS_EPT]) {
 #pragma unroll
@@ -289,9 +290,11 @@ static int launch_bloch_sum_chunks(const q4c_plan *p, int n_parts, const double 
       // elements x 9 complex sums)
       const int groups = (nk + 8) / 9, kper = (nk + groups - 1) / groups;
       auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)(ncp * n_parts * groups)), dim3(256), 0, s, p->dp, n_parts, ncp,
-                           p->d_cp_off, p->d_ct_off, p->d_ct_pair, p->d_ct_flag, nk, groups, kper,
-                           (const double *)phase, store, out + 2 * (int64_t)k0 * n_parts * clen);
+        for_grids(ncp * n_parts * groups, [&](int64_t wg0, unsigned grid) {
+          hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, s, p->dp, n_parts, ncp, p->d_cp_off, p->d_ct_off,
+                             p->d_ct_pair, p->d_ct_flag, wg0, nk, groups, kper, (const double *)phase, store,
+                             out + 2 * (int64_t)k0 * n_parts * clen);
+        });
       };
       if (kper <= 2)
         launch(k_bloch_sum<2>);

@@ -34,6 +34,14 @@ struct BlockItem {
 };
 static_assert(sizeof(BlockItem) == 8, "BlockItem is 8 bytes");
 
+// Workgroups of one launch where their number has no other bound (a grid
+// dimension holds 2^32 threads): f(first workgroup, workgroups) for each launch.
+constexpr int64_t kGridMax = 1 << 22;
+template <typename F>
+void for_grids(int64_t total, F f) {
+  for (int64_t w = 0; w < total; w += kGridMax) f(w, (unsigned)(total - w < kGridMax ? total - w : kGridMax));
+}
+
 // Bytes of the buffer that a block row's results are stored through with 32-bit
 // offsets.
 constexpr int64_t kStageRange = 0x7ffffff8;

@@ -268,11 +268,11 @@ __device__ __forceinline__ void walk_shells(const DevPlan &d, const FnData &m, i
 // ---------------------------------------------------------------------------
 
 template <bool HILO>
-__global__ __launch_bounds__(512, 4) void k_tabulate(DevPlan d, const WorkItem *tiles, int64_t t0, int64_t nt, int npb,
+__global__ __launch_bounds__(512, 4) void k_tabulate(DevPlan d, const WorkItem *tiles, int64_t t0, int64_t wg0, int npb,
                                                      int64_t b0, int deriv, void *out) {
   constexpr int SR = T + 1;
   __shared__ double st[2][64 * SR];
-  const int64_t bid = xcd_map(blockIdx.x + (int64_t)blockIdx.y * gridDim.x, nt * npb);  // as in k_panel
+  const int64_t bid = wg0 + xcd_map(blockIdx.x, gridDim.x);  // as in k_panel
   const WorkItem it = tiles[t0 + bid / npb];
   const int b = it.batch;
   const int g0 = d.batch_pt_off[b], P = d.batch_pt_off[b + 1] - g0;
@@ -412,11 +412,11 @@ constexpr int panel_stage(int kind) {           // staged bytes per wave: four r
                             : 4 * PR8 + 72 * PR2;
 }
 template <int KIND>
-__global__ __launch_bounds__(64, 3) void k_panel(DevPlan d, const WorkItem *tiles, int64_t t0, int64_t nt,
-                                                             int sub, int npb, double *panel, const double *om) {
+__global__ __launch_bounds__(64, 3) void k_panel(DevPlan d, const WorkItem *tiles, int64_t t0, int64_t wg0, int sub,
+                                              int npb, double *panel, const double *om) {
   __shared__ __attribute__((aligned(16))) unsigned char st[panel_stage(KIND)];
   // neighbouring waves (of one batch) on one XCD
-  const int64_t bid = xcd_map(blockIdx.x + (int64_t)blockIdx.y * gridDim.x, nt * sub * npb), pos = bid / npb;
+  const int64_t bid = wg0 + xcd_map(blockIdx.x, gridDim.x), pos = bid / npb;
   const int p0 = 64 * (int)(bid % npb);
   const WorkItem it = tiles[t0 + pos / sub];
   const int b = it.batch, rows = T / sub;
@@ -1344,13 +1344,12 @@ int launch_tabulate(const q4c_plan *p, int64_t b0, int64_t b1, int deriv, int dt
   int pmax = 0;
   for (int64_t b = b0; b < b1; ++b) pmax = std::max(pmax, (int)(p->batch_pt_off[b + 1] - p->batch_pt_off[b]));
   const int npb = (pmax + 63) / 64;
-  const dim3 grid((unsigned)nt, (unsigned)npb);
   {
     TimedLaunch tl_(p, Q4C_TIMER_TABULATE, s);
-    if (dtype == Q4C_DTYPE_F32_HILO)
-      hipLaunchKernelGGL(k_tabulate<true>, grid, dim3(512), 0, s, p->dp, p->d_ptile, t0, nt, npb, b0, deriv, out);
-    else
-      hipLaunchKernelGGL(k_tabulate<false>, grid, dim3(512), 0, s, p->dp, p->d_ptile, t0, nt, npb, b0, deriv, out);
+    for_grids(nt * npb, [&](int64_t wg0, unsigned grid) {
+      hipLaunchKernelGGL(dtype == Q4C_DTYPE_F32_HILO ? k_tabulate<true> : k_tabulate<false>, dim3(grid), dim3(512), 0, s,
+                         p->dp, p->d_ptile, t0, wg0, npb, b0, deriv, out);
+    });
   }
   return check_launch("k_tabulate");
 }
@@ -1367,14 +1366,16 @@ static void launch_work(K kernel_p, K kernel_1, unsigned grid, bool persistent, 
     hipLaunchKernelGGL(kernel_1, dim3(grid), dim3(NT), 0, s, dp, work, order, w0, nw, om, panel, staging, tickets);
 }
 
-// The panels of a pass: one workgroup per slot of its batches.
+// The panels of a pass: one wave per (tile or quarter tile, 64 points).
 template <typename K>
 static void launch_panel(K kernel, const q4c_plan *p, const Pass &ps, double *panel, hipStream_t s) {
   const int64_t nt = ps.t1 - ps.t0;
   const int npb = (ps.p_max + 63) / 64;
   const int sub = panel_sub(nt * npb);
-  hipLaunchKernelGGL(kernel, dim3((unsigned)(nt * sub), (unsigned)npb), dim3(64), 0, s, p->dp, p->d_ptile, ps.t0, nt, sub, npb,
-                     panel, (const double *)p->d_om);
+  for_grids(nt * sub * npb, [&](int64_t wg0, unsigned grid) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, s, p->dp, p->d_ptile, ps.t0, wg0, sub, npb, panel,
+                       (const double *)p->d_om);
+  });
 }
 
 int launch_integrate(const q4c_plan *p, const double *v, int precision, uint32_t parts, uint32_t flags,
