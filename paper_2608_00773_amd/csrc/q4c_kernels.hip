@@ -381,6 +381,14 @@ __device__ __forceinline__ void split3_bf16x2(double a, double b, uint32_t &w1, 
   w3 = pack_bf16(ra - __uint_as_float(w2 << 16), rb - __uint_as_float(w2 & 0xffff0000u));
 }
 
+// LDS accesses of a wave's lanes before this are ordered before those after it,
+// for the compiler (the hardware runs a wave's LDS accesses in order).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // One wave (a workgroup of its own: nothing is shared) per (batch, T / sub
 // functions, 64 points), one point per lane.  All lanes work on the same
 // function, so a shell's interval search, table read and cubic are done once
@@ -446,7 +454,7 @@ __global__ __launch_bounds__(64, 3) void k_panel(DevPlan d, const WorkItem *tile
     // every lane has staged its values: the barrier (no instruction) also
     // keeps the compiler from running lanes with different radial branches
     // through here apart
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     {
       // FP64 planes: 8 quads of four rows per store, 16 bytes per lane
       const int row = (lane >> 1) & 3, qd = lane >> 3;
@@ -488,7 +496,7 @@ __global__ __launch_bounds__(64, 3) void k_panel(DevPlan d, const WorkItem *tile
               *reinterpret_cast<const stage_u32x4 *>(st + S2 + (8 * q + row) * PR2 + oc * 16);
       }
     }
-    __builtin_amdgcn_wave_barrier();  // the rows are read
+    wave_sync();  // the rows are read
   };
   // stages the values of panel row i: phi, then psi (H/S) or the gradient
   auto put = [&](int i, double f, double fx, double fy, double fz) {
