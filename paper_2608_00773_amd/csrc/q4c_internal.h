@@ -195,6 +195,7 @@ struct q4c_plan {
   // ---- work, passes, reductions
   std::vector<q4c::WorkItem> work;
   std::vector<int64_t> batch_part_off;
+  double tab_fill = 1.0;             // share of the lanes of 64-point chunks that have a point, over the function tiles
   bool stage_far = false;            // some batch's staging exceeds kStageRange
   std::vector<q4c::Pass> passes;
   std::vector<int32_t> red_pair;

@@ -38,6 +38,11 @@ namespace {
 // Basis functions
 // ---------------------------------------------------------------------------
 
+// A function's value is the same to the bit in every kernel that forms it:
+// products and sums are fused within an expression only, not as the code
+// around them happens to allow.
+#pragma clang fp contract(on)
+
 // Real solid harmonics S_lm = s^l Y_lm (App. B convention, Condon-Shortley
 // phase as written there: Y_1,1 = -sqrt(3/4pi) x/s) and their gradients,
 // l <= 4, indexed by lm = l^2 + l + m.
@@ -110,10 +115,6 @@ __device__ __forceinline__ void solid_harmonic(int lm, double x, double y, doubl
 }
 
 // ---------------------------------------------------------------------------
-// Contraction
-// ---------------------------------------------------------------------------
-
-// ---------------------------------------------------------------------------
 // Tabulation: one wave walks the shells of up to 64 functions at 64 points.
 // ---------------------------------------------------------------------------
 
@@ -134,6 +135,19 @@ __device__ __forceinline__ int radial_interval(double s, int n, double k1, doubl
   }
   dd = fma(-(double)j * (double)j, k2, s);
   return j;
+}
+
+// 1 / s and s of a squared distance s2 (0 for 0), s to its last bit: the steep
+// radials of tight functions carry its error 10 times and more into phi (V,
+// relative to its terms: RMS error 1.2e-15 -> 2.8e-16 on 60 atoms).
+__device__ __forceinline__ void distance(double s2, double &rinv, double &s) {
+  rinv = s = 0.0;
+  if (s2 > 0.0) {
+    rinv = __builtin_amdgcn_rsq(s2);
+    rinv = rinv * (1.5 - 0.5 * s2 * rinv * rinv);
+    s = s2 * rinv;
+    s = fma(fma(-s, s, s2), 0.5 * rinv, s);
+  }
 }
 
 // lane k's value of a vector register as a scalar
@@ -193,16 +207,7 @@ __device__ __forceinline__ void walk_shells(const DevPlan &d, const FnData &m, i
       geo.dy = py - lane_f64(m.ay, k);
       geo.dz = pz - lane_f64(m.az, k);
       const double s2 = geo.s2 = geo.dx * geo.dx + geo.dy * geo.dy + geo.dz * geo.dz;
-      geo.rinv = geo.s = 0.0;
-      if (s2 > 0.0) {
-        geo.rinv = __builtin_amdgcn_rsq(s2);
-        geo.rinv = geo.rinv * (1.5 - 0.5 * s2 * geo.rinv * geo.rinv);
-        // s to its last bit: the steep radials of tight functions carry its
-        // error 10 times and more into phi (V, relative to its terms: RMS error
-        // 1.2e-15 -> 2.8e-16 on 60 atoms)
-        geo.s = s2 * geo.rinv;
-        geo.s = fma(fma(-geo.s, geo.s, s2), 0.5 * geo.rinv, geo.s);
-      }
+      distance(s2, geo.rinv, geo.s);
     }
     const double rc = lane_f64(m.rc, k);
     rad.c = rad.e = dbl4{0.0, 0.0, 0.0, 0.0};
@@ -251,6 +256,8 @@ __device__ __forceinline__ void walk_shells(const DevPlan &d, const FnData &m, i
     }
   }
 }
+
+#pragma clang fp contract(fast)
 
 // ---------------------------------------------------------------------------
 // nao_tabulate: out is [ncomp][P][n] per batch (FP64), or [ncomp][2][P][n]
@@ -318,6 +325,135 @@ __global__ __launch_bounds__(512, 4) void k_tabulate(DevPlan d, const WorkItem *
   };
   pass(std::integral_constant<int, 0>{});
   if (deriv) pass(std::integral_constant<int, 2>{});
+}
+
+// nao_tabulate where batches leave many of k_tabulate's lanes without a point
+// (launch_tabulate): one workgroup per (batch, 64-function tile), 8 points at a
+// time, every (function, point) on a lane of its own, the functions in the order
+// of lm.
+struct TileMeta {
+  double ax[T], ay[T], az[T];  // centres
+  double rc[T];                // cutoffs (0 for padding)
+  double k1[T], k2[T];         // nint^2 / rcut, rcut / nint^2
+  int64_t coef[T];             // offset of the shell's table
+  int nint[T], lm[T];
+  int order[T];                // tile functions sorted by lm
+};
+
+// Stage metadata of the tile's functions (threads 0 .. T-1) and an ordering
+// by lm, so that lanes working on neighbouring items mostly take the same
+// solid-harmonic branch.
+__device__ __forceinline__ void load_tile_meta(const DevPlan &d, TileMeta &M, int f0, int n, int r0) {
+  const int tid = threadIdx.x;
+  if (tid < T) {
+    const int lf = r0 + tid;
+    if (lf < n) {
+      const int fn = d.loc_fn[f0 + lf];
+      const int a = d.fn_atom[fn], shlm = d.fn_shlm[fn], sh = shlm >> 5;
+      M.ax[tid] = d.R[3 * a];
+      M.ay[tid] = d.R[3 * a + 1];
+      M.az[tid] = d.R[3 * a + 2];
+      M.rc[tid] = d.shell_rcut[sh];
+      M.k1[tid] = d.shell_knot[2 * sh];
+      M.k2[tid] = d.shell_knot[2 * sh + 1];
+      M.coef[tid] = d.shell_coef_off[sh];
+      M.nint[tid] = d.shell_nint[sh];
+      M.lm[tid] = shlm & 31;
+    } else {
+      M.ax[tid] = M.ay[tid] = M.az[tid] = 0.0;
+      M.rc[tid] = 0.0;
+      M.k1[tid] = M.k2[tid] = 0.0;
+      M.coef[tid] = 0;
+      M.nint[tid] = 0;
+      M.lm[tid] = 32;  // padding sorts last
+    }
+  }
+  __syncthreads();
+  if (tid < T) {
+    const int mine = M.lm[tid];
+    int rank = 0;
+    for (int o = 0; o < T; ++o) rank += (M.lm[o] < mine) || (M.lm[o] == mine && o < tid);
+    M.order[rank] = tid;
+  }
+}
+
+#pragma clang fp contract(on)
+// phi and grad phi of tile function m at point (px, py, pz), as walk_shells.
+__device__ __forceinline__ void tab_meta(const DevPlan &d, const TileMeta &M, int m, double px, double py, double pz,
+                                         double &f, double &fx, double &fy, double &fz) {
+  const double dx = px - M.ax[m], dy = py - M.ay[m], dz = pz - M.az[m];
+  const double s2 = dx * dx + dy * dy + dz * dz, rc = M.rc[m];
+  if (!(s2 < rc * rc)) {
+    f = fx = fy = fz = 0.0;
+    return;
+  }
+  double rinv, s, dd;
+  distance(s2, rinv, s);
+  const int j = radial_interval(s, M.nint[m], M.k1[m], M.k2[m], dd);
+  const dbl4 c = *reinterpret_cast<const dbl4 *>(d.coef + M.coef[m] + 4 * (int64_t)j);
+  const double R = ((c[3] * dd + c[2]) * dd + c[1]) * dd + c[0];
+  const double q = ((3.0 * c[3] * dd + 2.0 * c[2]) * dd + c[1]) * rinv;  // Rt'(s) / s
+  double S, gx, gy, gz;
+  solid_harmonic(M.lm[m], dx, dy, dz, S, gx, gy, gz);
+  f = R * S;
+  fx = q * dx * S + R * gx;
+  fy = q * dy * S + R * gy;
+  fz = q * dz * S + R * gz;
+}
+
+#pragma clang fp contract(fast)
+
+template <bool HILO>
+__global__ __launch_bounds__(256) void k_tabulate_few(DevPlan d, const WorkItem *tiles, int64_t t0, int64_t b0,
+                                                      int deriv, void *out) {
+  constexpr int CP = 8;
+  constexpr int SR = T + 1;
+  __shared__ TileMeta M;
+  __shared__ double st[4 * CP * SR];
+  const WorkItem it = tiles[t0 + blockIdx.x];
+  const int b = it.batch;
+  const int g0 = d.batch_pt_off[b], P = d.batch_pt_off[b + 1] - g0;
+  const int f0 = d.batch_fn_off[b], n = d.batch_fn_off[b + 1] - f0;
+  const int r0 = it.ti * T;
+  const int nrow = n - r0 < T ? n - r0 : T;
+  const int nq = deriv ? 4 : 1;
+  const int64_t plane = (int64_t)P * n;
+  const int64_t base = (int64_t)nq * (d.tab_off[b] - d.tab_off[b0]);  // values before this batch
+  load_tile_meta(d, M, f0, n, r0);
+  __syncthreads();
+  for (int g8 = 0; g8 < P; g8 += CP) {
+    for (int e = threadIdx.x; e < T * CP; e += 256) {
+      const int k = e / CP, pt = e % CP;
+      const int fl = M.order[k];
+      double f = 0.0, fx = 0.0, fy = 0.0, fz = 0.0;
+      const int g = g8 + pt;
+      if (M.nint[fl] > 0 && g < P) tab_meta(d, M, fl, d.px[g0 + g], d.py[g0 + g], d.pz[g0 + g], f, fx, fy, fz);
+      st[(0 * CP + pt) * SR + fl] = f;
+      st[(1 * CP + pt) * SR + fl] = fx;
+      st[(2 * CP + pt) * SR + fl] = fy;
+      st[(3 * CP + pt) * SR + fl] = fz;
+    }
+    __syncthreads();
+    // (component, point) rows of the tile's functions: 256 threads = 4 rows x 64 functions
+    for (int e = threadIdx.x; e < nq * CP * T; e += 256) {
+      const int fl = e % T, row = e / T;
+      const int q = row / CP, pt = row % CP;
+      const int g = g8 + pt;
+      if (fl < nrow && g < P) {
+        const double x = st[(q * CP + pt) * SR + fl];
+        const int64_t o = (int64_t)g * n + r0 + fl;
+        if (HILO) {
+          float *of = static_cast<float *>(out) + 2 * (base + q * plane);
+          const float hi = (float)x;
+          of[o] = hi;
+          of[plane + o] = (float)(x - (double)hi);
+        } else {
+          static_cast<double *>(out)[base + q * plane + o] = x;
+        }
+      }
+    }
+    __syncthreads();  // st consumed
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1346,12 +1482,30 @@ static int check_launch(const char *what) {
 // looked up twice).
 static int panel_sub(int64_t waves) { return waves <= 1024 ? 4 : 1; }
 
+// Whether k_tabulate_few is the faster one: batches of few points, where a share
+// of k_tabulate's lanes has no point (the values are the same).  24 atoms, with
+// gradients, k_tabulate / k_tabulate_few: 8 points per batch 94 / 29 us, 32 120 /
+// 76, 48 148 / 128, 64 46 / 52 (a quarter of the batches), 80 80 / 63, 96 81 / 75,
+// 112 82 / 90, 144 103 / 113; values alone 50 / 23, 64 / 60, 69 / 82, 25 / 40, 41
+// / 48 up to 80 points.
+static bool tabulate_few(const q4c_plan *p, int deriv) {
+  return p->max_batch_points <= 128 && p->tab_fill < (deriv ? 0.8 : 0.6);
+}
+
 int launch_tabulate(const q4c_plan *p, int64_t b0, int64_t b1, int deriv, int dtype, void *out, hipStream_t s) {
   const int64_t t0 = p->batch_tile_off[b0], nt = p->batch_tile_off[b1] - t0;
   if (nt <= 0) return Q4C_OK;
   int pmax = 0;
   for (int64_t b = b0; b < b1; ++b) pmax = std::max(pmax, (int)(p->batch_pt_off[b + 1] - p->batch_pt_off[b]));
   const int npb = (pmax + 63) / 64;
+  if (tabulate_few(p, deriv)) {
+    {
+      TimedLaunch tl_(p, Q4C_TIMER_TABULATE, s);
+      hipLaunchKernelGGL(dtype == Q4C_DTYPE_F32_HILO ? k_tabulate_few<true> : k_tabulate_few<false>, dim3((unsigned)nt),
+                         dim3(256), 0, s, p->dp, p->d_ptile, t0, b0, deriv, out);
+    }
+    return check_launch("k_tabulate_few");
+  }
   {
     TimedLaunch tl_(p, Q4C_TIMER_TABULATE, s);
     for_grids(nt * npb, [&](int64_t wg0, unsigned grid) {

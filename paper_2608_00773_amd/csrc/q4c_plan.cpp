@@ -558,6 +558,15 @@ int build_host(q4c_plan *p, const q4c_basis *b, const q4c_grid *g, const std::ve
     p->tab_off[b + 1] = p->tab_off[b] + (int64_t)(p->batch_pt_off[b + 1] - p->batch_pt_off[b]) *
                                             (p->batch_fn_off[b + 1] - p->batch_fn_off[b]);
   p->fn_entries = (int64_t)p->loc_fn.size();
+  {
+    double points = 0.0, lanes = 0.0;
+    for (int64_t b = 0; b < p->n_batches; ++b) {
+      const int64_t P = p->batch_pt_off[b + 1] - p->batch_pt_off[b], nt = p->batch_tile_off[b + 1] - p->batch_tile_off[b];
+      points += (double)(P * nt);
+      lanes += (double)((P + 63) / 64 * 64 * nt);
+    }
+    if (lanes > 0.0) p->tab_fill = points / lanes;
+  }
   // per pass: work items by decreasing estimated cost (padded points x active
   // rows x active columns; a diagonal tile computes about half its blocks)
   p->work_order.resize(p->work.size());
