@@ -1825,9 +1825,9 @@ int q4c_plan_autotune(q4c_plan *p, const double *v_dev, int32_t precision, doubl
   };
   for (int kernel = 0; kernel < 2 && rc == Q4C_OK; ++kernel) {
     if (kernel == Q4C_KERNEL_DENSITY && !coef_dev) break;
-    // workgroups that fit on the chip at once: two per CU for every
-    // contraction kernel and the adjoint
-    const int occ = 2;
+    // workgroups that fit on the chip at once: two per CU for the contractions
+    // (V alone launches twice as many by itself), three for the adjoint
+    const int occ = kernel == Q4C_KERNEL_CONTRACT ? 2 : 3;
     const int cand_p[3] = {0, occ * p->n_cu, 2 * occ * p->n_cu};
     q4c::LaunchCfg best{};
     double best_ms = 1e300;
