@@ -215,7 +215,10 @@ __device__ __forceinline__ void grad_item(int np, int Pp, int i0, int q0, const 
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
         (void *)(pq + c * plane + 4 * (int64_t)i0), (short)0, 0x7ffffff0, 0x00020000);
 #pragma unroll
-    for (int f = 0; f < F; ++f)
+    for (int f = 0; f < F; ++f) {
+      double t[Q];  // this block's rows first: shorter chains round less
+#pragma unroll
+      for (int q = 0; q < Q; ++q) t[q] = 0.0;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const bool pair = f < 2 * FP;
@@ -224,14 +227,17 @@ __device__ __forceinline__ void grad_item(int np, int Pp, int i0, int q0, const 
 #pragma unroll
         for (int q = 0; q < QP; ++q) {
           const dbl2 e = __builtin_bit_cast(dbl2, __builtin_amdgcn_raw_buffer_load_b128(rs, bp[q] + fo, 0, 0));
-          s[2 * q][c] += acc[f][2 * q][r] * e[0];
-          s[2 * q + 1][c] += acc[f][2 * q + 1][r] * e[1];
+          t[2 * q] += acc[f][2 * q][r] * e[0];
+          t[2 * q + 1] += acc[f][2 * q + 1][r] * e[1];
         }
         if (Q & 1) {
           const double e = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, bp[QP] + fo, 0, 0));
-          s[Q - 1][c] += acc[f][Q - 1][r] * e;
+          t[Q - 1] += acc[f][Q - 1][r] * e;
         }
       }
+#pragma unroll
+      for (int q = 0; q < Q; ++q) s[q][c] += t[q];
+    }
     __builtin_amdgcn_sched_barrier(0);  // one component's loads at a time
   }
   // over the rows of the four lane groups; group lk writes component lk
