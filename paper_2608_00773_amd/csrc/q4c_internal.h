@@ -65,14 +65,9 @@ struct DevPlan {
   const int32_t *batch_pt_off;      // [n_batches + 1]
   const int32_t *batch_fn_off;      // [n_batches + 1]
   const int32_t *loc_fn;            // [fn_entries] global function
-  const int32_t *loc_slot;          // [fn_entries] slot (relevant atom) within the batch
-  const int64_t *loc_info;          // [fn_entries] slot | slot's first local function << 20 | its function count << 40
+  const int64_t *loc_info;          // [fn_entries] slot (relevant atom of the batch) | slot's first local function << 20 | its function count << 40
   const int64_t *loc_rowoff;        // [fn_entries] staging offset of the function's slot block row (pass relative)
   const int32_t *batch_slot_off;    // [n_batches + 1]
-  const int32_t *slot_fnoff;        // [n_slots] local function offset of the slot
-  const int32_t *slot_nfn;          // [n_slots]
-  int32_t stage_far;                // some batch's staging exceeds kStageRange
-  const int64_t *slot_row_off;      // [n_slots] staging offset of the slot's block row (pass relative)
   const int64_t *batch_part_off;    // [n_batches] first adjoint partial of the batch (pass relative)
   const int64_t *pair_off;          // [n_pairs + 1]
   const int32_t *pair_na, *pair_nb; // [n_pairs]
@@ -84,6 +79,7 @@ struct DevPlan {
   const int64_t *batch_sp_off;      // [n_batches + 1]
   const int64_t *tab_off;           // [n_batches + 1] prefix of P_b n_b (nao_tabulate layout)
   const int64_t *panel_off;         // [n_batches] pass-relative offset of the batch's operand panel
+  int32_t stage_far;                // some batch's staging exceeds kStageRange
   int64_t store_len;
   int64_t n_active;
   int64_t n_points;
@@ -227,7 +223,7 @@ struct q4c_plan {
   int64_t *d_inc_src = nullptr;
   int32_t *d_untouched = nullptr;
   q4c::WorkItem *d_ptile = nullptr;
-  double *d_om = nullptr;  // [n_active + 16] point weights w_g v_g of the current call
+  double *d_om = nullptr;  // [n_active] point weights w_g v_g of the current call
   q4c::BlockItem *d_den = nullptr;       // adjoint items per pass, batch order
   q4c::BlockItem *d_den_cost = nullptr;  // the same by decreasing cost
   q4c::BlockItem *d_blocks = nullptr;       // forward block items per pass, batch order

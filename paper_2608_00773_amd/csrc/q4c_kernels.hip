@@ -466,20 +466,16 @@ __global__ __launch_bounds__(256) void k_tabulate_few(DevPlan d, const WorkItem 
 // 128-byte runs, for the adjoint (points as rows).
 // ---------------------------------------------------------------------------
 
-__device__ __forceinline__ int64_t panel_index(int q, int pt, int i, int Pp, int np) {
-  return ((int64_t)(q * (Pp >> 2) + (pt >> 2)) * np + i) * 4 + (pt & 3);
-}
-
 __global__ void k_zero_u32(unsigned *p, int64_t n) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     p[i] = 0u;
 }
 
-// w_g v_g for every active point (batch order); 16 zero entries after the end.
+// w_g v_g for every active point (batch order).
 __global__ void k_om(DevPlan d, const double *v, double *om) {
   const int64_t n = d.n_active;
-  for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < n + 16; g += (int64_t)gridDim.x * blockDim.x)
-    om[g] = g < n ? d.pw[g] * v[d.perm[g]] : 0.0;
+  for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < n; g += (int64_t)gridDim.x * blockDim.x)
+    om[g] = d.pw[g] * v[d.perm[g]];
 }
 
 // Panel kinds:
@@ -493,8 +489,8 @@ __global__ void k_om(DevPlan d, const double *v, double *om) {
 //             and split part t of sqrt|w v| times the gradient (formed in
 //             FP64), plane 3 q + t of (Pp / 8) point octets x np functions x
 //             8 points (16 bytes per function and octet)
-// The FP64 and FP32 planes use the 4-point interleave of panel_index (FP32
-// planes counted in floats).
+// The FP64 and FP32 planes use the 4-point interleave above (FP32 planes
+// counted in floats).
 enum { PK_F64 = 0, PK_HS = 1, PK_F32 = 2, PK_SPLIT = 3, PK_BF16 = 4 };
 
 // BF16 (8 significant bits) three-way split of two values a, b at once:
@@ -503,7 +499,6 @@ enum { PK_F64 = 0, PK_HS = 1, PK_F32 = 2, PK_SPLIT = 3, PK_BF16 = 4 };
 // |x - x1 - x2 - x3| <= (2^-24 + 2^-24) |x|.  Part k of both values comes
 // as one word wk (a in the low half, b in the high half), from one packed
 // conversion per part.
-typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
@@ -1557,7 +1552,7 @@ int launch_integrate(const q4c_plan *p, const double *v, int precision, uint32_t
   int rc;
   {
     TimedLaunch tl_(p, Q4C_TIMER_OTHER, s);
-    const unsigned nb = (unsigned)std::min<int64_t>((p->n_active + 16 + 255) / 256, 65535);
+    const unsigned nb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((p->n_active + 255) / 256, 65535));
     hipLaunchKernelGGL(k_om, dim3(nb), dim3(256), 0, s, p->dp, v, p->d_om);
   }
   if ((rc = check_launch("k_om")) != Q4C_OK) return rc;
@@ -1665,7 +1660,7 @@ int launch_integrate_hs(const q4c_plan *p, const double *v, uint32_t flags, doub
   int rc;
   {
     TimedLaunch tl_(p, Q4C_TIMER_OTHER, s);
-    const unsigned nb = (unsigned)std::min<int64_t>((p->n_active + 16 + 255) / 256, 65535);
+    const unsigned nb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((p->n_active + 255) / 256, 65535));
     hipLaunchKernelGGL(k_om, dim3(nb), dim3(256), 0, s, p->dp, v, p->d_om);
   }
   if ((rc = check_launch("k_om")) != Q4C_OK) return rc;

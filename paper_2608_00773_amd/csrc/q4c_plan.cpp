@@ -512,7 +512,6 @@ int build_host(q4c_plan *p, const q4c_basis *b, const q4c_grid *g, const std::ve
     }
     // slots
     int off = 0;
-    int32_t slot0 = (int32_t)p->slot_atom.size();
     for (size_t si = 0; si < rel.size(); ++si) {
       int a = rel[si];
       int nf = p->atom_fn_off[a + 1] - p->atom_fn_off[a];
@@ -536,7 +535,6 @@ int build_host(q4c_plan *p, const q4c_basis *b, const q4c_grid *g, const std::ve
       staging += 5 * (int64_t)nf * (nb_fn - off);
       off += nf;
     }
-    (void)slot0;
     p->batch_slot_off.push_back((int32_t)p->slot_atom.size());
     p->batch_fn_off.push_back((int32_t)p->loc_fn.size());
     for (int ti = 0; ti < nt; ++ti)
@@ -605,8 +603,8 @@ int build_device(q4c_plan *p) {
     if (rc != Q4C_OK) return rc;                               \
   } while (0)
   double *R, *rcut, *coef, *px, *py, *pz, *pw;
-  int32_t *fn_atom, *fn_shlm, *nint, *perm, *bpo, *bfo, *lfn, *lsl, *bso, *sfo, *snf, *pna, *pnb, *pa, *pb;
-  int64_t *coff, *sro, *bpt, *poff, *toff, *pnoff;
+  int32_t *fn_atom, *fn_shlm, *nint, *perm, *bpo, *bfo, *lfn, *bso, *pna, *pnb, *pa, *pb;
+  int64_t *coff, *bpt, *poff, *toff, *pnoff;
   double *sknot;
   UP(p->R, R);
   UP(p->fn_atom, fn_atom);
@@ -624,11 +622,7 @@ int build_device(q4c_plan *p) {
   UP(p->batch_pt_off, bpo);
   UP(p->batch_fn_off, bfo);
   UP(p->loc_fn, lfn);
-  UP(p->loc_slot, lsl);
   UP(p->batch_slot_off, bso);
-  UP(p->slot_fnoff, sfo);
-  UP(p->slot_nfn, snf);
-  UP(p->slot_row_off, sro);
   UP(p->batch_part_off, bpt);
   UP(p->pair_off, poff);
   UP(p->pair_na, pna);
@@ -685,7 +679,7 @@ int build_device(q4c_plan *p) {
   if (rc != Q4C_OK) return rc;
   rc = device_alloc(p, 64, (void **)&p->d_flag);
   if (rc != Q4C_OK) return rc;
-  rc = device_alloc(p, (size_t)(p->n_active + 16) * sizeof(double), (void **)&p->d_om);
+  rc = device_alloc(p, (size_t)std::max<int64_t>(p->n_active, 1) * sizeof(double), (void **)&p->d_om);
   if (rc != Q4C_OK) return rc;
   rc = device_alloc(p, (size_t)q4c::kFold * (p->store_len + 1) * sizeof(double), (void **)&p->d_coef_fold);
   if (rc != Q4C_OK) return rc;
@@ -769,11 +763,7 @@ int build_device(q4c_plan *p) {
   d.batch_pt_off = bpo;
   d.batch_fn_off = bfo;
   d.loc_fn = lfn;
-  d.loc_slot = lsl;
   d.batch_slot_off = bso;
-  d.slot_fnoff = sfo;
-  d.slot_nfn = snf;
-  d.slot_row_off = sro;
   d.batch_part_off = bpt;
   d.stage_far = p->stage_far;
   d.pair_off = poff;
