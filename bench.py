@@ -43,10 +43,12 @@ PREC = {"f64": 0, "split": 1, "f32": 2, "bf16x3": 3, "f64valu": 4}
 # without either).  Any change to those sources makes a figure unknown: it is
 # then reported as null, as it is for the present sources, whose counters have
 # not been taken.
-KERNEL_SOURCES = ("q4c_kernels.hip", "q4c_forward_kernels.hip", "q4c_density_kernels.hip", "q4c_device.h")
+KERNEL_SOURCES = ("q4c_kernels.hip", "q4c_forward_kernels.hip", "q4c_density_kernels.hip", "q4c_device.h",
+                  "q4c_internal.h")
 TRAFFIC = {}
 # The same for k_contract_hs (q4c_integrate_HS) per component and launch shape,
-# keyed by the SHA-256 of q4c_hs_kernels.hip and q4c_device.h.
+# keyed by the SHA-256 of HS_SOURCES.
+HS_SOURCES = ("q4c_hs_kernels.hip", "q4c_device.h", "q4c_internal.h")
 HS_TRAFFIC = {}
 
 
@@ -178,7 +180,7 @@ def bench_hs(wl, timed, steps: int, cpu_frac: float, with_cpu: bool, components=
     import paper_2608_00773_amd as q
     import workload as W
     dev = torch.device("cuda:0")
-    hsha = source_sha("q4c_hs_kernels.hip", "q4c_device.h")
+    hsha = source_sha(*HS_SOURCES)
     t0 = time.perf_counter()
     wl_l = W.with_ket(wl, 7101)
     wl_s = W.small_component(wl_l, 7102)

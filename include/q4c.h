@@ -392,9 +392,8 @@ int q4c_spinor_density_to_scalar(const q4c_plan *plan_large, const q4c_plan *pla
  *   n_g = sum_ij C_ij phi_i phi_j,  d n_g / d x_a = sum_ij C_ij (d_a phi_i phi_j + phi_i d_a phi_j)
  * out_dev (device): [4][n_points] in user order: n, dn/dx, dn/dy, dn/dz
  * (zero outside every support).  FP64 MFMA; fixed-order sums (bitwise
- * repeatable).  Uses the launch shape of density_on_grid; the first call
- * allocates the plan's gradient partials (4x the adjoint partials of the
- * largest pass). */
+ * repeatable).  The first call allocates the batches' coefficient matrices
+ * and the gradient partials of the largest pass. */
 int density_gradient_on_grid(const q4c_plan *plan, const double *coef_dev, double *out_dev, void *stream);
 
 /* Periodic systems (paper Sec. II C).  A plan for a solid holds the atoms of

@@ -95,7 +95,8 @@ __global__ void k_coef_fold(DevPlan d, const double *coef, uint32_t terms, int s
 // points spread over the quads).  120-atom cluster 15.3 -> 9.6 ms, 17-atom
 // molecule 0.52 -> 0.34 ms against ten products from LDS row images with a
 // barrier every 16 points; FP32 W terms, 48 atoms, 2.84 -> 2.11 ms.  The
-// seven MFMAs alone take 6.7 ms (cluster) at their peak rate.
+// seven MFMAs alone take 6.7 ms (cluster) at their peak rate, and the matrix pipe
+// is busy for 72% of the active cycles.
 //
 // F32W (density_on_grid in FP32): the nine W products per K step run on FP32
 // MFMA, coefficients and row values rounded to FP32; the FP32 sums over 32

@@ -39,8 +39,8 @@ constexpr int kJoin = 32;  // points between two joins of the D and M sums (see 
 // panel, 16 bytes (two points) each, one K pair ahead in a second register
 // set.  A wave reads (1 + NB) KB x 4 per 14 NB MFMAs; four waves of a
 // workgroup take consecutive row blocks of one column pair and share its
-// lines in L1 (70% of the reads hit there, 86% of the rest in L2).  Waves
-// never wait for each other.
+// lines in L1 (70% of the reads hit there, 76% of the rest in L2 on the cluster
+// below, 84% on the slab).  Waves never wait for each other.
 //
 // Wso is the difference of sums that grow with the products of D, so these run
 // over kJoin points only and then join the running Ws and Wso.  RMS error of Wso
@@ -56,7 +56,7 @@ constexpr int kJoin = 32;  // points between two joins of the D and M sums (see 
 // batch on average) 14.5 -> 9.4 ms, dense 300-atom slab (319 per batch) 43.3
 // -> 29.0 ms against ten products from 64 x 64 tiles in LDS with a barrier
 // every 8 points; the seven MFMAs alone take 6.7 and 21.3 ms at their peak
-// rate.
+// rate (the matrix pipe is busy for 76 and 78% of the active cycles).
 template <int NB>
 __device__ __forceinline__ void forward_item(const DevPlan &d, int f0, int n, int g0, int P, const double *pb, int rb,
                                              int cb, const double *om, double *staging) {

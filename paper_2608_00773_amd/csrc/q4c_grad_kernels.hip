@@ -137,10 +137,10 @@ __global__ __launch_bounds__(256) void k_grad_cdense(DevPlan d, const int32_t *i
 // three K steps ahead, and the waves of a workgroup (items of one batch) share
 // them in L1 and L2.
 //
-// Bound: the matrix pipe two thirds of the time, and L2 misses: an item reads
+// Bound: the matrix pipe 63% of the time, and L2 misses (66% of its reads): an item reads
 // 512 n bytes each of M and phi per 64 x 64 outputs, and a batch's M (0.9 MB at
 // n = 335) leaves an XCD's L2 between the waves that share it.  40 atoms, both
-// components (155 and 335 functions per batch on average) 4.17 -> 3.31 ms
+// components (155 and 335 functions per batch on average) 4.17 -> 3.29 ms
 // against 64 x 64 tiles in LDS with a barrier every 16 functions; the MFMAs
 // alone take 1.7 ms at their peak rate.  Chunks of at most 48 points with
 // three waves per SIMD took the same time.

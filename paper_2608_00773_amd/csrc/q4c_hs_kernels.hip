@@ -30,7 +30,7 @@ struct OperandHS {
 // Bound: FP64 matrix pipe.  60 atoms, both components (163 and 353 functions
 // per batch on average) 8.6 -> 7.1 ms against 64 x 64 tiles in LDS with a
 // barrier every 16 points; the MFMAs alone take 4.7 ms at their peak rate, 5.3
-// at the clock of this kernel (75% of the active cycles; the other vector
+// at the clock of this kernel (74% of the active cycles; the other vector
 // instructions, 1.4 per MFMA, 8% more).
 template <int NB>
 __device__ __forceinline__ void hs_item(const DevPlan &d, int f0, int n, int g0, int P, const double *pb, int rb, int cb,

@@ -1,6 +1,6 @@
 // HIP kernels of libq4c for CDNA4 (gfx950).
 //
-//  k_tabulate        nao_tabulate: phi and grad phi of a batch's relevant
+//  k_tabulate[_few]  nao_tabulate: phi and grad phi of a batch's relevant
 //                    functions at its points (Eq. 12a, App. B), as the
 //                    panels compute them; FP64 or FP32 hi + lo output.
 //  k_om              w_g v_g per active point (the weighting of Eq. 29).
