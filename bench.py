@@ -35,21 +35,44 @@ PREC = {"f64": 0, "split": 1, "f32": 2, "bf16x3": 3, "f64valu": 4}
 # from two rocprofv3 counter runs (FETCH_SIZE, WRITE_SIZE), each scaled by what
 # the same counter reads for an elementwise copy of 1 GiB (read x2, write x1):
 # the timed launches, and per launch shape the autotuner's trial launches of
-# the same runs (persistent sizes 512 and 1024 read the same bytes).  Keyed by
+# the same runs (both persistent sizes read the same bytes).  Keyed by
 # kernel, the SHA-256 of the kernel sources the counters were taken on
 # (KERNEL_SOURCES), the precision, the workload and the launch shape: work order
 # (0: batch order, which keeps a batch's blocks on one L2; 1: the cost-sorted
 # queue, which does not) and whether the launch is persistent (None for kernels
 # without either).  Any change to those sources makes a figure unknown: it is
-# then reported as null, as it is for the present sources, whose counters have
-# not been taken.
+# then reported as null.
 KERNEL_SOURCES = ("q4c_kernels.hip", "q4c_forward_kernels.hip", "q4c_density_kernels.hip", "q4c_device.h",
                   "q4c_internal.h")
-TRAFFIC = {}
+_KS = "f69df37efd96059251ba1aa1499e5c2b8d6cfa2e26cd11a7ca3f665971b7300e"
+TRAFFIC = {
+    ("k_forward", _KS, "f64", "cluster-120", (0, False)): 20.07e9 + 8.93e9,
+    ("k_forward", _KS, "f64", "cluster-120", (0, True)): 27.37e9 + 8.83e9,
+    ("k_forward", _KS, "f64", "cluster-120", (1, False)): 74.46e9 + 9.23e9,
+    ("k_forward", _KS, "f64", "cluster-120", (1, True)): 91.04e9 + 9.18e9,
+    ("k_density_items", _KS, "f64", "cluster-120", (0, False)): 23.78e9 + 0.49e9,
+    ("k_density_items", _KS, "f64", "cluster-120", (0, True)): 30.02e9 + 0.51e9,
+    ("k_density_items", _KS, "f64", "cluster-120", (1, False)): 91.21e9 + 0.49e9,
+    ("k_density_items", _KS, "f64", "cluster-120", (1, True)): 96.95e9 + 0.51e9,
+    ("k_panel", _KS, "f64", "cluster-120", None): 0.17e9 + 11.49e9,
+    ("k_reduce", _KS, "f64", "cluster-120", None): 7.37e9 + 0.03e9,
+    ("k_contract_b3", _KS, "bf16x3", "cluster-120", (0, False)): 10.72e9 + 6.96e9,
+    ("k_contract_b3", _KS, "bf16x3", "cluster-120", (0, True)): 9.68e9 + 7.15e9,
+    ("k_contract_b3", _KS, "bf16x3", "cluster-120", (1, False)): 52.61e9 + 8.27e9,
+    ("k_contract_b3", _KS, "bf16x3", "cluster-120", (1, True)): 48.07e9 + 8.11e9,
+    ("k_panel", _KS, "bf16x3", "cluster-120", None): 0.17e9 + 9.34e9,
+    ("k_reduce", _KS, "bf16x3", "cluster-120", None): 7.37e9 + 0.03e9,
+}
 # The same for k_contract_hs (q4c_integrate_HS) per component and launch shape,
 # keyed by the SHA-256 of HS_SOURCES.
 HS_SOURCES = ("q4c_hs_kernels.hip", "q4c_device.h", "q4c_internal.h")
-HS_TRAFFIC = {}
+_HS = "92ce3d0d882e85264b7807af7ed1881a2c964ec2dd8d7e9232d1d2ac16132a1d"
+HS_TRAFFIC = {
+    (_HS, "large", 120, (0, False)): 6.962e9 + 3.686e9,
+    (_HS, "large", 120, (0, True)): 17.021e9 + 3.628e9,
+    (_HS, "small", 120, (0, False)): 8.713e9 + 8.509e9,
+    (_HS, "small", 120, (0, True)): 18.643e9 + 8.373e9,
+}
 
 
 def source_sha(*names):
